@@ -80,7 +80,7 @@ def kernel_class(name: str) -> str:
         return "count_l1" if "F32, true" in name else "count_l2"
     if "k_scatter" in name:
         return "scatter_l1" if "F32, true" in name else "scatter_l2"
-    if any(s in name for s in ("k_local_sort", "k_local_words", "k_rfis", "k_rquick", "k_oversize")):
+    if any(s in name for s in ("k_local_sort", "k_local_rank", "k_local_rare", "k_rfis", "k_rquick", "k_oversize")):
         return "local_sort"
     if "k_splitters" in name:
         return "splitters"
@@ -270,8 +270,9 @@ def bench_plain(args, R, torch):
                 caps = {nums[-1]}
             elif "k_rquick" in dom_name:
                 caps = {nums[-2]} if nums[-2] <= 2048 else {3072, 4096}
-            else:
-                caps = {nums[-2] * nums[-1]}
+            else:  # the classes one launch of a shape sorts
+                caps = {64 * 4: {256}, 256 * 4: {1024}, 512 * 8: {2048, 3072, 4096}, 512 * 12: {6144},
+                        1024 * 12: {8192, 12288}}.get(nums[-2] * nums[-1], {nums[-2] * nums[-1]})
             ks_sum = 0
             for s in range(args.steps):
                 R.sort(inputs[s % len(DISTS)], workspace=ws, out=(ko, po))

@@ -237,10 +237,10 @@ typedef struct {
                               bucket size (at most 4): more, smaller levels
                               shorten nothing but lengthen each scatter's runs;
                               the value is stored plus one (1 = none, 0 keeps) */
-  uint32_t class_shape;    /* bit c set: final-size class c (0..8) runs its word
-                              sort with the alternative workgroup shape (twice
-                              the threads, half the keys per thread) -- bit 31
-                              must be set for the mask to be taken (0 keeps) */
+  uint32_t class_shape;    /* bit c: a hint for final-size class c (0..8), stored
+                              and returned; the local sorts have one workgroup
+                              shape per class and do not read it.  Bit 31 must
+                              be set for the mask to be taken (0 keeps) */
 } rsort_tuning;
 
 int rsort_get_tuning(rsort_tuning *out);

@@ -73,13 +73,6 @@ struct BoolC {
   static constexpr bool value = B;
 };
 
-// A value the caller knows to be the same in every lane (read from LDS, say),
-// moved to a scalar register.
-__device__ __forceinline__ uint32_t uniform(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ uint64_t uniform64(uint64_t x) {
-  return ((uint64_t)uniform((uint32_t)(x >> 32)) << 32) | uniform((uint32_t)x);
-}
-
 // The chained scan's per-chunk status words start at zero on every level.
 __device__ __forceinline__ void scan_flags_clear(const Work& w, uint32_t t, uint32_t nt) {
   for (uint64_t i = t; i < w.scan_blocks; i += nt) w.scan_flags[i] = 0ull;
@@ -254,9 +247,6 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(Work w, int lev, uint32_t
   const int cur = lev & 1;
   const uint32_t m = (uint32_t)min((uint64_t)w.ctl->big_count[cur], w.big_max);
   const BigSeg* B = w.big[cur];
-  // the first level of a segmented call: the class lists hold only the
-  // user segments routed so far (k_init); the levels append theirs after
-  if (lev == 0 && threadIdx.x < (unsigned)kNumClasses) w.ctl->class_in[threadIdx.x] = w.ctl->class_count[threadIdx.x];
   if (threadIdx.x == 0) {
     const uint32_t runs = w.ctl->runs;
     const bool short_runs = glog_small && runs && w.n / runs < kShortRun;
@@ -964,21 +954,13 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(Work w) {
 }
 
 // Exclusive scan of a tile histogram: one value per thread, non-zero only
-// in the first kMaxK threads (the bins).  Rows of 16 lanes are scanned with
-// DPP row shifts, rows are joined through lane reads, and the at most
-// kMaxK / 64 bin waves through LDS (tmp: kMaxK / 64 words), with one
-// barrier.  Called by every thread of the block.
+// in the first kMaxK threads (the bins).  Waves are scanned with DPP row
+// shifts, and the at most kMaxK / 64 bin waves joined through LDS (tmp: kMaxK
+// / 64 words), with one barrier.  Called by every thread of the block.
 __device__ __forceinline__ uint32_t bins_excl_scan(uint32_t v, uint32_t* tmp) {
   constexpr uint32_t NW = kMaxK / kWave;
   const uint32_t lane = lane_id(), w = threadIdx.x / kWave;
-  uint32_t inc = v;
-  inc += dpp_u32<0x111>(inc);  // row_shr:1 (lanes without a source add 0)
-  inc += dpp_u32<0x112>(inc);  // row_shr:2
-  inc += dpp_u32<0x114>(inc);  // row_shr:4
-  inc += dpp_u32<0x118>(inc);  // row_shr:8
-  const uint32_t r0 = lane_u32(inc, 15), r1 = lane_u32(inc, 31), r2 = lane_u32(inc, 47);
-  const uint32_t row = lane >> 4;
-  inc += (row > 0 ? r0 : 0u) + (row > 1 ? r1 : 0u) + (row > 2 ? r2 : 0u);
+  const uint32_t inc = wave_incl_scan_dpp(v);
   if (w < NW && lane == kWave - 1) tmp[w] = inc;
   __syncthreads();
   uint32_t off = 0;
@@ -1424,16 +1406,13 @@ static inline uint32_t grid_for(uint64_t work, uint32_t per_cu) {
 
 
 
-// Algorithm of each size class: RFIS, RQuick or the LDS merge sort.
-template <typename K, bool F32, bool PAY>
-static int launch_class_sort(int c, const Work& w, const K* kin, const uint32_t* pay_in, K* kout, uint32_t* perm_out,
-                             uint32_t* pay_out, uint64_t cap_c, hipStream_t st, const Tuning& t) {
-  const int cb = c & 0xFF;  // c may carry kDirect
-  if (h_class_max[cb] <= t.rfis_max)
-    return launch_rfis_class<K, F32, PAY>(c, w, kin, pay_in, kout, perm_out, pay_out, cap_c, st);
-  if (h_class_max[cb] <= t.rquick_max)
-    return launch_rquick_class<K, F32, PAY>(c, w, kin, pay_in, kout, perm_out, pay_out, cap_c, st);
-  return launch_merge_class<K, F32, PAY>(c, w, kin, pay_in, kout, perm_out, pay_out, cap_c, st);
+// Algorithm of a size class: RFIS (classes 0 to 2) or RQuick (classes 3 to 5)
+// up to the tuning's thresholds, else the ranking in bins.
+enum class ClassAlgo { kRank, kRfis, kRquick };
+static ClassAlgo class_algo(int c, const Tuning& t) {
+  if (h_class_max[c] <= t.rfis_max) return c <= 2 ? ClassAlgo::kRfis : ClassAlgo::kRank;
+  if (h_class_max[c] <= t.rquick_max) return c >= 3 && c <= 5 ? ClassAlgo::kRquick : ClassAlgo::kRank;
+  return ClassAlgo::kRank;
 }
 
 template <typename K, bool F32, bool PAY>
@@ -1456,15 +1435,20 @@ static int enqueue_typed(const void* keys_in, const uint32_t* pay_in, const uint
     // the whole input fits one workgroup: one launch, no segment lists
     int c = 0;
     while (n > h_class_max[c]) c++;
-    return launch_class_sort<K, F32, PAY>(c | kDirect, w, kin, pay_in, kout, perm_out, pay_out, 1, st, t);
+    const ClassAlgo al = class_algo(c, t);
+    if (al == ClassAlgo::kRfis)
+      return launch_rfis_class<K, F32, PAY>(c | kDirect, w, kin, pay_in, kout, perm_out, pay_out, 1, st);
+    if (al == ClassAlgo::kRquick)
+      return launch_rquick_class<K, F32, PAY>(c | kDirect, w, kin, pay_in, kout, perm_out, pay_out, 1, st);
+    return launch_direct<K, F32, PAY>(c, w, kin, pay_in, kout, perm_out, pay_out, st);
   }
   // A single-level plain sort with at most about two final buckets per CU
-  // routes all of them to the class kernel for twice the target size (and
-  // the one above it), so the local sorts run in one or two launches.
+  // routes all of them to the largest class group that runs two workgroups
+  // per CU (and the class above it), so the local sorts run in one or two
+  // launches.
   uint32_t cmin = 0;
   if (!seg_off && levels == 1 && n <= (uint64_t)target * 2 * num_cu()) {
-    const uint32_t want = std::min<uint32_t>(2 * target, cap);
-    while (cmin + 2 < (uint32_t)kNumClasses && h_class_max[cmin] < want) cmin++;
+    while (cmin < 7 && h_class_max[cmin] < cap) cmin++;
   }
   // a single-level sort of few buckets (cmin > 0) is latency-bound on its
   // one-workgroup sample sort: 16 samples per bucket keep its buckets
@@ -1541,15 +1525,21 @@ static int enqueue_typed(const void* keys_in, const uint32_t* pay_in, const uint
 
   // final segments by size class (a class can only be non-empty if its lower
   // bound is below cap)
+  uint32_t ranked = 0;  // classes ranked in bins
   for (int c = (int)cmin; c < kNumClasses - 1; c++) {
     if (c > 0 && h_class_max[c - 1] >= cap) break;
-    const int kinds = levels == 0 ? kInputOnly : (num_segs > 1 ? kMixed : 0);
-    const int rc = launch_class_sort<K, F32, PAY>(c | kinds, w, kin, pay_in, kout, perm_out, pay_out, w.cls_cap[c],
-                                                  st, t);
+    const ClassAlgo al = class_algo(c, t);
+    int rc = 0;
+    if (al == ClassAlgo::kRank)
+      ranked |= 1u << c;
+    else if (al == ClassAlgo::kRfis)
+      rc = launch_rfis_class<K, F32, PAY>(c, w, kin, pay_in, kout, perm_out, pay_out, w.cls_cap[c], st);
+    else
+      rc = launch_rquick_class<K, F32, PAY>(c, w, kin, pay_in, kout, perm_out, pay_out, w.cls_cap[c], st);
     if (rc) return rc;
   }
   {
-    const int rc = launch_local_fallbacks<K, F32, PAY>(w, cap, kin, pay_in, kout, perm_out, pay_out, st);
+    const int rc = launch_local_ranks<K, F32, PAY>(ranked, w, kin, pay_in, kout, perm_out, pay_out, st);
     if (rc) return rc;
   }
   {

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace rs {
 
 constexpr int kMaxLogK = 9;               // at most 512 buckets per level
@@ -32,11 +34,9 @@ struct FinalSeg {
   uint64_t start;
   uint32_t len;
   uint32_t src;  // low byte: 0 caller input (positions implicit), 1 buffer A, 2 buffer B;
-                 // kPairsFlag: handed from the word sort to the pair sort;
-                 // kMergeFlag: handed from the binned word sort to the merged one
+                 // kPairsFlag: handed from the ranking in bins to the merge sort
 };
 constexpr uint32_t kPairsFlag = 0x100;
-constexpr uint32_t kMergeFlag = 0x200;
 
 // Control block at the start of the workspace (all counters device-side).
 struct Ctl {
@@ -49,7 +49,6 @@ struct Ctl {
   uint32_t runs;                   // (tile, bucket) runs the first level's scatter wrote
   uint32_t glog;                   // log2 keys per tile group of the levels after the first (0: as planned)
   uint32_t ids0;                   // 1: the first level (one segment) passes bucket ids from count to scatter
-  uint32_t class_in[kNumClasses];  // segmented calls: user segments at the front of each class list
   uint32_t queue[2][8];            // per-XCD tile-group queues of the count and scatter passes
   uint32_t class_count[kNumClasses];  // final segments per size class (last = oversize)
   uint32_t level_max[kMaxLevels];  // largest bucket created per level
@@ -100,6 +99,13 @@ __device__ __forceinline__ uint32_t get_bucket_id(const uint8_t* ids, uint64_t s
   return logk <= 8 ? (uint32_t)ids[2 * s + r] : (uint32_t)((const uint16_t*)(ids + 2 * s))[r];
 }
 
+// a[i] with a scalar base and a 32-bit byte offset (i * sizeof(T) < 2^32).
+template <typename T>
+__device__ __forceinline__ T& at32(T* a, uint32_t i) {
+  using C = std::conditional_t<std::is_const<T>::value, const char, char>;
+  return *reinterpret_cast<T*>(reinterpret_cast<C*>(a) + (uint32_t)(i * (uint32_t)sizeof(T)));
+}
+
 // The element buffers of the levels interleave each element's ordinal key
 // and input position in one record of 32-bit words (key low, key high for
 // 64-bit keys, then the position), so that one memory instruction moves a
@@ -129,6 +135,18 @@ struct BufView {
       v = c;
     }
   }
+  // get with a scalar base and a 32-bit byte offset
+  __device__ __forceinline__ void get32(uint32_t i, K& k, uint32_t& v) const {
+    struct Rec {
+      uint32_t x[W];
+    };
+    const Rec r = at32(reinterpret_cast<const Rec*>(p), i);
+    if constexpr (sizeof(K) == 8)
+      k = ((uint64_t)r.x[1] << 32) | r.x[0];
+    else
+      k = r.x[0];
+    v = r.x[W - 1];
+  }
   __device__ __forceinline__ void put(uint64_t i, K k, uint32_t v) const {
     uint32_t* r = p + i * W;
     r[0] = (uint32_t)k;
@@ -145,15 +163,6 @@ __device__ __forceinline__ BufView<K> buf_view(const Work& w, int b) {
 // plain call as one segment in a single launch.  The kernels then receive a
 // negative class argument.
 constexpr int kDirect = 0x100;
-// Launcher flag: no sample-sort level ran, so every final segment lies in the
-// caller's input (positions implicit) and the class kernels need no table of
-// positions.
-constexpr int kInputOnly = 0x200;
-// Launcher flag: final segments of both kinds (a segmented call where some
-// user segments were split by levels): the class kernels run once for the
-// input segments and once for the buffer segments.
-constexpr int kMixed = 0x400;
-
 // Final segments of class cls (cls < 0: the direct single-segment mode).
 __device__ __forceinline__ uint32_t final_count(const Work& w, int cls) {
   if (cls < 0) return 1u;

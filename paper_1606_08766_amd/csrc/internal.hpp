@@ -20,7 +20,7 @@ struct Tuning {
   uint32_t tile_log2 = 13;  // scatter tile: 2^tile_log2 keys
   uint32_t force_fallback = 0;
   uint32_t extra_levels = 0;  // sample-sort levels beyond the fewest needed
-  uint32_t class_shape = 0;   // bit c: class c uses its alternative workgroup shape
+  uint32_t class_shape = 0;   // stored for the caller only (rsort.h)
 };
 
 Tuning& tuning();
@@ -32,11 +32,8 @@ int enqueue_sort(int kt, const void* keys_in, const uint32_t* pay_in, const uint
                  hipStream_t st);
 size_t workspace_bytes(int kt, uint64_t n, uint32_t num_segs, bool pay);
 
-// Per-class local sorts (final segments of class c, read from the class list
-// in the workspace).  Merge sort: engine.hip; RFIS / RQuick: small.hip.
-template <typename K, bool F32, bool PAY>
-int launch_merge_class(int c, const Work& w, const K* kin, const uint32_t* pay_in, K* kout, uint32_t* perm_out,
-                       uint32_t* pay_out, uint64_t cap_c, hipStream_t st);
+// Per-class local sorts by RFIS and RQuick (final segments of class c, read
+// from the class list in the workspace): small.hip.
 template <typename K, bool F32, bool PAY>
 int launch_rfis_class(int c, const Work& w, const K* kin, const uint32_t* pay_in, K* kout, uint32_t* perm_out,
                       uint32_t* pay_out, uint64_t cap_c, hipStream_t st);
@@ -44,11 +41,16 @@ template <typename K, bool F32, bool PAY>
 int launch_rquick_class(int c, const Work& w, const K* kin, const uint32_t* pay_in, K* kout, uint32_t* perm_out,
                         uint32_t* pay_out, uint64_t cap_c, hipStream_t st);
 
-// Segments the word sorts handed over (merge sort of words, then pair sort),
-// launched once after all classes (local.hip).
+// A plain call of one final segment, of class c (local.hip).
 template <typename K, bool F32, bool PAY>
-int launch_local_fallbacks(const Work& w, uint32_t cap, const K* kin, const uint32_t* pay_in, K* kout,
-                           uint32_t* perm_out, uint32_t* pay_out, hipStream_t st);
+int launch_direct(int c, const Work& w, const K* kin, const uint32_t* pay_in, K* kout, uint32_t* perm_out,
+                  uint32_t* pay_out, hipStream_t st);
+
+// The final segments of the classes in the bit mask, and then those that were
+// handed over to the merge sort (local.hip).
+template <typename K, bool F32, bool PAY>
+int launch_local_ranks(uint32_t classes, const Work& w, const K* kin, const uint32_t* pay_in, K* kout,
+                       uint32_t* perm_out, uint32_t* pay_out, hipStream_t st);
 
 // Global-memory fallback sort of final segments longer than cap (local.hip).
 template <typename K, bool F32, bool PAY>

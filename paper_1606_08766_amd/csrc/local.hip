@@ -25,489 +25,500 @@ struct Shape {
 
 
 // ---------------------------------------------------------------------------
-// The final segments a class kernel sorts.  flag 0: segment q = blockIdx.x +
-// i * gridDim.x of class cls.  Otherwise (the launches after all classes):
-// every segment of every class whose src carries `flag`; each thread checks
-// one segment and the flagged ones are collected in LDS (s_list holds THREADS
-// entries), so that the search is parallel rather than a chain of dependent
-// loads.  body(cc, q) runs on every thread of the block.
-template <int THREADS, typename F>
-__device__ __forceinline__ void for_each_segment(const Work& w, int cls, uint32_t flag, uint32_t* s_list,
-                                                 uint32_t& s_n, F&& body, int part = 0) {
-  if (!flag) {
-    // part 1 / 2: a mixed call's user segments / level segments.  k_init
-    // routes every user segment before any level runs, so they are the
-    // first class_in entries of each class list.
-    uint32_t q0 = 0, q1 = final_count(w, cls);
-    if (part && cls >= 0) {
-      const uint32_t nin = min(w.ctl->class_in[cls], q1);
-      if (part == 1)
-        q1 = nin;
-      else
-        q0 = nin;
-    }
-    for (uint32_t q = q0 + blockIdx.x; q < q1; q += gridDim.x) body(cls, q);
-    return;
+// One segment sorted in LDS as (key, position) pairs by the merge sort: exact
+// for every input, whatever its keys.  len <= THREADS * ITEMS.  Called by
+// every thread of the block; ends with a barrier.
+template <typename K, bool F32, bool PAY, int THREADS, int ITEMS>
+__device__ __forceinline__ void sort_pairs(const Work& w, const FinalSeg& f, const LdsArr<K>& sa, const K* in_keys,
+                                           const uint32_t* in_pay, K* keys_out, uint32_t* perm_out,
+                                           uint32_t* pay_out) {
+  const BufView<K> sb{f.src ? w.buf_rec[f.src - 1] : nullptr};
+  const uint32_t* srcp = f.src ? w.buf_pay[f.src - 1] : in_pay;
+  K k[ITEMS];
+  uint32_t v[ITEMS], p[ITEMS];
+#pragma unroll
+  for (int i = 0; i < ITEMS; i++) {
+    // thread t takes logical elements t*ITEMS+i; load striped for coalescing
+    // and let the first sort round place them (any input order is valid).
+    const uint32_t j = i * THREADS + threadIdx.x;
+    k[i] = KMax<K>::v;
+    v[i] = j < f.len ? j : kPadIdx;
+    p[i] = j;
   }
-  for (int cc = 0; cc <= kNumClasses - 2; cc++) {
-    const uint32_t cnt = final_count(w, cc);
-    for (uint32_t q0 = blockIdx.x * THREADS; q0 < cnt; q0 += gridDim.x * THREADS) {
-      if (threadIdx.x == 0) s_n = 0;
-      __syncthreads();
-      const uint32_t q = q0 + threadIdx.x;
-      if (q < cnt && (w.cls[cc][q].src & flag)) s_list[atomicAdd(&s_n, 1u)] = q;
-      __syncthreads();
-      const uint32_t n = s_n;
-      for (uint32_t k = 0; k < n; k++) body(cc, s_list[k]);
-      __syncthreads();
+  // one source per segment (uniform), so each branch issues all its loads
+  // before any is used
+  if (f.src) {
+#pragma unroll
+    for (int i = 0; i < ITEMS; i++)
+      if (i * THREADS + threadIdx.x < f.len) sb.get(f.start + i * THREADS + threadIdx.x, k[i], v[i]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < ITEMS; i++)
+      if (i * THREADS + threadIdx.x < f.len) k[i] = in_keys[f.start + i * THREADS + threadIdx.x];  // raw bits
+  }
+  if constexpr (F32) {
+    if (!f.src) {
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++)
+        if (i * THREADS + threadIdx.x < f.len) k[i] = ord_of<K, F32>(k[i]);
     }
   }
+  lds_merge_sort<K, THREADS, ITEMS, PAY>(k, v, p, sa);
+#pragma unroll
+  for (int i = 0; i < ITEMS; i++) {
+    const int q = lpad(threadIdx.x * ITEMS + i);
+    sa.put(q, k[i], v[i]);
+    if constexpr (PAY) sa.p[q] = p[i];
+  }
+  __syncthreads();
+  if constexpr (PAY) {
+    // the payloads are gathered before any output store (a load issued
+    // after stores waits for them)
+    uint32_t pv[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; i++) {
+      const uint32_t j = i * THREADS + threadIdx.x;
+      pv[i] = j < f.len ? srcp[f.start + sa.p[lpad(j)]] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < ITEMS; i++) {
+      const uint32_t j = i * THREADS + threadIdx.x;
+      if (j < f.len) {
+        const int q = lpad(j);
+        keys_out[f.start + j] = to_output<K, F32>(sa.key(q));
+        if (perm_out) perm_out[f.start + j] = sa.v[q];
+        pay_out[f.start + j] = pv[i];
+      }
+    }
+  } else {
+    for (uint32_t j = threadIdx.x; j < f.len; j += THREADS) {
+      const int q = lpad(j);
+      keys_out[f.start + j] = to_output<K, F32>(sa.key(q));
+      if (perm_out) perm_out[f.start + j] = sa.v[q];
+    }
+  }
+  __syncthreads();
 }
 
-// ---------------------------------------------------------------------------
-// Final segments of one size class: one workgroup each, sorted in LDS as
-// (key, position) pairs.  FLAGGED: the segments of every class that the word
-// sort below handed over (kPairsFlag); the shape then fits the largest class.
-template <typename K, bool F32, bool PAY, int THREADS, int ITEMS, bool FLAGGED = false>
-__global__ __launch_bounds__(THREADS) void k_local_sort(Work w, int cls, const K* in_keys, const uint32_t* in_pay,
-                                                        K* keys_out, uint32_t* perm_out, uint32_t* pay_out) {
-  constexpr int N = THREADS * ITEMS;
-  constexpr int NP = lpad_size(N);
+// A whole plain call that fits one workgroup, sorted in one launch.
+template <typename K, bool F32, bool PAY, int THREADS, int ITEMS>
+__global__ __launch_bounds__(THREADS) void k_local_sort(Work w, const K* in_keys, const uint32_t* in_pay, K* keys_out,
+                                                        uint32_t* perm_out, uint32_t* pay_out) {
+  constexpr int NP = lpad_size(THREADS * ITEMS);
   __shared__ uint32_t s_lo[NP];
   __shared__ uint32_t s_hi[sizeof(K) == 8 ? NP : 1];
   __shared__ uint32_t s_v[NP];
   __shared__ uint32_t s_p[PAY ? NP : 1];
-  const LdsArr<K> sa{s_lo, s_hi, s_v, s_p};
-  direct_reset(w, cls);
-  __shared__ uint32_t s_list[FLAGGED ? THREADS : 1];
-  __shared__ uint32_t s_n;
-  for_each_segment<THREADS>(w, cls, FLAGGED ? kPairsFlag : 0u, s_list, s_n, [&](int cc, uint32_t q) {
-    FinalSeg f = final_at(w, cc, q);
-    if (FLAGGED && !(f.src & kPairsFlag)) return;  // uniform
-    f.src &= 0xFFu;
-    const BufView<K> sb{f.src ? w.buf_rec[f.src - 1] : nullptr};
-    const uint32_t* srcp = f.src ? w.buf_pay[f.src - 1] : in_pay;
-    K k[ITEMS];
-    uint32_t v[ITEMS], p[ITEMS];
-#pragma unroll
-    for (int i = 0; i < ITEMS; i++) {
-      // thread t takes logical elements t*ITEMS+i; load striped for coalescing
-      // and let the first sort round place them (any input order is valid).
-      const uint32_t j = i * THREADS + threadIdx.x;
-      k[i] = KMax<K>::v;
-      v[i] = j < f.len ? j : kPadIdx;
-      p[i] = j;
-    }
-    // one source per segment (uniform), so each branch issues all its loads
-    // before any is used
-    if (f.src) {
-#pragma unroll
-      for (int i = 0; i < ITEMS; i++)
-        if (i * THREADS + threadIdx.x < f.len) sb.get(f.start + i * THREADS + threadIdx.x, k[i], v[i]);
-    } else {
-#pragma unroll
-      for (int i = 0; i < ITEMS; i++)
-        if (i * THREADS + threadIdx.x < f.len) k[i] = in_keys[f.start + i * THREADS + threadIdx.x];  // raw bits
-    }
-    if constexpr (F32) {
-      if (!f.src) {
-#pragma unroll
-        for (int i = 0; i < ITEMS; i++)
-          if (i * THREADS + threadIdx.x < f.len) k[i] = ord_of<K, F32>(k[i]);
-      }
-    }
-    lds_merge_sort<K, THREADS, ITEMS, PAY>(k, v, p, sa);
-#pragma unroll
-    for (int i = 0; i < ITEMS; i++) {
-      const int q = lpad(threadIdx.x * ITEMS + i);
-      sa.put(q, k[i], v[i]);
-      if constexpr (PAY) s_p[q] = p[i];
-    }
-    __syncthreads();
-    if constexpr (PAY) {
-      // the payloads are gathered before any output store (a load issued
-      // after stores waits for them)
-      uint32_t pv[ITEMS];
-#pragma unroll
-      for (int i = 0; i < ITEMS; i++) {
-        const uint32_t j = i * THREADS + threadIdx.x;
-        pv[i] = j < f.len ? srcp[f.start + s_p[lpad(j)]] : 0u;
-      }
-#pragma unroll
-      for (int i = 0; i < ITEMS; i++) {
-        const uint32_t j = i * THREADS + threadIdx.x;
-        if (j < f.len) {
-          const int q = lpad(j);
-          keys_out[f.start + j] = to_output<K, F32>(sa.key(q));
-          if (perm_out) perm_out[f.start + j] = s_v[q];
-          pay_out[f.start + j] = pv[i];
-        }
-      }
-    } else {
-      for (uint32_t j = threadIdx.x; j < f.len; j += THREADS) {
-        const int q = lpad(j);
-        keys_out[f.start + j] = to_output<K, F32>(sa.key(q));
-        if (perm_out) perm_out[f.start + j] = s_v[q];
-      }
-    }
-    __syncthreads();
-  });
+  direct_reset(w, -1);
+  sort_pairs<K, F32, PAY, THREADS, ITEMS>(w, final_at(w, -1, 0), LdsArr<K>{s_lo, s_hi, s_v, s_p}, in_keys, in_pay,
+                                          keys_out, perm_out, pay_out);
 }
 
 // ---------------------------------------------------------------------------
-// Bins of the word sort: a segment's words are distinct, so each word's rank
-// is the number of smaller words.  The words are first distributed into 2^LB
-// bins by the top bits of (word - lower bound), which keeps the bins in word
-// order; a word's rank is then the start of its bin plus the number of smaller
-// words inside the bin, found by comparing against the bin's words only.  On
-// the key distributions the sample sort leaves in a final segment (near
-// uniform over its range) a bin holds about 3 to 8 words (up to 16 in the
-// instances of at most 4096 words), so this takes far
-// fewer steps than a merge sort's log2(len) rounds.  The ranking costs about
-// the sum over the bins of size^2 compares; where that exceeds kRankBudget per
-// word (runs of equal keys, keys clustered far apart) the segment is left to
-// the merge sort.
+// Final segments ranked in bins: one workgroup per segment, its elements held
+// in registers from the load to the output, LDS used for 32-bit words that
+// rank them and then to bring them into rank order.
+//
+// With d = key - lower bound of the keys (rb bits) and x = position - smallest
+// position (ib bits), the element's word is the top 32 bits of the rb + ib bit
+// number (d, x), which orders like (key, position).  Its top LB bits are the
+// bin, of which there is one per element of a full segment.  A rank is the
+// start of the bin plus the number of smaller words in it:
+//   count    one LDS atomic per element gives its place in its bin,
+//   scan     the bin starts, and the sum of squared bin sizes (the compares
+//            ranking will take),
+//   place    the words, bin by bin,
+//   rank     every thread compares its own elements with their bins' words
+//            (and may read past a bin's end: later bins hold larger words).
+// Equal words of different elements (keys that differ in few low bits, or
+// equal keys near to each other) get equal ranks, which leaves the sum of all
+// ranks below len (len - 1) / 2: such a segment (uniform test) goes on with
+// the next 32 bits of (d, x) among its equals (rank_ties).  A segment whose
+// ranking would take more than kRankBudget compares per element (keys
+// clustered far apart) is marked kPairsFlag and left to k_local_rare.
+//
+// Few distinct keys need no case of their own: d then has few bits and the
+// bins go on with the position.
+//
+// Bound: VALU issue (a wave's instruction occupies its SIMD for four cycles)
+// and HBM.  Hence 32-bit words computed once, one bin per element (few
+// compares), and element minima by their upper halves first.  LDS is 8 B per
+// element: words and bins share the memory of the staging area.
 constexpr uint32_t kRankBudget = 128;
 
-// Bin phase: c holds the element words, element j = i * THREADS + t as c[i];
-// elements j >= len are not used.  Counts the words of each bin (bin[0 .. S]
-// are zero on entry; r receives each word's place among its bin's words, in
-// no particular order), turns the counts into bin starts (bin[S] = len) and
-// returns, uniformly over the block, whether the ranking fits kRankBudget.
-// The first wave scans the bins (S / 64 per lane) and leaves the ranking
-// cost in *cost.
-template <int THREADS, int ITEMS, int LB>
-__device__ __forceinline__ bool bin_count(const uint64_t (&c)[ITEMS], uint32_t len, uint32_t* bin, uint32_t* cost,
-                                          int t, const BinMap& bm, uint32_t (&r)[ITEMS]) {
-  constexpr int S = 1 << LB;
-  constexpr int PL = S / kWave;  // bins per lane of the scanning wave
-  static_assert(PL >= 1, "at least one bin per lane");
+// Exclusive scan of the THREADS * BPT bin counts in place (bin is 16-byte
+// aligned, BPT a multiple of 4); returns the sum of their squares, uniformly.
+template <int THREADS, int BPT>
+__device__ __forceinline__ uint32_t bins_scan(uint32_t* bin, uint32_t len, uint32_t* tmp, int t) {
+  constexpr int NW = THREADS / kWave;
+  static_assert(BPT % 4 == 0 && NW <= 16, "bins are read by fours, the waves' sums fit one row");
+  const uint32_t lane = lane_id(), wv = t / kWave;
+  uint4* const b4 = reinterpret_cast<uint4*>(bin) + t * (BPT / 4);
+  uint32_t sum = 0, sq = 0;
 #pragma unroll
-  for (int i = 0; i < ITEMS; i++) {
-    r[i] = 0;
-    if ((uint32_t)(i * THREADS + t) < len) r[i] = atomicAdd(&bin[bm(c[i])], 1u);
+  for (int k = 0; k < BPT / 4; k++) {
+    const uint4 x = b4[k];
+    sum += x.x + x.y + x.z + x.w;
+    sq += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
+  }
+  const uint32_t inc = wave_incl_scan_dpp(sum), sqi = wave_incl_scan_dpp(sq);
+  if (lane == kWave - 1) {
+    tmp[wv] = inc;
+    tmp[NW + wv] = sqi;
   }
   __syncthreads();
-  if (t < kWave) {
-    // one scan of (sum of squared bin sizes, bin size): the low half gives
-    // the bin starts, the high half's total the ranking cost (both fit 32 bits)
-    uint64_t v = 0;
-#pragma unroll 4
-    for (int k = 0; k < PL; k++) {
-      const uint32_t x = bin[t * PL + k];
-      v += ((uint64_t)(x * x) << 32) | x;
-    }
-    const uint64_t inc = wave_incl_scan<uint64_t>(v);
-    uint32_t e = (uint32_t)(inc - v);
-#pragma unroll 4
-    for (int k = 0; k < PL; k++) {  // the counts are read again: fewer registers
-      const uint32_t x = bin[t * PL + k];
-      bin[t * PL + k] = e;
-      e += x;
-    }
-    if (t == kWave - 1) {
-      bin[S] = len;
-      *cost = (uint32_t)(inc >> 32);
-    }
+  // every wave scans the waves' sums in one row of lanes
+  const uint32_t ws = row_incl_scan_dpp((int)lane < NW ? tmp[lane] : 0u);
+  const uint32_t wq = row_incl_scan_dpp((int)lane < NW ? tmp[NW + lane] : 0u);
+  const uint32_t uw = uniform(wv);
+  const uint32_t off = uw ? lane_u32(ws, (int)uw - 1) : 0u, cost = lane_u32(wq, NW - 1);
+  uint32_t e = off + inc - sum;
+#pragma unroll
+  for (int k = 0; k < BPT / 4; k++) {  // the counts are read again: fewer registers
+    uint4 x = b4[k];
+    const uint32_t e1 = e + x.x, e2 = e1 + x.y, e3 = e2 + x.z;
+    b4[k] = make_uint4(e, e1, e2, e3);
+    e = e3 + x.w;
   }
+  if (t == THREADS - 1) bin[THREADS * BPT] = len;
   __syncthreads();
-  return *cost <= kRankBudget * len;
+  return cost;
 }
 
-// Rank phase, after bin_count succeeded: places the words in their bins (in
-// wb, unpadded), ranks every word and writes the sorted words to lo/hi at
-// lpad(rank); wb and lo/hi are the same LDS memory, and the caller
-// synchronises before reading lo/hi.  wb holds at least len + 3 words (ranking
-// reads up to three words past a bin's end; the three words past len are set
-// to all ones, larger than any word).
-template <int THREADS, int ITEMS, int LB>
-__device__ __forceinline__ void bin_rank(const uint64_t (&c)[ITEMS], const uint32_t (&r)[ITEMS], uint32_t len,
-                                         uint64_t* wb, uint32_t* lo, uint32_t* hi, const uint32_t* bin, int t,
-                                         const BinMap& bm) {
+// Ranks of a segment with equal words.  Elements of equal rank r are a group
+// of m that owns the ranks r .. r + m - 1; `rounds` times, the groups are
+// ordered by the next 32 bits limb(round, i).  fr and cnt hold N values each
+// and are free on entry and exit (a barrier on both sides).
+template <int THREADS, int ITEMS, typename LimbFn>
+__device__ __forceinline__ void rank_ties(uint32_t* fr, uint32_t* cnt, uint32_t len, uint32_t (&rank)[ITEMS],
+                                          int rounds, LimbFn limb, int t) {
+#pragma unroll 1
+  for (int round = 0; round < rounds; round++) {
 #pragma unroll
-  for (int i = 0; i < ITEMS; i++) {
-    if ((uint32_t)(i * THREADS + t) < len) wb[bin[bm(c[i])] + r[i]] = c[i];
-  }
-  if (t < 3) wb[len + t] = ~0ull;
-  __syncthreads();
-  // rank of the word at each position: words of later bins and the all-ones
-  // words are larger, so the count may run past the bin's end
-  uint32_t rk[ITEMS];
-  uint64_t wv[ITEMS];
+    for (int i = 0; i < ITEMS; i++) cnt[i * THREADS + t] = 0;
+    __syncthreads();
+    uint32_t pl[ITEMS];
 #pragma unroll
-  for (int i = 0; i < ITEMS; i++) {
-    const uint32_t p = i * THREADS + t;  // < N: inside wb
-    const uint64_t w = wb[p];
-    uint32_t db = bm(w);
-    db = p < len ? db : 0u;
-    const uint32_t s0 = bin[db];
-    const uint32_t s1 = p < len ? bin[db + 1] : s0;
-    uint32_t less = 0;
-    for (uint32_t q = s0; q < s1; q += 4) {
-      less += wb[q] < w ? 1u : 0u;
-      less += wb[q + 1] < w ? 1u : 0u;
-      less += wb[q + 2] < w ? 1u : 0u;
-      less += wb[q + 3] < w ? 1u : 0u;
+    for (int i = 0; i < ITEMS; i++) {
+      pl[i] = 0;
+      if (t < (int)len - i * THREADS) pl[i] = atomicAdd(&cnt[rank[i]], 1u);
     }
-    rk[i] = s0 + less;
-    wv[i] = w;
-  }
-  __syncthreads();
+    __syncthreads();
 #pragma unroll
-  for (int i = 0; i < ITEMS; i++) {
-    if ((uint32_t)(i * THREADS + t) < len) {
-      const int qq = lpad((int)rk[i]);
-      lo[qq] = (uint32_t)wv[i];
-      hi[qq] = (uint32_t)(wv[i] >> 32);
+    for (int i = 0; i < ITEMS; i++)
+      if (t < (int)len - i * THREADS) fr[rank[i] + pl[i]] = limb(round, i);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ITEMS; i++) {
+      if (t < (int)len - i * THREADS) {
+        const uint32_t m = cnt[rank[i]], v = limb(round, i), r0 = rank[i];
+#pragma unroll 1
+        for (uint32_t q = 0; m > 1 && q < m; q++) rank[i] += fr[r0 + q] < v ? 1u : 0u;
+      }
     }
+    __syncthreads();
+  }
+}
+
+// Sorts the final segments of the classes in a bit mask, the longest class
+// first.
+template <typename K, bool F32, bool PAY, int THREADS, int ITEMS, int WPE>
+__global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t classes, const K* in_keys,
+                                                             const uint32_t* in_pay, K* keys_out, uint32_t* perm_out,
+                                                             uint32_t* pay_out) {
+  constexpr int N = THREADS * ITEMS;
+  constexpr int LB = 31 - __builtin_clz((unsigned)N);  // 2^LB bins: one per element, or more than half
+  constexpr int BPT = (1 << LB) / THREADS;
+  // words, then bins; the staging area of the output uses the same memory
+  __shared__ __align__(16) uint32_t s_mem[2 * N + 8];
+  __shared__ uint32_t s_red[6 * (THREADS / kWave)];
+  __shared__ uint32_t s_tmp[2 * (THREADS / kWave)];
+  __shared__ uint32_t s_sum;
+  uint32_t* const fr = s_mem;           // N words, and 3 beyond
+  uint32_t* const bin = s_mem + N + 4;  // 2^LB + 1 bins
+  uint64_t* const st = reinterpret_cast<uint64_t*>(s_mem);
+  // the (at most three) classes, the longest first, and their segment counts
+  const int c0 = 31 - __builtin_clz(classes);
+  const uint32_t m1 = classes & ~(1u << c0);
+  const int c1 = m1 ? 31 - __builtin_clz(m1) : c0;
+  const uint32_t m2 = m1 & ~(1u << c1);
+  const int c2 = m2 ? 31 - __builtin_clz(m2) : c1;
+  const uint32_t n0 = uniform(final_count(w, c0)), n1 = n0 + uniform(m1 ? final_count(w, c1) : 0u),
+                 total = n1 + uniform(m2 ? final_count(w, c2) : 0u);
+  auto seg_at = [&](uint32_t q) -> FinalSeg* {
+    return q < n0 ? w.cls[c0] + q : q < n1 ? w.cls[c1] + (q - n0) : w.cls[c2] + (q - n1);
+  };
+  K key[ITEMS];
+  uint32_t idx[ITEMS], pay[ITEMS];
+  // Thread t takes elements i * THREADS + t.  One source per segment
+  // (uniform), every lane loads (lanes past the end reload the last element),
+  // so that all loads go out before any is used.  Bases are scalar, elements
+  // 32-bit byte offsets.
+  auto load = [&](uint32_t len, uint32_t src, uint64_t start, int t) {
+    const uint32_t* const psrc = PAY ? (src ? w.buf_pay[src - 1] : in_pay) + start : nullptr;
+    if (src) {
+      const BufView<K> sb{w.buf_rec[src - 1] + start * BufView<K>::W};
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++) {
+        const uint32_t j = min((uint32_t)(i * THREADS + t), len - 1);
+        sb.get32(j, key[i], idx[i]);
+        if constexpr (PAY) pay[i] = at32(psrc, j);
+      }
+    } else {
+      const K* const kin = in_keys + start;
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++) {
+        const uint32_t j = min((uint32_t)(i * THREADS + t), len - 1);
+        key[i] = at32(kin, j);  // raw bits
+        idx[i] = j;
+        if constexpr (PAY) pay[i] = at32(psrc, j);
+      }
+    }
+  };
+  uint32_t q = blockIdx.x;
+  if (q >= total) return;
+  FinalSeg f = *seg_at(q);
+  load(uniform(f.len), uniform(f.src), uniform64(f.start), threadIdx.x);
+  for (;;) {
+    const uint32_t len = uniform(f.len), src = uniform(f.src);
+    const uint64_t start = uniform64(f.start);
+    // the next segment's descriptor now, its elements before the last output
+    // of this one (whose registers they take): a load that follows stores
+    // waits for them, and so would the start of every segment
+    const uint32_t qn = q + gridDim.x;
+    const bool more = qn < total;
+    f = *seg_at(more ? qn : q);
+    // an opaque copy of the thread index: per-thread addresses are recomputed
+    // per segment rather than hoisted out of the loop and kept live
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    K* const kout = keys_out + start;
+    uint32_t* const pout = perm_out ? perm_out + start : nullptr;
+    uint32_t* const yout = PAY ? pay_out + start : nullptr;
+    if constexpr (F32) {
+      if (!src) {
+#pragma unroll
+        for (int i = 0; i < ITEMS; i++) key[i] = ord_of<K, F32>(key[i]);
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < BPT / 4; b++) reinterpret_cast<uint4*>(bin)[b * THREADS + t] = make_uint4(0, 0, 0, 0);
+    if (t == 0) s_sum = 0;
+    // bounds of the keys (64-bit keys: of their upper halves) and positions
+    constexpr int KS = sizeof(K) == 8 ? 32 : 0;
+    uint32_t hmn = ~0u, hmx = 0u, imn = ~0u, imx = 0u;
+#pragma unroll
+    for (int i = 0; i < ITEMS; i++) {
+      const uint32_t h = (uint32_t)((uint64_t)key[i] >> KS);
+      hmn = min(hmn, h);
+      hmx = max(hmx, h);
+      imn = min(imn, idx[i]);
+      imx = max(imx, idx[i]);
+    }
+    // (the barrier of the reduction also orders the stores above before their readers)
+    const Range4 br = block_range<uint32_t, THREADS>(hmn, hmx, imn, imx, s_red, t);
+    imn = br.imn;
+    const uint32_t ir = br.imx - br.imn;
+    K mn;
+    uint64_t kr;
+    if constexpr (sizeof(K) == 4) {
+      mn = (K)br.kmn;
+      kr = br.kmx - br.kmn;
+    } else {
+      mn = br.kmn << 32;
+      kr = ((br.kmx - br.kmn) << 32) | 0xFFFFFFFFu;
+      if (br.kmx - br.kmn < (1u << LB)) {  // uniform: the upper halves tell too little
+        uint64_t mn2 = ~0ull, mx2 = 0ull;
+#pragma unroll
+        for (int i = 0; i < ITEMS; i++) {
+          mn2 = key[i] < mn2 ? key[i] : mn2;
+          mx2 = key[i] > mx2 ? key[i] : mx2;
+        }
+        __syncthreads();  // the first reduction's values have been read
+        const Range4 b2 = block_range<uint64_t, THREADS>(mn2, mx2, 0u, 0u, s_red, t);
+        mn = b2.kmn;
+        kr = b2.kmx - b2.kmn;
+      }
+    }
+    const int rb = kr ? 64 - __clzll((long long)kr) : 0, ib = ir ? 32 - __clz((int)ir) : 0;
+    // wd = (d >> sr) << sl | x >> si: 32 bits, or rb + ib if that is less
+    const int sr = max(rb - 32, 0), sl = min(32 - min(rb, 32), ib), si = ib - sl;
+    const int bsh = max(min(rb, 32) + sl - LB, 0);
+    uint32_t wd[ITEMS], rank[ITEMS];
+    if (sl == 0) {  // uniform: key bits only
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++) wd[i] = (uint32_t)((uint64_t)(K)(key[i] - mn) >> sr);
+    } else {
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++)
+        wd[i] = ((rb ? (uint32_t)(key[i] - mn) : 0u) << (sl & 31)) | ((idx[i] - imn) >> si);
+    }
+#pragma unroll
+    for (int i = 0; i < ITEMS; i++) {
+      rank[i] = 0;  // first the place in the bin
+      if (t < (int)len - i * THREADS) rank[i] = atomicAdd(&bin[wd[i] >> bsh], 1u);
+    }
+    __syncthreads();
+    const bool rare = bins_scan<THREADS, BPT>(bin, len, s_tmp, t) > kRankBudget * len;  // uniform
+    if (rare) {
+      if (t == 0) seg_at(q)->src = src | kPairsFlag;
+    } else {
+#pragma unroll
+    for (int i = 0; i < ITEMS; i++)
+      if (t < (int)len - i * THREADS) fr[bin[wd[i] >> bsh] + rank[i]] = wd[i];
+    if (t < 3) fr[len + t] = ~0u;
+    __syncthreads();
+    // bin start and size of every element, then its rank
+#pragma unroll
+    for (int i = 0; i < ITEMS; i++) {
+      if (t < (int)len - i * THREADS) {
+        const uint32_t b = wd[i] >> bsh, s0 = bin[b];
+        rank[i] = ((bin[b + 1] - s0) << 16) | s0;
+      }
+    }
+    uint32_t sum = 0;
+#pragma unroll
+    for (int i = 0; i < ITEMS; i++) {
+      if (t < (int)len - i * THREADS) {
+        const uint32_t* a = fr + (rank[i] & 0xFFFFu);
+        uint32_t n = rank[i] >> 16, less = 0;
+#pragma unroll 1
+        for (uint32_t k = 0; k < n; k += 4) {
+          const uint32_t x0 = a[k], x1 = a[k + 1], x2 = a[k + 2], x3 = a[k + 3];
+          less += x0 < wd[i] ? 1u : 0u;
+          less += x1 < wd[i] ? 1u : 0u;
+          less += x2 < wd[i] ? 1u : 0u;
+          less += x3 < wd[i] ? 1u : 0u;
+        }
+        rank[i] = (rank[i] & 0xFFFFu) + less;
+        sum += rank[i];
+      }
+    }
+    const bool exact = sr == 0 && si == 0;  // uniform: words are distinct
+    if (!exact) {
+      sum = wave_incl_scan_dpp(sum);
+      if (lane_id() == kWave - 1) atomicAdd(&s_sum, sum);
+    }
+    __syncthreads();  // every word read
+    if (!exact && s_sum != (uint32_t)(((uint64_t)len * (len - 1)) >> 1)) {
+      // the bits of (d, x) below the word: those of d that were dropped (sr of
+      // them), then x (all of it, or its low si bits)
+      rank_ties<THREADS, ITEMS>(
+          fr, bin, len, rank, sr ? 2 : 1,
+          [&](int round, int i) -> uint32_t {
+            return sr && round == 0 ? (uint32_t)(key[i] - mn) : idx[i] - imn;
+          },
+          t);
+    }
+    // into rank order and out; the last array's registers are free for the
+    // next segment once it is staged
+    if constexpr (sizeof(K) == 4) {
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++)
+        if (t < (int)len - i * THREADS) st[rank[i]] = ((uint64_t)idx[i] << 32) | key[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++)
+        if (t < (int)len - i * THREADS) st[rank[i]] = (uint64_t)key[i];
+    }
+    constexpr bool TWO = sizeof(K) == 8 || PAY;  // two rounds through the staging area
+    if constexpr (TWO) {
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++) {
+        const uint32_t j = i * THREADS + t;
+        if (t < (int)len - i * THREADS) {
+          const uint64_t x = st[j];
+          at32(kout, j) = to_output<K, F32>((K)x);
+          if constexpr (sizeof(K) == 4) {
+            if (pout) at32(pout, j) = (uint32_t)(x >> 32);
+          }
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++) {
+        if (t < (int)len - i * THREADS) {
+          if constexpr (sizeof(K) == 4)
+            fr[rank[i]] = pay[i];
+          else if constexpr (PAY)
+            st[rank[i]] = ((uint64_t)pay[i] << 32) | idx[i];
+          else
+            fr[rank[i]] = idx[i];
+        }
+      }
+    }
+    }
+    __syncthreads();
+    if (more) load(uniform(f.len), uniform(f.src), uniform64(f.start), t);
+    if (!rare) {
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++) {
+        const uint32_t j = i * THREADS + t;
+        if (t < (int)len - i * THREADS) {
+          if constexpr (sizeof(K) == 4 && !PAY) {
+            const uint64_t x = st[j];
+            at32(kout, j) = to_output<K, F32>((K)x);
+            if (pout) at32(pout, j) = (uint32_t)(x >> 32);
+          } else if constexpr (sizeof(K) == 4) {
+            at32(yout, j) = fr[j];
+          } else if constexpr (PAY) {
+            const uint64_t x = st[j];
+            if (pout) at32(pout, j) = (uint32_t)x;
+            at32(yout, j) = (uint32_t)(x >> 32);
+          } else {
+            if (pout) at32(pout, j) = fr[j];
+          }
+        }
+      }
+    }
+    if (!more) break;
+    q = qn;
+    __syncthreads();  // the next segment clears its bins in the staging area
   }
 }
 
 // ---------------------------------------------------------------------------
-// Final segments of one size class sorted as single 64-bit words.  With mn the
-// segment's smallest key and rb the bit width of (largest key - mn), and PB
-// the bit width of a slot (the element's place in the segment as stored):
-//   exact words   rb + 32 (+ PB with payload) <= 64: the word
-//                 (key - mn, position [, slot]) orders exactly like the
-//                 (key, position) pair;
-//   slot words    otherwise: the word (top 64 - PB bits of key - mn, slot);
-//                 words with equal top parts (equal keys, or keys differing
-//                 only in dropped low bits) come out in slot order, which is
-//                 checked against their (key, position) order afterwards.
-// The words are distinct.  Segments of at least 1024 elements are ordered by
-// bins and ranks (bin_count, bin_rank); a segment whose ranking would cost too
-// much is marked kMergeFlag and left to the MERGE instance, launched once
-// after all classes with the largest class's shape, which (like the
-// instances for shorter segments) sorts the words with the LDS merge sort.  A
-// segment whose check finds a pair out of order is marked kPairsFlag and
-// sorted by k_local_sort<FLAGGED>, launched last.  Every path produces the
-// same output; words take half the LDS of pairs and one compare per step.
-// SRCBUF false: the instance for segments of the caller's input only (no
-// table of positions); true: for buffer segments, and for input segments too
-// unless `mixed` (then the other instance takes those).
-template <typename K, bool F32, bool PAY, int THREADS, int ITEMS, bool MERGE = false, bool SRCBUF = true>
-__global__ __launch_bounds__(THREADS, (THREADS >= 1024 ? 8 : 1)) void k_local_words(Work w, int cls, const K* in_keys, const uint32_t* in_pay,
-                                                         K* keys_out, uint32_t* perm_out, uint32_t* pay_out,
-                                                         int mixed) {
-  constexpr int N = THREADS * ITEMS;
-  constexpr int NP = lpad_size(N);
-  constexpr int PB = 32 - __builtin_clz((unsigned)(N - 1));
-  constexpr uint64_t SLOT = (1ull << PB) - 1;
-  constexpr int XB = PAY ? PB : 0;  // slot bits kept in exact words (payload gather)
-  // bins: about four words each in a full segment, for segments long
-  // enough to need them; eight in the instances of at most 4096 words, whose
-  // LDS then still fits three workgroups per CU
-  constexpr bool BINS = !MERGE && N >= 1024;
-  constexpr int LB = 31 - __builtin_clz((unsigned)(N <= 4096 ? N / 8 : N / 4));
-  // the merge sort and the output read words as two halves (lo, hi); the
-  // bins see the same memory as whole words
-  __shared__ uint64_t s_words[NP];
-  uint32_t* const s_lo = (uint32_t*)s_words;
-  uint32_t* const s_hi = s_lo + NP;
-  __shared__ uint32_t s_red[6 * (THREADS / kWave)];
-  __shared__ uint32_t s_bin[BINS ? (1 << LB) + 1 : 1];
-  __shared__ uint32_t s_cost;
-  // positions of the segment's elements by slot (for segments of a buffer),
-  // loaded coalesced with the keys; SRCBUF false: every segment lies in the
-  // caller's input and positions are slots
-  __shared__ uint32_t s_idx[SRCBUF ? N : 1];
-  static_assert(!BINS || NP >= N + 3, "room for the words read past a bin's end");
-  __shared__ uint32_t s_list[MERGE ? THREADS : 1];
+// The segments k_local_rank handed over, of every class, by the merge sort of
+// pairs: one resident-sized launch after all classes.  Each thread checks one
+// list entry and the marked ones are collected in LDS, so that the search is
+// parallel rather than a chain of dependent loads; the merge sort runs in the
+// smallest of three shapes that holds the segment.
+template <typename K, bool F32, bool PAY, int THREADS, int ITEMS>
+__global__ __launch_bounds__(THREADS) void k_local_rare(Work w, const K* in_keys, const uint32_t* in_pay, K* keys_out,
+                                                        uint32_t* perm_out, uint32_t* pay_out) {
+  constexpr int NP = lpad_size(THREADS * ITEMS);
+  __shared__ uint32_t s_lo[NP];
+  __shared__ uint32_t s_hi[sizeof(K) == 8 ? NP : 1];
+  __shared__ uint32_t s_v[NP];
+  __shared__ uint32_t s_p[PAY ? NP : 1];
+  __shared__ uint32_t s_list[THREADS];
   __shared__ uint32_t s_n;
-  for_each_segment<THREADS>(w, cls, MERGE ? kMergeFlag : 0u, s_list, s_n, [&](int cc, uint32_t q) {
-    FinalSeg f = final_at(w, cc, q);
-    if (MERGE && !(f.src & kMergeFlag)) return;  // uniform
-    f.src &= 0xFFu;
-    if (SRCBUF ? (mixed && f.src == 0) : f.src != 0) return;  // the other instance's
-    // an opaque copy of the thread index: per-thread addresses are recomputed
-    // per segment rather than hoisted out of the loop and kept live
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
-    const BufView<K> sb{f.src ? w.buf_rec[f.src - 1] : nullptr};
-    const uint32_t* srcp = f.src ? w.buf_pay[f.src - 1] : in_pay;
-    auto idx_at = [&](uint32_t j) -> uint32_t { return (SRCBUF && f.src) ? s_idx[j] : j; };
-    auto key_at = [&](uint32_t j) -> K { return f.src ? sb.key(f.start + j) : load_ord<K, F32>(in_keys, f.start + j); };
-    // thread t takes slots i*THREADS+t (striped, coalesced).  All ITEMS loads
-    // are issued before any is used: a use inside each guarded load would
-    // wait for that load before the next one goes out.  The keys then wait
-    // in the word memory until the minimum is known.
-    const bool from_buf = SRCBUF && f.src;
-    K kr[ITEMS];
-    uint32_t ir[ITEMS];
-#pragma unroll
-    for (int i = 0; i < ITEMS; i++) {
-      kr[i] = K(0);
-      ir[i] = i * THREADS + tid;
-    }
-    if (from_buf) {  // uniform: one source per segment
-#pragma unroll
-      for (int i = 0; i < ITEMS; i++)
-        if (i * THREADS + tid < f.len) sb.get(f.start + i * THREADS + tid, kr[i], ir[i]);
-    } else {
-#pragma unroll
-      for (int i = 0; i < ITEMS; i++)
-        if (i * THREADS + tid < f.len) kr[i] = in_keys[f.start + i * THREADS + tid];
-    }
-    K mn = KMax<K>::v, mx = K(0);
-    uint32_t imn = ~0u, imx = 0u;
-#pragma unroll
-    for (int i = 0; i < ITEMS; i++) {
-      const uint32_t j = i * THREADS + tid;
-      if (j < f.len) {
-        const K key = from_buf ? kr[i] : ord_of<K, F32>(kr[i]);
-        if (from_buf) s_idx[j] = ir[i];
-        s_words[j] = (uint64_t)key;
-        mn = key < mn ? key : mn;
-        mx = key > mx ? key : mx;
-        imn = min(imn, ir[i]);
-        imx = max(imx, ir[i]);
+  const LdsArr<K> sa{s_lo, s_hi, s_v, s_p};
+  for (int c = 0; c <= kNumClasses - 2; c++) {
+    const uint32_t cnt = final_count(w, c);
+    // neighbouring entries go to different workgroups: marked segments
+    // (the tails of a distribution) often lie next to each other
+    for (uint32_t q0 = 0; q0 < cnt; q0 += gridDim.x * THREADS) {
+      if (threadIdx.x == 0) s_n = 0;
+      __syncthreads();
+      const uint32_t q = q0 + threadIdx.x * gridDim.x + blockIdx.x;
+      if (q < cnt && (w.cls[c][q].src & kPairsFlag)) s_list[atomicAdd(&s_n, 1u)] = q;
+      __syncthreads();
+      const uint32_t n = s_n;
+      for (uint32_t k = 0; k < n; k++) {
+        FinalSeg f = w.cls[c][s_list[k]];
+        f.src &= 0xFFu;
+        if (f.len <= THREADS * ITEMS / 4)
+          sort_pairs<K, F32, PAY, THREADS, ITEMS / 4>(w, f, sa, in_keys, in_pay, keys_out, perm_out, pay_out);
+        else if (f.len <= THREADS * ITEMS / 2)
+          sort_pairs<K, F32, PAY, THREADS, ITEMS / 2>(w, f, sa, in_keys, in_pay, keys_out, perm_out, pay_out);
+        else
+          sort_pairs<K, F32, PAY, THREADS, ITEMS>(w, f, sa, in_keys, in_pay, keys_out, perm_out, pay_out);
       }
+      __syncthreads();
     }
-    if constexpr (BINS) {
-      for (int b = tid; b <= (1 << LB); b += THREADS) s_bin[b] = 0;
-    }
-    {
-      // its barrier also orders the stores above before their readers
-      const Range4 br = block_range<K, THREADS>(mn, mx, imn, imx, s_red, tid);
-      mn = (K)br.kmn;
-      mx = (K)br.kmx;
-      imn = br.imn;
-      imx = br.imx;
-    }
-    const uint64_t range = (uint64_t)(mx - mn);
-    const int rb = range ? 64 - __clzll((long long)range) : 0;
-    const bool exact = rb + 32 + XB <= 64;
-    // slot words keep the top 64 - PB bits of (key - mn): drop low bits when
-    // the key range is wider than that
-    const int drop = exact ? 0 : max(rb + PB - 64, 0);
-    // the order of equal word prefixes must be checked unless it is exact: no
-    // key bits dropped and slots in position order (segments of the input)
-    const bool check = !exact && (drop > 0 || f.src != 0);
-    const int sh = exact ? 32 + XB : PB;
-    uint64_t c[ITEMS];
-#pragma unroll
-    for (int i = 0; i < ITEMS; i++) {
-      const uint32_t j = i * THREADS + tid;
-      uint64_t low = j;
-      if (exact) low = ((uint64_t)(j < f.len ? idx_at(j) : 0u) << XB) | (PAY ? j : 0u);
-      c[i] = j < f.len ? (((uint64_t)((K)s_words[j] - mn) >> drop) << sh) | low : ~0ull;
-    }
-    if constexpr (BINS) {
-      // bounds of the words: exact words are at least (position min) and at
-      // most (key range, position max, all slot bits); slot words lie in
-      // [0, (key range >> drop, len - 1)]
-      BinMap bm;
-      if (exact && rb < LB) {  // key part, then the top bits of the position
-        const uint32_t ib = LB - rb, ir = imx - imn;
-        const int ibits = ir ? 32 - __clz(ir) : 0;
-        bm = BinMap{(uint64_t)imn << XB, (uint32_t)sh, ib, (uint32_t)(XB + max(ibits - (int)ib, 0)), (1u << ib) - 1u};
-      } else {
-        const uint64_t wmn = exact ? (uint64_t)imn << XB : 0ull;
-        const uint64_t wmx = exact ? ((uint64_t)range << sh) | ((uint64_t)imx << XB) | (PAY ? SLOT : 0ull)
-                                   : (((uint64_t)range >> drop) << PB) | (uint64_t)(f.len - 1);
-        const uint64_t wr = wmx - wmn;
-        const int bits = wr ? 64 - __clzll((long long)wr) : 0;
-        bm = BinMap{wmn, (uint32_t)(bits > LB ? bits - LB : 0), 0u, 0u, 0u};
-      }
-      uint32_t r[ITEMS];
-      if (!bin_count<THREADS, ITEMS, LB>(c, f.len, s_bin, &s_cost, tid, bm, r)) {
-        // uniform; every thread is past its reads of this segment's LDS
-        if (tid == 0) w.cls[cc][q].src = f.src | kMergeFlag;
-        return;
-      }
-      bin_rank<THREADS, ITEMS, LB>(c, r, f.len, s_words, s_lo, s_hi, s_bin, tid, bm);
-    } else {
-      __syncthreads();  // every key read from the word memory
-      lds_merge_sort_words<THREADS, ITEMS>(c, s_lo, s_hi, tid);
-#pragma unroll
-      for (int i = 0; i < ITEMS; i++) {
-        const int qq = lpad(tid * ITEMS + i);
-        s_lo[qq] = (uint32_t)c[i];
-        s_hi[qq] = (uint32_t)(c[i] >> 32);
-      }
-    }
-    __syncthreads();
-    bool bad = false;
-    if constexpr (!PAY) {
-      for (uint32_t j = tid; j < f.len; j += THREADS) {
-        const int qq = lpad(j);
-        const uint64_t cj = ((uint64_t)s_hi[qq] << 32) | s_lo[qq];
-        const uint32_t slot = (uint32_t)(cj & SLOT);
-        uint32_t idx;
-        K key;
-        if (exact) {
-          idx = (uint32_t)(cj >> XB);
-          key = (K)(mn + (K)(cj >> sh));
-        } else {
-          idx = idx_at(slot);
-          key = drop ? key_at(slot) : (K)(mn + (K)(cj >> sh));
-          if (check && j + 1 < f.len) {
-            const int qn = lpad(j + 1);
-            const uint64_t cn = ((uint64_t)s_hi[qn] << 32) | s_lo[qn];
-            if ((cn >> PB) == (cj >> PB)) {
-              // equal prefixes: the pair order decides
-              const uint32_t sn = (uint32_t)(cn & SLOT);
-              if (pair_less(key_at(sn), idx_at(sn), key, idx)) bad = true;
-            }
-          }
-        }
-        keys_out[f.start + j] = to_output<K, F32>(key);
-        if (perm_out) perm_out[f.start + j] = idx;
-      }
-    } else {
-      // with a payload, gathered by slot from global memory: the thread's
-      // sorted elements j = tid + k * THREADS are read (LDS, and the global
-      // key and payload reads by slot) before any output store, since a load
-      // issued after stores waits for them
-      K okey[ITEMS];
-      uint32_t oidx[ITEMS], opay[ITEMS];
-#pragma unroll
-      for (int k = 0; k < ITEMS; k++) {
-        const uint32_t j = tid + k * THREADS;
-        okey[k] = K(0);
-        oidx[k] = 0;
-        opay[k] = 0;
-        if (j < f.len) {
-          const int qq = lpad(j);
-          const uint64_t cj = ((uint64_t)s_hi[qq] << 32) | s_lo[qq];
-          const uint32_t slot = (uint32_t)(cj & SLOT);
-          if (exact) {
-            oidx[k] = (uint32_t)(cj >> XB);
-            okey[k] = (K)(mn + (K)(cj >> sh));
-          } else {
-            oidx[k] = idx_at(slot);
-            okey[k] = drop ? key_at(slot) : (K)(mn + (K)(cj >> sh));
-          }
-          opay[k] = srcp[f.start + slot];
-        }
-      }
-      if (check) {  // uniform
-#pragma unroll
-        for (int k = 0; k < ITEMS; k++) {
-          const uint32_t j = tid + k * THREADS;
-          if (j + 1 < f.len) {
-            const uint64_t cj = ((uint64_t)s_hi[lpad(j)] << 32) | s_lo[lpad(j)];
-            const uint64_t cn = ((uint64_t)s_hi[lpad(j + 1)] << 32) | s_lo[lpad(j + 1)];
-            if ((cn >> PB) == (cj >> PB)) {
-              // equal prefixes: the pair order decides
-              const uint32_t sn = (uint32_t)(cn & SLOT);
-              if (pair_less(key_at(sn), idx_at(sn), okey[k], oidx[k])) bad = true;
-            }
-          }
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < ITEMS; k++) {
-        const uint32_t j = tid + k * THREADS;
-        if (j < f.len) {
-          keys_out[f.start + j] = to_output<K, F32>(okey[k]);
-          if (perm_out) perm_out[f.start + j] = oidx[k];
-          pay_out[f.start + j] = opay[k];
-        }
-      }
-    }
-    if (__syncthreads_or(bad) && threadIdx.x == 0) w.cls[cc][q].src = f.src | kPairsFlag;
-  }, mixed ? (SRCBUF ? 2 : 1) : 0);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -632,86 +643,34 @@ __global__ __launch_bounds__(THREADS) void k_oversize(Work w, const K* in_keys, 
   }
 }
 
-// Local sort of one class with the merge sort.  A one-segment direct sort
-// runs the pair sort alone; a class list runs the word sort and then the pair
-// sort over the segments the word sort handed over.
-#ifndef RS_WORDS_PER_CU
-#define RS_WORDS_PER_CU 64
-#endif
+// A plain call that fits one workgroup (class c is the smallest that holds it).
 template <typename K, bool F32, bool PAY, int T, int I>
-static int merge_class_launch(int c, const Work& w, const K* kin, const uint32_t* pay_in, K* kout,
-                              uint32_t* perm_out, uint32_t* pay_out, uint64_t cap_c, hipStream_t st) {
-  static const std::string shape = std::to_string(T) + ", " + std::to_string(I);
-  static const std::string t_pairs = "(k_local_sort<K, F32, PAY, " + shape + ">)";
-  static const std::string t_words = "(k_local_words<K, F32, PAY, " + shape + ">)";
-  static const std::string t_words_in = "(k_local_words<K, F32, PAY, " + shape + ", false, false>)";
-  if (c & kDirect) {
-    RS_LAUNCH_TAGGED((k_local_sort<K, F32, PAY, T, I>), t_pairs.c_str(), 1, T, st, w, -1, kin, pay_in, kout,
-                     perm_out, pay_out);
-    return 0;
-  }
-  // the word sort takes about one workgroup per segment (bounded); handed-over
-  // segments are sorted by launch_local_fallbacks after all classes
-  const int cb = c & 0xFF;
-  const int mixed = (c & kMixed) ? 1 : 0;
-  if (c & (kInputOnly | kMixed))  // input segments
-    RS_LAUNCH_TAGGED((k_local_words<K, F32, PAY, T, I, false, false>), t_words_in.c_str(),
-                     grid_for(cap_c, RS_WORDS_PER_CU), T, st, w, cb, kin, pay_in, kout, perm_out, pay_out, mixed);
-  if (!(c & kInputOnly))  // buffer segments (and input ones unless mixed)
-    RS_LAUNCH_TAGGED((k_local_words<K, F32, PAY, T, I>), t_words.c_str(), grid_for(cap_c, RS_WORDS_PER_CU), T, st, w,
-                     cb, kin, pay_in, kout, perm_out, pay_out, mixed);
-  return 0;
-}
-
-// The segments the word sorts of all classes handed over: the merge sort of
-// words for those whose ranking was too costly, then the pair sort for those
-// whose word order failed the check.  One resident-sized launch each, with
-// the shape of the largest class a call can have.
-template <typename K, bool F32, bool PAY, int T, int I>
-static int fallback_launch(const Work& w, const K* kin, const uint32_t* pay_in, K* kout, uint32_t* perm_out,
-                            uint32_t* pay_out, hipStream_t st) {
-  static const std::string shape = std::to_string(T) + ", " + std::to_string(I);
-  static const std::string t_merge = "(k_local_words<K, F32, PAY, " + shape + ", true>)";
-  static const std::string t_flagged = "(k_local_sort<K, F32, PAY, " + shape + ", true>)";
-  const uint32_t g = grid_for(1u << 30, 1);
-  RS_LAUNCH_TAGGED((k_local_words<K, F32, PAY, T, I, true>), t_merge.c_str(), g, T, st, w, 0, kin, pay_in, kout,
-                   perm_out, pay_out, 0);
-  RS_LAUNCH_TAGGED((k_local_sort<K, F32, PAY, T, I, true>), t_flagged.c_str(), g, T, st, w, 0, kin, pay_in, kout,
-                   perm_out, pay_out);
+static int direct_launch(const Work& w, const K* kin, const uint32_t* pay_in, K* kout, uint32_t* perm_out,
+                         uint32_t* pay_out, hipStream_t st) {
+  static const std::string tag =
+      "(k_local_sort<K, F32, PAY, " + std::to_string(T) + ", " + std::to_string(I) + ">)";
+  RS_LAUNCH_TAGGED((k_local_sort<K, F32, PAY, T, I>), tag.c_str(), 1, T, st, w, kin, pay_in, kout, perm_out, pay_out);
   return 0;
 }
 
 template <typename K, bool F32, bool PAY>
-int launch_local_fallbacks(const Work& w, uint32_t cap, const K* kin, const uint32_t* pay_in, K* kout,
-                           uint32_t* perm_out, uint32_t* pay_out, hipStream_t st) {
-  if constexpr (!PAY) {
-    if (cap > 8192) return fallback_launch<K, F32, PAY, 768, 16>(w, kin, pay_in, kout, perm_out, pay_out, st);
-  }
-  return fallback_launch<K, F32, PAY, 1024, 8>(w, kin, pay_in, kout, perm_out, pay_out, st);
-}
-
-template <typename K, bool F32, bool PAY>
-int launch_merge_class(int c, const Work& w, const K* kin, const uint32_t* pay_in, K* kout, uint32_t* perm_out,
-                       uint32_t* pay_out, uint64_t cap_c, hipStream_t st) {
-  const int cb = c & 0xFF;
-  auto go = [&](auto tag, uint32_t) -> int {
+int launch_direct(int c, const Work& w, const K* kin, const uint32_t* pay_in, K* kout, uint32_t* perm_out,
+                  uint32_t* pay_out, hipStream_t st) {
+  auto go = [&](auto tag) -> int {
     constexpr int T = decltype(tag)::T, I = decltype(tag)::I;
-    return merge_class_launch<K, F32, PAY, T, I>(c, w, kin, pay_in, kout, perm_out, pay_out, cap_c, st);
+    return direct_launch<K, F32, PAY, T, I>(w, kin, pay_in, kout, perm_out, pay_out, st);
   };
-  // alternative shapes (tuning.class_shape): twice the threads, half the keys
-  // per thread, for the classes from 1024 to 8192 keys
-  const bool alt = (c & kDirect) == 0 && ((tuning().class_shape >> cb) & 1u);
-  switch (cb) {
-    case 0: return go(Shape<64, 1>{}, 16);
-    case 1: return go(Shape<64, 4>{}, 16);
-    case 2: return alt ? go(Shape<512, 2>{}, 8) : go(Shape<256, 4>{}, 8);
-    case 3: return alt ? go(Shape<512, 4>{}, 8) : go(Shape<256, 8>{}, 8);
-    case 4: return alt ? go(Shape<768, 4>{}, 4) : go(Shape<384, 8>{}, 4);
-    case 5: return alt ? go(Shape<1024, 4>{}, 3) : go(Shape<512, 8>{}, 3);
-    case 6: return go(Shape<768, 8>{}, 2);
-    case 7: return go(Shape<1024, 8>{}, 1);
+  switch (c) {
+    case 0: return go(Shape<64, 1>{});
+    case 1: return go(Shape<64, 4>{});
+    case 2: return go(Shape<256, 4>{});
+    case 3: return go(Shape<256, 8>{});
+    case 4: return go(Shape<384, 8>{});
+    case 5: return go(Shape<512, 8>{});
+    case 6: return go(Shape<768, 8>{});
+    case 7: return go(Shape<1024, 8>{});
     case 8:
-      if constexpr (!PAY) return go(Shape<768, 16>{}, 1);
+      if constexpr (!PAY) return go(Shape<768, 16>{});
       break;
     default:
       break;
@@ -719,17 +678,68 @@ int launch_merge_class(int c, const Work& w, const K* kin, const uint32_t* pay_i
   return 0;
 }
 
-#define RS_INST_MERGE(K, F, P)                                                                                 \
-  template int launch_merge_class<K, F, P>(int, const Work&, const K*, const uint32_t*, K*, uint32_t*, uint32_t*, \
-                                           uint64_t, hipStream_t);                                              \
-  template int launch_local_fallbacks<K, F, P>(const Work&, uint32_t, const K*, const uint32_t*, K*, uint32_t*,   \
-                                               uint32_t*, hipStream_t);
-RS_INST_MERGE(uint32_t, false, false)
-RS_INST_MERGE(uint32_t, true, false)
-RS_INST_MERGE(uint64_t, false, false)
-RS_INST_MERGE(uint32_t, false, true)
-RS_INST_MERGE(uint32_t, true, true)
-RS_INST_MERGE(uint64_t, false, true)
+// Classes sorted by one launch of k_local_rank, on workgroups of T threads
+// with I elements each.  per_cu: workgroups resident on a CU; the grid is four
+// times that many (each takes several segments, the next one's elements in
+// flight while it writes out; once or twice as many measured the same).
+template <typename K, bool F32, bool PAY, int T, int I, int WPE>
+static int rank_launch(uint32_t classes, uint32_t per_cu, const Work& w, const K* kin, const uint32_t* pay_in,
+                       K* kout, uint32_t* perm_out, uint32_t* pay_out, hipStream_t st) {
+  static const std::string tag =
+      "(k_local_rank<K, F32, PAY, " + std::to_string(T) + ", " + std::to_string(I) + ">)";
+  if (!classes) return 0;
+  uint64_t cap = 0;
+  for (int c = 0; c < kNumClasses - 1; c++) cap += (classes >> c) & 1u ? w.cls_cap[c] : 0;
+  RS_LAUNCH_TAGGED((k_local_rank<K, F32, PAY, T, I, WPE>), tag.c_str(), grid_for(cap, per_cu * 4), T, st, w, classes,
+                   kin, pay_in, kout, perm_out, pay_out);
+  return 0;
+}
+
+// Shapes.  What counts is how many elements a CU has in flight without
+// register spills (a spilled register's reload waits for the output stores:
+// 512 x 8 bounded to 64 registers took 856 instead of 547 us on the buckets
+// of at most 4096 of 2^28 u64 keys).  512 x 8 (80 registers, 33 KB) runs
+// three workgroups per CU, 512 x 12 (109 registers, 49 KB) two: the buckets of
+// 4097 to 6144 of that sort took 1230 us in 1024 x 8 workgroups, 1150 us in
+// 512 x 16 and 751 us in 512 x 12.  With a payload 512 x 8 keeps its 97
+// registers (297 us on the 1 GiB batch; 327 at 80).
+template <typename K, bool F32, bool PAY>
+int launch_local_ranks(uint32_t classes, const Work& w, const K* kin, const uint32_t* pay_in, K* kout,
+                       uint32_t* perm_out, uint32_t* pay_out, hipStream_t st) {
+  int rc = 0;
+  // longest segments first (a payload call has no class of 12288)
+  if constexpr (PAY)
+    rc = rank_launch<K, F32, PAY, 1024, 8, 4>(classes & 0x80u, 1, w, kin, pay_in, kout, perm_out, pay_out, st);
+  else
+    rc = rank_launch<K, F32, PAY, 1024, 12, 4>(classes & 0x180u, 1, w, kin, pay_in, kout, perm_out, pay_out, st);
+  if (!rc) rc = rank_launch<K, F32, PAY, 512, 12, 4>(classes & 0x40u, 2, w, kin, pay_in, kout, perm_out, pay_out, st);
+  if (!rc)
+    rc = rank_launch<K, F32, PAY, 512, 8, PAY ? 4 : 6>(classes & 0x38u, 3, w, kin, pay_in, kout, perm_out, pay_out,
+                                                       st);
+  if (!rc) rc = rank_launch<K, F32, PAY, 256, 4, 8>(classes & 0x04u, 8, w, kin, pay_in, kout, perm_out, pay_out, st);
+  if (!rc) rc = rank_launch<K, F32, PAY, 64, 4, 8>(classes & 0x03u, 32, w, kin, pay_in, kout, perm_out, pay_out, st);
+  if (rc) return rc;
+  if constexpr (PAY) {
+    RS_LAUNCH((k_local_rare<K, F32, PAY, 1024, 8>), grid_for(1u << 30, 1), 1024, st, w, kin, pay_in, kout, perm_out,
+              pay_out);
+  } else {
+    RS_LAUNCH((k_local_rare<K, F32, PAY, 768, 16>), grid_for(1u << 30, 1), 768, st, w, kin, pay_in, kout, perm_out,
+              pay_out);
+  }
+  return 0;
+}
+
+#define RS_INST_LOCAL(K, F, P)                                                                                    \
+  template int launch_direct<K, F, P>(int, const Work&, const K*, const uint32_t*, K*, uint32_t*, uint32_t*,       \
+                                      hipStream_t);                                                                \
+  template int launch_local_ranks<K, F, P>(uint32_t, const Work&, const K*, const uint32_t*, K*, uint32_t*,        \
+                                           uint32_t*, hipStream_t);
+RS_INST_LOCAL(uint32_t, false, false)
+RS_INST_LOCAL(uint32_t, true, false)
+RS_INST_LOCAL(uint64_t, false, false)
+RS_INST_LOCAL(uint32_t, false, true)
+RS_INST_LOCAL(uint32_t, true, true)
+RS_INST_LOCAL(uint64_t, false, true)
 
 
 template <typename K, bool F32, bool PAY>

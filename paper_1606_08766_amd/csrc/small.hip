@@ -148,7 +148,7 @@ int launch_rfis_class(int c, const Work& w, const K* kin, const uint32_t* pay_in
       RS_LAUNCH((k_rfis<K, F32, PAY, 256, 1024>), g2, 256, st, w, ca, kin, pay_in, kout, perm_out, pay_out);
       break;
     default:
-      return launch_merge_class<K, F32, PAY>(c, w, kin, pay_in, kout, perm_out, pay_out, cap_c, st);
+      return -3;  // not this algorithm's class (small_class_algo)
   }
   return 0;
 }
@@ -434,7 +434,7 @@ int launch_rquick_class(int c, const Work& w, const K* kin, const uint32_t* pay_
                 seed);
       break;
     default:
-      return launch_merge_class<K, F32, PAY>(c, w, kin, pay_in, kout, perm_out, pay_out, cap_c, st);
+      return -3;  // not this algorithm's class (small_class_algo)
   }
   return 0;
 }
