@@ -233,30 +233,23 @@ __global__ __launch_bounds__(kStartThreads) void k_start_plain(Work w, uint64_t 
   }
 }
 
-// Per level: tile groups and count-matrix bases of the segments to split.
-// glog_small (levels after the first of a plain sort; 0 otherwise): when the
-// first level's scatter wrote runs of fewer than kShortRun keys on average
-// (keys spread over all buckets of every tile), this level's groups hold
-// 2^glog_small keys instead of 2^group_log2, and the count and scatter passes
-// read the choice from ctl->glog.
-constexpr int kPlanThreads = 1024;
+// Per level: tile groups and count-matrix bases of the segments to split, by
+// one workgroup (of the splitter launch, which needs the same lists and none
+// of this).  glog_small (levels after the first of a plain sort; 0 otherwise):
+// when the first level's scatter wrote runs of fewer than kShortRun keys on
+// average (keys spread over all buckets of every tile), this level's groups
+// hold 2^glog_small keys instead of 2^group_log2, and the count and scatter
+// passes read the choice from ctl->glog.
 constexpr uint32_t kShortRun = 128;
-__global__ __launch_bounds__(kPlanThreads) void k_plan(Work w, int lev, uint32_t glog_small) {
-  __shared__ uint32_t tmp[kPlanThreads / kWave + 1];
-  __shared__ uint32_t s_glog;
+template <int THREADS>
+__device__ __forceinline__ void plan_level(const Work& w, int lev, uint32_t glog_small, uint32_t* tmp) {
   const int cur = lev & 1;
   const uint32_t m = (uint32_t)min((uint64_t)w.ctl->big_count[cur], w.big_max);
   const BigSeg* B = w.big[cur];
-  if (threadIdx.x == 0) {
-    const uint32_t runs = w.ctl->runs;
-    const bool short_runs = glog_small && runs && w.n / runs < kShortRun;
-    s_glog = short_runs ? glog_small : w.group_log2;
-    if (glog_small) w.ctl->glog = s_glog;
-  }
-  __syncthreads();
-  const uint32_t glog = s_glog;
+  const uint32_t runs = w.ctl->runs;
+  const uint32_t glog = glog_small && runs && w.n / runs < kShortRun ? glog_small : w.group_log2;
   uint32_t ct = 0, cc = 0;
-  for (uint32_t base = 0; base < m; base += kPlanThreads) {
+  for (uint32_t base = 0; base < m; base += THREADS) {
     const uint32_t i = base + threadIdx.x;
     uint32_t nt = 0, nc = 0;
     if (i < m) {
@@ -264,8 +257,8 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(Work w, int lev, uint32_t
       nc = nt << B[i].logk;
     }
     uint32_t tt, tc;
-    const uint32_t et = block_excl_scan<kPlanThreads>(nt, tmp, &tt);
-    const uint32_t ec = block_excl_scan<kPlanThreads>(nc, tmp, &tc);
+    const uint32_t et = block_excl_scan<THREADS>(nt, tmp, &tt);
+    const uint32_t ec = block_excl_scan<THREADS>(nc, tmp, &tc);
     if (i < m) {
       w.group_base[i] = ct + et;
       w.count_base[i] = cc + ec;
@@ -274,8 +267,9 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(Work w, int lev, uint32_t
     cc += tc;
   }
   if (threadIdx.x < 16) w.ctl->queue[threadIdx.x >> 3][threadIdx.x & 7] = 0;
-  scan_flags_clear(w, threadIdx.x, kPlanThreads);
+  scan_flags_clear(w, threadIdx.x, THREADS);
   if (threadIdx.x == 0) {
+    if (glog_small) w.ctl->glog = glog;
     w.ctl->scan_next = 0;
     w.group_base[m] = ct;
     w.count_base[m] = cc;
@@ -298,7 +292,8 @@ constexpr uint32_t kDupIdsDiv = 16;
 
 template <typename K, bool F32, bool SRC_IN, int THREADS, int ITEMS>
 __global__ __launch_bounds__(THREADS) void k_splitters(Work w, int lev, const K* in_keys, int src_buf,
-                                                       uint32_t a, uint64_t seed, int ids_ok, int staged) {
+                                                       uint32_t a, uint64_t seed, int ids_ok, int staged,
+                                                       int plan, uint32_t glog_small) {
   constexpr int N = THREADS * ITEMS;
   constexpr int NP = lpad_size(N);
   constexpr int LB = 31 - __builtin_clz((unsigned)(N / 8));  // bins of the ranking path
@@ -313,11 +308,16 @@ __global__ __launch_bounds__(THREADS) void k_splitters(Work w, int lev, const K*
   __shared__ K s_spl[kMaxK];  // level 0, segment 0: the sorted splitter keys
   __shared__ uint32_t s_dup;
   const LdsArr<K> sa{s_lo, s_hi, s_v, nullptr};
+  if (plan && blockIdx.x == gridDim.x - 1) {  // the last workgroup plans the level
+    __shared__ uint32_t s_plan[THREADS / kWave + 1];
+    plan_level<THREADS>(w, lev, glog_small, s_plan);
+    return;
+  }
   const int cur = lev & 1;
   const uint32_t m = (uint32_t)min((uint64_t)w.ctl->big_count[cur], w.big_max);
   const BufView<K> bv{SRC_IN ? nullptr : w.buf_rec[src_buf]};
   K* tkey = (K*)w.tree_key;
-  for (uint32_t s = blockIdx.x; s < m; s += gridDim.x) {
+  for (uint32_t s = blockIdx.x; s < m; s += gridDim.x - (plan ? 1u : 0u)) {
     const BigSeg bs = w.big[cur][s];
     // a samples per bucket, fewer when a * k would exceed the LDS sample
     const uint32_t ae = min(a, (uint32_t)(THREADS * ITEMS) >> bs.logk);
@@ -646,7 +646,7 @@ struct GroupQueue {
 };
 
 // Keys per tile group (log2) of level lev: as the host planned it, unless the
-// level's plan chose smaller groups (k_plan).
+// level's plan chose smaller groups (plan_level).
 __device__ __forceinline__ uint32_t group_log2_of(const Work& w, int lev) {
   if (lev == 0) return w.group_log2;  // (no load on the first level)
   const uint32_t g = w.ctl->glog;
@@ -801,22 +801,27 @@ __global__ __launch_bounds__(THREADS, sizeof(K) == 4 ? 8 : 1) void k_count(Work 
 // chained scan with decoupled look-back.  Workgroups take chunks of
 // kScanChunk counts in order from a counter; each publishes its chunk's sum
 // at once and, after looking back at its predecessors' published sums (or
-// inclusive prefixes), its inclusive prefix.  A chunk's predecessors are held
-// by workgroups that are already running, so every wait ends; the wait is
-// bounded all the same (status set to an internal error after kScanSpinMax
-// polls).  Status word of chunk c: flag << 32 | value, flag 1 = the chunk's
-// sum, 2 = the inclusive prefix through the chunk; zeroed before each level.
-// Sums are taken modulo 2^32: offsets are only ever subtracted from offsets
-// of the same segment, which is shorter than 2^32.
+// inclusive prefixes), its inclusive prefix.  The first wave looks back, at 64
+// predecessors at a time: by one thread, a predecessor at a time, the scan of
+// a 2^20-key sort took 9.3 us and larger ones were better off in three
+// launches.  A status word holds all that is passed on (flag << 32 | value,
+// flag 1 = the chunk's sum, 2 = the inclusive prefix through the chunk; zeroed
+// before each level), so relaxed loads and stores do.  A chunk's predecessors
+// are held by workgroups that are already running, so every wait ends; the
+// wait is bounded all the same (status set to an internal error after
+// kScanSpinMax polls).  Sums are taken modulo 2^32: offsets are only ever
+// subtracted from offsets of the same segment, which is shorter than 2^32.
 constexpr int kScanThreads = 256, kScanItems = 16, kScanChunk = kScanThreads * kScanItems;
 constexpr uint32_t kScanSpinMax = 1u << 26;
-constexpr uint64_t kChainedScanMax = 1u << 20;  // larger count matrices use reduce-then-scan
 
 __global__ __launch_bounds__(kScanThreads) void k_scan(Work w) {
   __shared__ uint32_t tmp[kScanThreads / kWave + 1];
   __shared__ uint32_t s_chunk, s_prefix;
   const uint32_t M = w.ctl->total_counts;
   const uint32_t nb = (M + kScanChunk - 1) / kScanChunk;
+  // as many workgroups as chunks take part (the others would only queue for
+  // the chunk counter, at about 10 ns each)
+  if (blockIdx.x >= nb) return;
   for (;;) {
     if (threadIdx.x == 0) s_chunk = atomicAdd(&w.ctl->scan_next, 1u);
     __syncthreads();
@@ -843,33 +848,38 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(Work w) {
     for (int i = 0; i < kScanItems; i++) sum += v[i];
     uint32_t tot;
     uint32_t e = block_excl_scan<kScanThreads>(sum, tmp, &tot);
-    if (threadIdx.x == 0) {
-      uint32_t prefix = 0;
-      if (c == 0) {
-        __hip_atomic_store(&w.scan_flags[0], (2ull << 32) | tot, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-      } else {
-        __hip_atomic_store(&w.scan_flags[c], (1ull << 32) | tot, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        uint32_t j = c - 1, spins = 0;
-        for (;;) {
-          const uint64_t st =
-              __hip_atomic_load(&w.scan_flags[j], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-          const uint32_t flag = (uint32_t)(st >> 32);
-          if (flag == 0) {
+    if (threadIdx.x < kWave) {  // the first wave
+      const uint32_t lane = threadIdx.x;
+      auto publish = [&](uint64_t flag, uint32_t v) {
+        if (lane == 0)
+          __hip_atomic_store(&w.scan_flags[c], (flag << 32) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      };
+      uint32_t prefix = 0, spins = 0;
+      if (c > 0) {
+        publish(1, tot);
+        for (uint32_t end = c;;) {  // lane l looks at chunk end - 1 - l; below chunk 0 lies the prefix 0
+          const uint64_t s = lane < end ? __hip_atomic_load(&w.scan_flags[end - 1 - lane], __ATOMIC_RELAXED,
+                                                            __HIP_MEMORY_SCOPE_AGENT)
+                                        : 2ull << 32;
+          const uint32_t flag = (uint32_t)(s >> 32);
+          const uint64_t done = __ballot(flag == 2);
+          // lanes up to the nearest prefix, whose values are added up
+          const uint64_t need = done ? (done & (0ull - done)) * 2 - 1 : ~0ull;
+          if (__ballot(flag == 0) & need) {  // one of them is not published yet
             if (++spins > kScanSpinMax) {
-              set_status(w.ctl, -3);
+              if (lane == 0) set_status(w.ctl, -3);
               break;
             }
             __builtin_amdgcn_s_sleep(1);
             continue;
           }
-          prefix += (uint32_t)st;
-          if (flag == 2 || j == 0) break;
-          j--;
+          prefix += lane_u32(wave_incl_scan_dpp((need >> lane) & 1ull ? (uint32_t)s : 0u), kWave - 1);
+          if (done) break;
+          end -= kWave;
         }
-        __hip_atomic_store(&w.scan_flags[c], (2ull << 32) | (uint32_t)(prefix + tot), __ATOMIC_RELEASE,
-                           __HIP_MEMORY_SCOPE_AGENT);
       }
-      s_prefix = prefix;
+      publish(2, prefix + tot);
+      if (lane == 0) s_prefix = prefix;
     }
     __syncthreads();
     e += s_prefix;
@@ -891,65 +901,6 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(Work w) {
       }
     }
     __syncthreads();  // s_chunk / s_prefix are rewritten next
-  }
-}
-
-// Large count matrices: reduce-then-scan in three launches (partial sums of
-// chunks, a one-workgroup scan of the partials, the down-sweep), which for
-// thousands of chunks beats waiting on the chunks' predecessors.
-__global__ __launch_bounds__(kScanThreads) void k_scan_reduce(Work w) {
-  __shared__ uint32_t tmp[kScanThreads / kWave + 1];
-  const uint32_t M = w.ctl->total_counts;
-  const uint32_t nb = (M + kScanChunk - 1) / kScanChunk;
-  for (uint32_t blk = blockIdx.x; blk < nb; blk += gridDim.x) {
-    uint32_t s = 0;
-    const uint64_t base = (uint64_t)blk * kScanChunk;
-#pragma unroll
-    for (int i = 0; i < kScanItems; i++) {
-      const uint64_t j = base + i * kScanThreads + threadIdx.x;
-      if (j < M) s += w.counts[j];
-    }
-    uint32_t tot;
-    block_excl_scan<kScanThreads>(s, tmp, &tot);
-    if (threadIdx.x == 0) w.scan_part[blk] = tot;
-  }
-}
-
-constexpr int kScanTopThreads = 1024;
-__global__ __launch_bounds__(kScanTopThreads) void k_scan_partials(Work w) {
-  __shared__ uint32_t tmp[kScanTopThreads / kWave + 1];
-  const uint32_t M = w.ctl->total_counts;
-  const uint32_t nb = (M + kScanChunk - 1) / kScanChunk;
-  uint32_t carry = 0;
-  for (uint32_t base = 0; base < nb; base += kScanTopThreads) {
-    const uint32_t i = base + threadIdx.x;
-    const uint32_t v = i < nb ? w.scan_part[i] : 0u;
-    uint32_t tot;
-    const uint32_t e = block_excl_scan<kScanTopThreads>(v, tmp, &tot);
-    if (i < nb) w.scan_part[i] = carry + e;
-    carry += tot;
-  }
-}
-
-__global__ __launch_bounds__(kScanThreads) void k_scan_down(Work w) {
-  __shared__ uint32_t tmp[kScanThreads / kWave + 1];
-  const uint32_t M = w.ctl->total_counts;
-  const uint32_t nb = (M + kScanChunk - 1) / kScanChunk;
-  for (uint32_t blk = blockIdx.x; blk < nb; blk += gridDim.x) {
-    const uint64_t base = (uint64_t)blk * kScanChunk + (uint64_t)threadIdx.x * kScanItems;
-    uint32_t v[kScanItems];
-    uint32_t s = 0;
-#pragma unroll
-    for (int i = 0; i < kScanItems; i++) {
-      v[i] = (base + i < M) ? w.counts[base + i] : 0u;
-      s += v[i];
-    }
-    uint32_t e = block_excl_scan<kScanThreads>(s, tmp, nullptr) + w.scan_part[blk];
-#pragma unroll
-    for (int i = 0; i < kScanItems; i++) {
-      if (base + i < M) w.offsets[base + i] = e;
-      e += v[i];
-    }
   }
 }
 
@@ -1287,7 +1238,7 @@ static uint32_t group_log2_for(uint64_t n) {
 
 // Tile groups of the levels after the first of a plain sort hold at most
 // 2^kGroupUpLog2 keys, or 2^kGroupSmallLog2 when the first level's runs were
-// short (chosen on the device, k_plan).  Such a level splits k segments of
+// short (chosen on the device, plan_level).  Such a level splits k segments of
 // about n / k keys each, and with small groups the workgroups of an XCD,
 // which take consecutive groups, work on neighbouring tiles of one segment
 // at once, so their runs of each bucket land next to each other in HBM.  A
@@ -1332,7 +1283,6 @@ size_t layout(int kt, uint64_t n, uint32_t num_segs, bool pay, const Tuning& t, 
   const uint64_t o_cnt = take(count_max * 4);
   const uint64_t o_off = take(count_max * 4);
   const uint64_t o_par = take(scan_blocks * 8);
-  const uint64_t o_part = take(scan_blocks * 4);
   uint64_t o_cls[kNumClasses], cls_cap[kNumClasses];
   for (int c = 0; c < kNumClasses; c++) {
     const uint64_t lo = c == 0 ? 0 : h_class_max[c - 1];
@@ -1360,7 +1310,6 @@ size_t layout(int kt, uint64_t n, uint32_t num_segs, bool pay, const Tuning& t, 
     w->counts = (uint32_t*)(base + o_cnt);
     w->offsets = (uint32_t*)(base + o_off);
     w->scan_flags = (uint64_t*)(base + o_par);
-    w->scan_part = (uint32_t*)(base + o_part);
     for (int c = 0; c < kNumClasses; c++) {
       w->cls[c] = (FinalSeg*)(base + o_cls[c]);
       w->cls_cap[c] = cls_cap[c];
@@ -1440,20 +1389,25 @@ static int enqueue_typed(const void* keys_in, const uint32_t* pay_in, const uint
       return launch_rfis_class<K, F32, PAY>(c | kDirect, w, kin, pay_in, kout, perm_out, pay_out, 1, st);
     if (al == ClassAlgo::kRquick)
       return launch_rquick_class<K, F32, PAY>(c | kDirect, w, kin, pay_in, kout, perm_out, pay_out, 1, st);
-    return launch_direct<K, F32, PAY>(c, w, kin, pay_in, kout, perm_out, pay_out, st);
+    if constexpr (!PAY) return launch_direct<K, F32>(w, kin, kout, perm_out, st);
   }
   // A single-level plain sort with at most about two final buckets per CU
   // routes all of them to the largest class group that runs two workgroups
   // per CU (and the class above it), so the local sorts run in one or two
-  // launches.
+  // launches.  Other plain sorts leave out the classes of at most 1024 keys
+  // (three launches, 17 us of a 320 us sort): their buckets are about the
+  // target size, whatever the keys, so hardly any is that short.
   uint32_t cmin = 0;
-  if (!seg_off && levels == 1 && n <= (uint64_t)target * 2 * num_cu()) {
+  const bool few = !seg_off && levels == 1 && n <= (uint64_t)target * 2 * num_cu();
+  if (few) {
     while (cmin < 7 && h_class_max[cmin] < cap) cmin++;
+  } else if (!seg_off && levels > 0 && target >= 4096 && t.rfis_max <= 64 && t.rquick_max <= 64) {
+    cmin = 3;
   }
-  // a single-level sort of few buckets (cmin > 0) is latency-bound on its
+  // a single-level sort of few buckets is latency-bound on its
   // one-workgroup sample sort: 16 samples per bucket keep its buckets
   // within twice the target while halving that step
-  const uint32_t a0 = cmin ? std::min<uint32_t>(a, 16u) : a;
+  const uint32_t a0 = few ? std::min<uint32_t>(a, 16u) : a;
   // the first level's sample drawn at the start (k_start_plain), room in buffer B
   const int staged = (!seg_off && levels > 0 && n >= (uint64_t)kSplThreads * kSplItems) ? 1 : 0;
   if (!seg_off) {
@@ -1480,17 +1434,19 @@ static int enqueue_typed(const void* keys_in, const uint32_t* pay_in, const uint
     const bool last = lev + 1 == levels;
     // the level's buckets are routed by the scatter's workgroups (level_end)
     const LevelEnd le{cap, target, last ? 1u : 0u, (uint32_t)(dst + 1), ff, levels - lev - 1, cmin};
-    if (lev > 0 || seg_off) RS_LAUNCH(k_plan, 1, kPlanThreads, st, w, (int)lev, glog_small);  // level 0 of a plain sort: planned at the start
-    const uint32_t gs = grid_for(w.big_max, 4);
+    // level 0 of a plain sort is planned at the start, the others by one more
+    // workgroup of the splitter launch
+    const int plan = (lev > 0 || seg_off) ? 1 : 0;
+    const uint32_t gs = grid_for(w.big_max, 1) + plan;
     if (lev == 0) {
       // first-level bucket ids need the id buffer (two levels or more) and
       // are not taken by the payload scatter
       const int ids_ok = (w.ids != nullptr && !PAY) ? 1 : 0;
       RS_LAUNCH((k_splitters<K, F32, true, kSplThreads, kSplItems>), gs, kSplThreads, st, w, (int)lev, kin, src, a0,
-                t.seed, ids_ok, staged);
+                t.seed, ids_ok, staged, plan, glog_small);
     } else {
       RS_LAUNCH((k_splitters<K, false, false, kSplThreads, kSplItems>), gs, kSplThreads, st, w, (int)lev, kin, src, a,
-                t.seed, 0, 0);
+                t.seed, 0, 0, plan, glog_small);
     }
     // count tiles: 512 threads x 8 keys; scatter tiles: 512 x 8 (tile_log2
     // 12) or 1024 x 8 (tile_log2 13); both walk the same groups of
@@ -1502,14 +1458,7 @@ static int enqueue_typed(const void* keys_in, const uint32_t* pay_in, const uint
       RS_LAUNCH((k_count<K, F32, true, 512, 8>), gt, 512, st, w, (int)lev, kin, src);
     else
       RS_LAUNCH((k_count<K, false, false, 512, 8>), gt, 512, st, w, (int)lev, kin, src);
-    if (w.count_max <= kChainedScanMax) {
-      RS_LAUNCH(k_scan, grid_for(w.count_max / kScanChunk + 1, 4), kScanThreads, st, w);
-    } else {
-      const uint32_t gsc = grid_for(w.count_max / kScanChunk + 1, 8);
-      RS_LAUNCH(k_scan_reduce, gsc, kScanThreads, st, w);
-      RS_LAUNCH(k_scan_partials, 1, kScanTopThreads, st, w);
-      RS_LAUNCH(k_scan_down, gsc, kScanThreads, st, w);
-    }
+    RS_LAUNCH(k_scan, grid_for(w.count_max / kScanChunk + 1, 4), kScanThreads, st, w);
     if (tile_log2 == 12) {
       if (lev == 0)
         RS_LAUNCH((k_scatter<K, F32, true, PAY, 512, 8>), gs_sc, 512, st, w, (int)lev, kin, pay_in, src, dst, runs, le);
@@ -1540,10 +1489,6 @@ static int enqueue_typed(const void* keys_in, const uint32_t* pay_in, const uint
   }
   {
     const int rc = launch_local_ranks<K, F32, PAY>(ranked, w, kin, pay_in, kout, perm_out, pay_out, st);
-    if (rc) return rc;
-  }
-  {
-    const int rc = launch_oversize<K, F32, PAY>(w, kin, pay_in, kout, perm_out, pay_out, w.cls_cap[kNumClasses - 1], st);
     if (rc) return rc;
   }
   return 0;

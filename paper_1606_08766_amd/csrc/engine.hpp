@@ -56,7 +56,7 @@ struct Ctl {
   uint64_t class_keys[kNumClasses];  // keys routed to each size class
   // diagnostics of level 0, segment 0
   uint32_t l0_k;
-  uint32_t pad0;
+  uint32_t direct_rare;            // 1: a direct plain call's input is left to the merge sort
   uint64_t l0_spl_key[kMaxK];      // ordinal keys, sorted
   uint32_t l0_spl_pos[kMaxK];
   uint32_t l0_bucket[kMaxK];
@@ -73,7 +73,6 @@ struct Work {
   uint32_t* counts;      // [count_max]
   uint32_t* offsets;     // [count_max]
   uint64_t* scan_flags;  // [scan_blocks] chained-scan status of each chunk of the count matrix
-  uint32_t* scan_part;   // [scan_blocks] chunk sums of the reduce-then-scan
   FinalSeg* cls[kNumClasses];     // per size class lists
   uint64_t cls_cap[kNumClasses];
   uint32_t* buf_rec[2];  // A, B: [n] element records (ordinal key, position; see BufView)
@@ -174,8 +173,9 @@ __device__ __forceinline__ FinalSeg final_at(const Work& w, int cls, uint32_t q)
 }
 // In the direct mode no reset kernel runs: the first thread clears the status
 // and statistics of the workspace.
-__device__ __forceinline__ void direct_reset(const Work& w, int cls) {
-  if (cls < 0 && blockIdx.x == 0 && threadIdx.x == 0) {
+__device__ __forceinline__ void direct_reset(const Work& w) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    w.ctl->direct_rare = 0;
     w.ctl->status = 0;
     w.ctl->levels = 0;
     w.ctl->l0_k = 0;

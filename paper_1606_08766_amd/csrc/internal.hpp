@@ -41,21 +41,16 @@ template <typename K, bool F32, bool PAY>
 int launch_rquick_class(int c, const Work& w, const K* kin, const uint32_t* pay_in, K* kout, uint32_t* perm_out,
                         uint32_t* pay_out, uint64_t cap_c, hipStream_t st);
 
-// A plain call of one final segment, of class c (local.hip).
-template <typename K, bool F32, bool PAY>
-int launch_direct(int c, const Work& w, const K* kin, const uint32_t* pay_in, K* kout, uint32_t* perm_out,
-                  uint32_t* pay_out, hipStream_t st);
+// A plain call whose n keys fit one workgroup (local.hip).
+template <typename K, bool F32>
+int launch_direct(const Work& w, const K* kin, K* kout, uint32_t* perm_out, hipStream_t st);
 
 // The final segments of the classes in the bit mask, and then those that were
-// handed over to the merge sort (local.hip).
+// handed over to the merge sort and those longer than the LDS capacity
+// (local.hip).
 template <typename K, bool F32, bool PAY>
 int launch_local_ranks(uint32_t classes, const Work& w, const K* kin, const uint32_t* pay_in, K* kout,
                        uint32_t* perm_out, uint32_t* pay_out, hipStream_t st);
-
-// Global-memory fallback sort of final segments longer than cap (local.hip).
-template <typename K, bool F32, bool PAY>
-int launch_oversize(const Work& w, const K* kin, const uint32_t* pay_in, K* kout, uint32_t* perm_out,
-                    uint32_t* pay_out, uint64_t cap_c, hipStream_t st);
 
 // Sort of up to 2^36 keys with 64-bit positions (wide.hip).
 size_t wide_workspace_bytes(int kt, uint64_t n);

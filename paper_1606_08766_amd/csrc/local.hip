@@ -16,14 +16,6 @@ static inline uint32_t grid_for(uint64_t work, uint32_t per_cu) {
   return (uint32_t)std::max<uint64_t>(g, 1);
 }
 
-// Workgroup shape of a class kernel: THREADS x ITEMS elements.
-template <int THREADS, int ITEMS>
-struct Shape {
-  static constexpr int T = THREADS, I = ITEMS;
-};
-
-
-
 // ---------------------------------------------------------------------------
 // One segment sorted in LDS as (key, position) pairs by the merge sort: exact
 // for every input, whatever its keys.  len <= THREADS * ITEMS.  Called by
@@ -98,20 +90,6 @@ __device__ __forceinline__ void sort_pairs(const Work& w, const FinalSeg& f, con
     }
   }
   __syncthreads();
-}
-
-// A whole plain call that fits one workgroup, sorted in one launch.
-template <typename K, bool F32, bool PAY, int THREADS, int ITEMS>
-__global__ __launch_bounds__(THREADS) void k_local_sort(Work w, const K* in_keys, const uint32_t* in_pay, K* keys_out,
-                                                        uint32_t* perm_out, uint32_t* pay_out) {
-  constexpr int NP = lpad_size(THREADS * ITEMS);
-  __shared__ uint32_t s_lo[NP];
-  __shared__ uint32_t s_hi[sizeof(K) == 8 ? NP : 1];
-  __shared__ uint32_t s_v[NP];
-  __shared__ uint32_t s_p[PAY ? NP : 1];
-  direct_reset(w, -1);
-  sort_pairs<K, F32, PAY, THREADS, ITEMS>(w, final_at(w, -1, 0), LdsArr<K>{s_lo, s_hi, s_v, s_p}, in_keys, in_pay,
-                                          keys_out, perm_out, pay_out);
 }
 
 // ---------------------------------------------------------------------------
@@ -221,8 +199,12 @@ __device__ __forceinline__ void rank_ties(uint32_t* fr, uint32_t* cnt, uint32_t 
 }
 
 // Sorts the final segments of the classes in a bit mask, the longest class
-// first.
-template <typename K, bool F32, bool PAY, int THREADS, int ITEMS, int WPE>
+// first.  DIRECT: the whole input [0, n) of a plain call instead, by one
+// workgroup, which also runs the merge sort if its bins are too crowded (up to
+// kDirectPairs elements, as LDS holds pairs; longer inputs are left to
+// k_local_rare through ctl->direct_rare).
+constexpr int kDirectPairs = 8192;
+template <typename K, bool F32, bool PAY, int THREADS, int ITEMS, int WPE, bool DIRECT = false>
 __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t classes, const K* in_keys,
                                                              const uint32_t* in_pay, K* keys_out, uint32_t* perm_out,
                                                              uint32_t* pay_out) {
@@ -230,7 +212,8 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
   constexpr int LB = 31 - __builtin_clz((unsigned)N);  // 2^LB bins: one per element, or more than half
   constexpr int BPT = (1 << LB) / THREADS;
   // words, then bins; the staging area of the output uses the same memory
-  __shared__ __align__(16) uint32_t s_mem[2 * N + 8];
+  constexpr int NP = lpad_size(N);
+  __shared__ __align__(16) uint32_t s_mem[DIRECT && N <= kDirectPairs ? 3 * NP : 2 * N + 8];
   __shared__ uint32_t s_red[6 * (THREADS / kWave)];
   __shared__ uint32_t s_tmp[2 * (THREADS / kWave)];
   __shared__ uint32_t s_sum;
@@ -243,7 +226,7 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
   const int c1 = m1 ? 31 - __builtin_clz(m1) : c0;
   const uint32_t m2 = m1 & ~(1u << c1);
   const int c2 = m2 ? 31 - __builtin_clz(m2) : c1;
-  const uint32_t n0 = uniform(final_count(w, c0)), n1 = n0 + uniform(m1 ? final_count(w, c1) : 0u),
+  const uint32_t n0 = DIRECT ? 1u : uniform(final_count(w, c0)), n1 = n0 + uniform(m1 ? final_count(w, c1) : 0u),
                  total = n1 + uniform(m2 ? final_count(w, c2) : 0u);
   auto seg_at = [&](uint32_t q) -> FinalSeg* {
     return q < n0 ? w.cls[c0] + q : q < n1 ? w.cls[c1] + (q - n0) : w.cls[c2] + (q - n1);
@@ -277,7 +260,8 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
   };
   uint32_t q = blockIdx.x;
   if (q >= total) return;
-  FinalSeg f = *seg_at(q);
+  if constexpr (DIRECT) direct_reset(w);
+  FinalSeg f = DIRECT ? FinalSeg{0ull, (uint32_t)w.n, 0u} : *seg_at(q);
   load(uniform(f.len), uniform(f.src), uniform64(f.start), threadIdx.x);
   for (;;) {
     const uint32_t len = uniform(f.len), src = uniform(f.src);
@@ -287,7 +271,7 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
     // waits for them, and so would the start of every segment
     const uint32_t qn = q + gridDim.x;
     const bool more = qn < total;
-    f = *seg_at(more ? qn : q);
+    if constexpr (!DIRECT) f = *seg_at(more ? qn : q);
     // an opaque copy of the thread index: per-thread addresses are recomputed
     // per segment rather than hoisted out of the loop and kept live
     int t = threadIdx.x;
@@ -361,7 +345,14 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
     __syncthreads();
     const bool rare = bins_scan<THREADS, BPT>(bin, len, s_tmp, t) > kRankBudget * len;  // uniform
     if (rare) {
-      if (t == 0) seg_at(q)->src = src | kPairsFlag;
+      if constexpr (!DIRECT) {
+        if (t == 0) seg_at(q)->src = src | kPairsFlag;
+      } else if constexpr (N > kDirectPairs) {
+        if (t == 0) w.ctl->direct_rare = 1;
+      } else {
+        sort_pairs<K, F32, PAY, THREADS, ITEMS>(w, f, LdsArr<K>{s_mem, s_mem + NP, s_mem + 2 * NP, nullptr}, in_keys,
+                                                in_pay, keys_out, perm_out, pay_out);
+      }
     } else {
 #pragma unroll
     for (int i = 0; i < ITEMS; i++)
@@ -479,68 +470,17 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
 }
 
 // ---------------------------------------------------------------------------
-// The segments k_local_rank handed over, of every class, by the merge sort of
-// pairs: one resident-sized launch after all classes.  Each thread checks one
-// list entry and the marked ones are collected in LDS, so that the search is
-// parallel rather than a chain of dependent loads; the merge sort runs in the
-// smallest of three shapes that holds the segment.
-template <typename K, bool F32, bool PAY, int THREADS, int ITEMS>
-__global__ __launch_bounds__(THREADS) void k_local_rare(Work w, const K* in_keys, const uint32_t* in_pay, K* keys_out,
-                                                        uint32_t* perm_out, uint32_t* pay_out) {
-  constexpr int NP = lpad_size(THREADS * ITEMS);
-  __shared__ uint32_t s_lo[NP];
-  __shared__ uint32_t s_hi[sizeof(K) == 8 ? NP : 1];
-  __shared__ uint32_t s_v[NP];
-  __shared__ uint32_t s_p[PAY ? NP : 1];
-  __shared__ uint32_t s_list[THREADS];
-  __shared__ uint32_t s_n;
-  const LdsArr<K> sa{s_lo, s_hi, s_v, s_p};
-  for (int c = 0; c <= kNumClasses - 2; c++) {
-    const uint32_t cnt = final_count(w, c);
-    // neighbouring entries go to different workgroups: marked segments
-    // (the tails of a distribution) often lie next to each other
-    for (uint32_t q0 = 0; q0 < cnt; q0 += gridDim.x * THREADS) {
-      if (threadIdx.x == 0) s_n = 0;
-      __syncthreads();
-      const uint32_t q = q0 + threadIdx.x * gridDim.x + blockIdx.x;
-      if (q < cnt && (w.cls[c][q].src & kPairsFlag)) s_list[atomicAdd(&s_n, 1u)] = q;
-      __syncthreads();
-      const uint32_t n = s_n;
-      for (uint32_t k = 0; k < n; k++) {
-        FinalSeg f = w.cls[c][s_list[k]];
-        f.src &= 0xFFu;
-        if (f.len <= THREADS * ITEMS / 4)
-          sort_pairs<K, F32, PAY, THREADS, ITEMS / 4>(w, f, sa, in_keys, in_pay, keys_out, perm_out, pay_out);
-        else if (f.len <= THREADS * ITEMS / 2)
-          sort_pairs<K, F32, PAY, THREADS, ITEMS / 2>(w, f, sa, in_keys, in_pay, keys_out, perm_out, pay_out);
-        else
-          sort_pairs<K, F32, PAY, THREADS, ITEMS>(w, f, sa, in_keys, in_pay, keys_out, perm_out, pay_out);
-      }
-      __syncthreads();
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Fallback for final segments longer than cap (the balance guarantee of the
 // sampling holds only with high probability): bottom-up merge sort through
 // global memory by one workgroup, ping-ponging between the two buffers over
 // the segment's own range (that range of the other buffer is never used by
 // another segment).  Slow, exact, rare.
-template <typename K>
-struct GRun {
-  const K* k;
-  const uint32_t* v;
-  const uint32_t* p;
-};
-
+// sk, sv, sp: LDS arrays of THREADS * ITEMS values (sp: payload calls only).
 template <typename K, bool F32, bool PAY, int THREADS, int ITEMS>
-__global__ __launch_bounds__(THREADS) void k_oversize(Work w, const K* in_keys, const uint32_t* in_pay, K* keys_out,
-                                                      uint32_t* perm_out, uint32_t* pay_out) {
+__device__ __forceinline__ void sort_oversize(const Work& w, const K* in_keys, const uint32_t* in_pay, K* keys_out,
+                                              uint32_t* perm_out, uint32_t* pay_out, K* sk, uint32_t* sv,
+                                              uint32_t* sp) {
   constexpr int C = THREADS * ITEMS;
-  __shared__ K sk[C];
-  __shared__ uint32_t sv[C];
-  __shared__ uint32_t sp[C];
   const int cls = kNumClasses - 1;
   const uint32_t cnt = (uint32_t)min((uint64_t)w.ctl->class_count[cls], w.cls_cap[cls]);
   for (uint32_t q = blockIdx.x; q < cnt; q += gridDim.x) {
@@ -643,45 +583,87 @@ __global__ __launch_bounds__(THREADS) void k_oversize(Work w, const K* in_keys, 
   }
 }
 
-// A plain call that fits one workgroup (class c is the smallest that holds it).
-template <typename K, bool F32, bool PAY, int T, int I>
-static int direct_launch(const Work& w, const K* kin, const uint32_t* pay_in, K* kout, uint32_t* perm_out,
-                         uint32_t* pay_out, hipStream_t st) {
+// ---------------------------------------------------------------------------
+// What is left after all classes, in one resident-sized launch: the segments
+// k_local_rank handed over, of every class, by the merge sort of pairs, and
+// the segments longer than the LDS capacity (sort_oversize).  Each thread checks one
+// list entry and the marked ones are collected in LDS, so that the search is
+// parallel rather than a chain of dependent loads; the merge sort runs in the
+// smallest of three shapes that holds the segment.
+template <typename K, bool F32, bool PAY, int THREADS, int ITEMS>
+__global__ __launch_bounds__(THREADS) void k_local_rare(Work w, const K* in_keys, const uint32_t* in_pay, K* keys_out,
+                                                        uint32_t* perm_out, uint32_t* pay_out, int direct) {
+  constexpr int NP = lpad_size(THREADS * ITEMS);
+  constexpr int C = THREADS * 4;  // chunk of the oversize sort
+  __shared__ __align__(8) uint32_t s_lo[NP];
+  __shared__ uint32_t s_hi[sizeof(K) == 8 ? NP : 1];
+  __shared__ uint32_t s_v[NP];
+  __shared__ uint32_t s_p[PAY ? NP : 1];
+  __shared__ uint32_t s_list[THREADS];
+  __shared__ uint32_t s_n;
+  static_assert(C * sizeof(K) <= NP * 4, "the chunk's keys fit s_lo");
+  const LdsArr<K> sa{s_lo, s_hi, s_v, s_p};
+  if (direct) {  // a plain call's whole input
+    if (w.ctl->direct_rare)
+      sort_pairs<K, F32, PAY, THREADS, ITEMS>(w, FinalSeg{0ull, (uint32_t)w.n, 0u}, sa, in_keys, in_pay, keys_out,
+                                              perm_out, pay_out);
+    return;
+  }
+  for (int c = 0; c <= kNumClasses - 2; c++) {
+    const uint32_t cnt = final_count(w, c);
+    // neighbouring entries go to different workgroups: marked segments
+    // (the tails of a distribution) often lie next to each other
+    for (uint32_t q0 = 0; q0 < cnt; q0 += gridDim.x * THREADS) {
+      if (threadIdx.x == 0) s_n = 0;
+      __syncthreads();
+      const uint32_t q = q0 + threadIdx.x * gridDim.x + blockIdx.x;
+      if (q < cnt && (w.cls[c][q].src & kPairsFlag)) s_list[atomicAdd(&s_n, 1u)] = q;
+      __syncthreads();
+      const uint32_t n = s_n;
+      for (uint32_t k = 0; k < n; k++) {
+        FinalSeg f = w.cls[c][s_list[k]];
+        f.src &= 0xFFu;
+        if (f.len <= THREADS * ITEMS / 4)
+          sort_pairs<K, F32, PAY, THREADS, ITEMS / 4>(w, f, sa, in_keys, in_pay, keys_out, perm_out, pay_out);
+        else if (f.len <= THREADS * ITEMS / 2)
+          sort_pairs<K, F32, PAY, THREADS, ITEMS / 2>(w, f, sa, in_keys, in_pay, keys_out, perm_out, pay_out);
+        else
+          sort_pairs<K, F32, PAY, THREADS, ITEMS>(w, f, sa, in_keys, in_pay, keys_out, perm_out, pay_out);
+      }
+      __syncthreads();
+    }
+  }
+  sort_oversize<K, F32, PAY, THREADS, 4>(w, in_keys, in_pay, keys_out, perm_out, pay_out, reinterpret_cast<K*>(s_lo),
+                                         s_v, s_p);
+}
+
+// A plain call that fits one workgroup.  Many threads with few elements each:
+// one workgroup has the GPU to itself.
+template <typename K, bool F32, int T, int I>
+static int direct_launch(const Work& w, const K* kin, K* kout, uint32_t* perm_out, hipStream_t st) {
   static const std::string tag =
-      "(k_local_sort<K, F32, PAY, " + std::to_string(T) + ", " + std::to_string(I) + ">)";
-  RS_LAUNCH_TAGGED((k_local_sort<K, F32, PAY, T, I>), tag.c_str(), 1, T, st, w, kin, pay_in, kout, perm_out, pay_out);
+      "(k_local_rank<K, F32, PAY, " + std::to_string(T) + ", " + std::to_string(I) + ", true>)";
+  RS_LAUNCH_TAGGED((k_local_rank<K, F32, false, T, I, 4, true>), tag.c_str(), 1, T, st, w, 1u, kin, nullptr, kout,
+                   perm_out, nullptr);
+  if constexpr (T * I > kDirectPairs)
+    RS_LAUNCH((k_local_rare<K, F32, false, 768, 16>), 1, 768, st, w, kin, nullptr, kout, perm_out, nullptr, 1);
   return 0;
 }
 
-template <typename K, bool F32, bool PAY>
-int launch_direct(int c, const Work& w, const K* kin, const uint32_t* pay_in, K* kout, uint32_t* perm_out,
-                  uint32_t* pay_out, hipStream_t st) {
-  auto go = [&](auto tag) -> int {
-    constexpr int T = decltype(tag)::T, I = decltype(tag)::I;
-    return direct_launch<K, F32, PAY, T, I>(w, kin, pay_in, kout, perm_out, pay_out, st);
-  };
-  switch (c) {
-    case 0: return go(Shape<64, 1>{});
-    case 1: return go(Shape<64, 4>{});
-    case 2: return go(Shape<256, 4>{});
-    case 3: return go(Shape<256, 8>{});
-    case 4: return go(Shape<384, 8>{});
-    case 5: return go(Shape<512, 8>{});
-    case 6: return go(Shape<768, 8>{});
-    case 7: return go(Shape<1024, 8>{});
-    case 8:
-      if constexpr (!PAY) return go(Shape<768, 16>{});
-      break;
-    default:
-      break;
-  }
-  return 0;
+template <typename K, bool F32>
+int launch_direct(const Work& w, const K* kin, K* kout, uint32_t* perm_out, hipStream_t st) {
+  if (w.n <= 256) return direct_launch<K, F32, 64, 4>(w, kin, kout, perm_out, st);
+  if (w.n <= 1024) return direct_launch<K, F32, 256, 4>(w, kin, kout, perm_out, st);
+  if (w.n <= 4096) return direct_launch<K, F32, 1024, 4>(w, kin, kout, perm_out, st);
+  if (w.n <= 8192) return direct_launch<K, F32, 1024, 8>(w, kin, kout, perm_out, st);
+  return direct_launch<K, F32, 1024, 12>(w, kin, kout, perm_out, st);
 }
 
 // Classes sorted by one launch of k_local_rank, on workgroups of T threads
-// with I elements each.  per_cu: workgroups resident on a CU; the grid is four
-// times that many (each takes several segments, the next one's elements in
-// flight while it writes out; once or twice as many measured the same).
+// with I elements each, per_cu of them per CU: four times what a CU holds (each
+// takes several segments, the next one's elements in flight while it writes
+// out; once or twice as many measured the same), fewer of the one-wave
+// workgroups, whose dispatch alone took 8 us when there were 32768.
 template <typename K, bool F32, bool PAY, int T, int I, int WPE>
 static int rank_launch(uint32_t classes, uint32_t per_cu, const Work& w, const K* kin, const uint32_t* pay_in,
                        K* kout, uint32_t* perm_out, uint32_t* pay_out, hipStream_t st) {
@@ -690,7 +672,7 @@ static int rank_launch(uint32_t classes, uint32_t per_cu, const Work& w, const K
   if (!classes) return 0;
   uint64_t cap = 0;
   for (int c = 0; c < kNumClasses - 1; c++) cap += (classes >> c) & 1u ? w.cls_cap[c] : 0;
-  RS_LAUNCH_TAGGED((k_local_rank<K, F32, PAY, T, I, WPE>), tag.c_str(), grid_for(cap, per_cu * 4), T, st, w, classes,
+  RS_LAUNCH_TAGGED((k_local_rank<K, F32, PAY, T, I, WPE>), tag.c_str(), grid_for(cap, per_cu), T, st, w, classes,
                    kin, pay_in, kout, perm_out, pay_out);
   return 0;
 }
@@ -709,29 +691,27 @@ int launch_local_ranks(uint32_t classes, const Work& w, const K* kin, const uint
   int rc = 0;
   // longest segments first (a payload call has no class of 12288)
   if constexpr (PAY)
-    rc = rank_launch<K, F32, PAY, 1024, 8, 4>(classes & 0x80u, 1, w, kin, pay_in, kout, perm_out, pay_out, st);
+    rc = rank_launch<K, F32, PAY, 1024, 8, 4>(classes & 0x80u, 4, w, kin, pay_in, kout, perm_out, pay_out, st);
   else
-    rc = rank_launch<K, F32, PAY, 1024, 12, 4>(classes & 0x180u, 1, w, kin, pay_in, kout, perm_out, pay_out, st);
-  if (!rc) rc = rank_launch<K, F32, PAY, 512, 12, 4>(classes & 0x40u, 2, w, kin, pay_in, kout, perm_out, pay_out, st);
+    rc = rank_launch<K, F32, PAY, 1024, 12, 4>(classes & 0x180u, 4, w, kin, pay_in, kout, perm_out, pay_out, st);
+  if (!rc) rc = rank_launch<K, F32, PAY, 512, 12, 4>(classes & 0x40u, 8, w, kin, pay_in, kout, perm_out, pay_out, st);
   if (!rc)
-    rc = rank_launch<K, F32, PAY, 512, 8, PAY ? 4 : 6>(classes & 0x38u, 3, w, kin, pay_in, kout, perm_out, pay_out,
+    rc = rank_launch<K, F32, PAY, 512, 8, PAY ? 4 : 6>(classes & 0x38u, 12, w, kin, pay_in, kout, perm_out, pay_out,
                                                        st);
-  if (!rc) rc = rank_launch<K, F32, PAY, 256, 4, 8>(classes & 0x04u, 8, w, kin, pay_in, kout, perm_out, pay_out, st);
+  if (!rc) rc = rank_launch<K, F32, PAY, 256, 4, 8>(classes & 0x04u, 16, w, kin, pay_in, kout, perm_out, pay_out, st);
   if (!rc) rc = rank_launch<K, F32, PAY, 64, 4, 8>(classes & 0x03u, 32, w, kin, pay_in, kout, perm_out, pay_out, st);
   if (rc) return rc;
   if constexpr (PAY) {
     RS_LAUNCH((k_local_rare<K, F32, PAY, 1024, 8>), grid_for(1u << 30, 1), 1024, st, w, kin, pay_in, kout, perm_out,
-              pay_out);
+              pay_out, 0);
   } else {
     RS_LAUNCH((k_local_rare<K, F32, PAY, 768, 16>), grid_for(1u << 30, 1), 768, st, w, kin, pay_in, kout, perm_out,
-              pay_out);
+              pay_out, 0);
   }
   return 0;
 }
 
 #define RS_INST_LOCAL(K, F, P)                                                                                    \
-  template int launch_direct<K, F, P>(int, const Work&, const K*, const uint32_t*, K*, uint32_t*, uint32_t*,       \
-                                      hipStream_t);                                                                \
   template int launch_local_ranks<K, F, P>(uint32_t, const Work&, const K*, const uint32_t*, K*, uint32_t*,        \
                                            uint32_t*, hipStream_t);
 RS_INST_LOCAL(uint32_t, false, false)
@@ -741,22 +721,8 @@ RS_INST_LOCAL(uint32_t, false, true)
 RS_INST_LOCAL(uint32_t, true, true)
 RS_INST_LOCAL(uint64_t, false, true)
 
-
-template <typename K, bool F32, bool PAY>
-int launch_oversize(const Work& w, const K* kin, const uint32_t* pay_in, K* kout, uint32_t* perm_out,
-                    uint32_t* pay_out, uint64_t cap_c, hipStream_t st) {
-  RS_LAUNCH((k_oversize<K, F32, PAY, 256, 16>), grid_for(cap_c, 1), 256, st, w, kin, pay_in, kout, perm_out, pay_out);
-  return 0;
-}
-
-#define RS_INST_OVER(K, F, P)                                                                                  \
-  template int launch_oversize<K, F, P>(const Work&, const K*, const uint32_t*, K*, uint32_t*, uint32_t*, uint64_t, \
-                                        hipStream_t);
-RS_INST_OVER(uint32_t, false, false)
-RS_INST_OVER(uint32_t, true, false)
-RS_INST_OVER(uint64_t, false, false)
-RS_INST_OVER(uint32_t, false, true)
-RS_INST_OVER(uint32_t, true, true)
-RS_INST_OVER(uint64_t, false, true)
+template int launch_direct<uint32_t, false>(const Work&, const uint32_t*, uint32_t*, uint32_t*, hipStream_t);
+template int launch_direct<uint32_t, true>(const Work&, const uint32_t*, uint32_t*, uint32_t*, hipStream_t);
+template int launch_direct<uint64_t, false>(const Work&, const uint64_t*, uint64_t*, uint32_t*, hipStream_t);
 
 }  // namespace rs

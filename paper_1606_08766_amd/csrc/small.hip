@@ -62,7 +62,7 @@ __global__ __launch_bounds__(THREADS) void k_rfis(Work w, int cls, const K* in_k
   constexpr int PER = (NMAX + THREADS - 1) / THREADS;
   __shared__ T sx[NMAX];
   __shared__ uint16_t dest[NMAX];  // dest[rank] = local index of that element
-  direct_reset(w, cls);
+  if (cls < 0) direct_reset(w);
   const uint32_t cnt = final_count(w, cls);
   for (uint32_t q = blockIdx.x; q < cnt; q += gridDim.x) {
     const FinalSeg f = final_at(w, cls, q);
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(THREADS) void k_rquick(Work w, int cls, const K* in
   __shared__ uint32_t off[P], len[P], xs[P], noff[P], nlen[P];
 
   const uint32_t wv = threadIdx.x / kWave, lane = lane_id();
-  direct_reset(w, cls);
+  if (cls < 0) direct_reset(w);
   const uint32_t cnt = final_count(w, cls);
   for (uint32_t q = blockIdx.x; q < cnt; q += gridDim.x) {
     const FinalSeg f = final_at(w, cls, q);

@@ -84,3 +84,15 @@ def test_many_segments_per_workgroup():
     ko, po, plo, _ = gpu_segmented(keys, off, pay)
     ek, ep, epl = O.segmented(keys, off, pay)
     assert same_bits(ko, ek) and np.array_equal(po, ep) and np.array_equal(plo, epl)
+
+
+@pytest.mark.parametrize("kt", ["u64", "u32", "f32"])
+@pytest.mark.parametrize("form", ["wide_dup", "halves", "straddle"])
+@pytest.mark.parametrize("n", [200, 1000, 1025, 4096, 4097, 8192, 8193, 12288])
+def test_direct_calls(kt, form, n):
+    """Plain calls of one workgroup, whose crowded bins are merge sorted in the
+    same launch (up to 8192 keys) or in the next."""
+    x = _keys(form, kt, n, np.random.default_rng(n))
+    ek, ep, _ = O.sort(x)
+    ko, po = gpu_sort(x)
+    assert same_bits(ko, ek) and np.array_equal(po, ep)
