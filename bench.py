@@ -56,10 +56,10 @@ def load_traffic(name: str = "traffic.json"):
 
 
 def kernel_key(name: str) -> str:
-    """Normalise a launch tag "(k_count<K, F32, true, 256, 16>)" or a profiler
-    name "rs::k_count<unsigned long, false, true, 256, 16>(rs::Work, ...)" to
-    "k_count/l1/256/16" (count/scatter carry their level) or
-    "k_local_sort/768/8"."""
+    """Normalise a launch tag "(k_split<K, F32, true, PAY, 1024, 8>)" or a
+    profiler name "rs::k_split<unsigned long, false, true, false, 1024, 8>(...)"
+    to "k_split/l1/1024/8" (the split kernels carry their level) or
+    "k_local_rank/512/8"."""
     import re
 
     m = re.search(r"(k_[a-z_0-9]+)\s*<([^>]*)>", name)
@@ -69,17 +69,15 @@ def kernel_key(name: str) -> str:
     base, args = m.group(1), [a.strip() for a in m.group(2).split(",")]
     nums = [a for a in args if a.isdigit()]
     parts = [base]
-    if base in ("k_count", "k_scatter", "k_splitters") and len(args) > 2:
+    if base in ("k_split", "k_splitters") and len(args) > 2:
         parts.append("l1" if args[2] == "true" else "l2")
     return "/".join(parts + nums)
 
 
 def kernel_class(name: str) -> str:
     """Map a launch tag to the pass it implements."""
-    if "k_count" in name:
-        return "count_l1" if "F32, true" in name else "count_l2"
-    if "k_scatter" in name:
-        return "scatter_l1" if "F32, true" in name else "scatter_l2"
+    if "k_split<" in name:
+        return "split_l1" if "F32, true" in name else "split_l2"
     if any(s in name for s in ("k_local_sort", "k_local_rank", "k_local_rare", "k_rfis", "k_rquick", "k_oversize")):
         return "local_sort"
     if "k_splitters" in name:
@@ -92,14 +90,10 @@ def kernel_class(name: str) -> str:
 def pass_bytes_per_key(ks: int):
     """Algorithmic HBM bytes per key of each pass (read + write) for keys of
     ks bytes and u32 positions: every byte a pass must move, counted once.
-    The second level's count needs only the key (plus the position of a key
-    that ties a splitter key, not counted here); the bytes a record layout
-    or a bucket-id array adds on top show up in the measured traffic ratio."""
+    (The matrices of run lengths show up in the measured traffic ratio.)"""
     return {
-        "count_l1": ks,                 # read keys
-        "scatter_l1": ks + ks + 4,      # read keys; write (key, position)
-        "count_l2": ks,                 # read keys
-        "scatter_l2": 2 * (ks + 4),     # read and write (key, position)
+        "split_l1": ks + ks + 4,        # read keys; write (key, position)
+        "split_l2": 2 * (ks + 4),       # read and write (key, position)
         "local_sort": 2 * (ks + 4),     # read (key, position); write key + perm
     }
 
@@ -379,8 +373,7 @@ def bench_batched(args, R, torch):
     cap = 8192
     n_lv = int(sizes[sizes > cap].sum())
     n_in = n - n_lv
-    pass_bytes = {"count_l1": 8 * n_lv,                        # keys
-                  "scatter_l1": (8 + 4 + 12 + 4) * n_lv,       # key + payload in; record + payload out
+    pass_bytes = {"split_l1": (8 + 4 + 16) * n_lv,             # key + payload in; record out
                   "local_sort": (8 + 4 + 16) * n_in + (12 + 4 + 16) * n_lv}  # in; key + payload + perm out
     traffic = load_traffic("traffic_batched_1gib.json") if args.batched_variant == "1gib" else None
     passes = {}
@@ -861,7 +854,7 @@ def main():
         rd = out["ceilings"]["read"]["GB_s"]
         for c, e in out["passes"].items():
             if "GB_s" in e:
-                e["frac_of_ceiling"] = round(e["GB_s"] / (rd if c.startswith("count") else cp), 4)
+                e["frac_of_ceiling"] = round(e["GB_s"] / cp, 4)
         out.update(run_extras(args, R, torch))
     if (args.workload == "plain" and args.key_type == "u64" and not args.no_cpu_baseline
             and int(os.environ.get("RANK", "0")) == 0):

@@ -105,7 +105,7 @@ int rsort_plain64(rsort_key_t kt, const void *keys_in, uint64_t n, void *keys_ou
  * allocated by the call.
  *   n  must need at most 64 MiB of workspace, i.e.
  *      rsort_plain_workspace(kt, n) <= 64 MiB: with the default tuning up to
- *      about 2.5 million u64 keys or 3.1 million u32 / f32 keys; larger n
+ *      about 2.6 million u64 keys or 3.6 million u32 / f32 keys; larger n
  *      returns RSORT_ENOMEM before any device call.
  * Calls on one GPU share its scratch array (each call resets what it uses):
  * calls whose work overlaps on the same GPU (e.g. on two streams) race and

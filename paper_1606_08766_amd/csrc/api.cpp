@@ -177,7 +177,7 @@ int rsort_stats(const void* workspace, void* stream, uint64_t* spl_keys, uint32_
     for (int i = 0; i < rs::kMaxLevels; i++) level_max[i] = c.level_max[i];
   if (level_buckets)
     for (int i = 0; i < rs::kMaxLevels; i++) level_buckets[i] = c.level_buckets[i];
-  if (oversize) *oversize = c.class_count[rs::kNumClasses - 1];
+  if (oversize) *oversize = c.class_count[rs::kNumClasses - 1] + c.class_done[rs::kNumClasses - 1];
   return c.status;
 }
 
@@ -190,7 +190,7 @@ int rsort_class_stats(const void* workspace, void* stream, uint32_t max_classes,
   const uint32_t m = std::min<uint32_t>(max_classes, rs::kNumClasses);
   for (uint32_t i = 0; i < m; i++) {
     if (class_max) class_max[i] = rs::class_max((int)i);
-    if (buckets) buckets[i] = c.class_count[i];
+    if (buckets) buckets[i] = c.class_count[i] + c.class_done[i];
     if (keys) keys[i] = c.class_keys[i];
   }
   return (int)rs::kNumClasses;

@@ -6,15 +6,20 @@
 //   splitters  draw a*k random sample positions per segment, gather
 //              (key, position) pairs, sort them in LDS and keep every a-th
 //              as a splitter (positions break key ties, Appendix G);
-//   count      classify every element with a branchless descent of the
+//   split      classify every element with a branchless descent of the
 //              splitter tree held in LDS (a Super Scalar Sample Sort style
 //              classifier; a key equal to a splitter key is resolved by the
-//              positions) and histogram buckets per tile;
-//   scan       exclusive prefix sum of the [segment][bucket][tile] counts;
-//   scatter    re-classify, rank inside (tile, bucket) with LDS atomics,
-//              stage the tile in LDS grouped by bucket and write contiguous
-//              runs: the paper's all-to-all exchange becomes a scatter
-//              through HBM at prefix-sum offsets.
+//              positions), rank inside (tile, bucket) with LDS atomics, stage
+//              the tile in LDS grouped by bucket and write it back as one
+//              contiguous piece, with the length of each bucket's run;
+//   scan       exclusive prefix sum of the [segment][bucket][tile] run
+//              lengths: the bucket bounds, and where each run's elements
+//              stand in their bucket;
+//   route      the level's buckets: split again or sort in LDS.
+// The paper's all-to-all exchange is thus done by the readers: the next level
+// and the local sorts gather a bucket's runs, one per tile (32 elements each
+// where 256 buckets share a tile of 8192).  Elements are read and written
+// once per level; no pass counts them first.
 // Buckets at most `cap` long become final segments and are sorted, one
 // workgroup each, in LDS; the rest are split again at the next level.
 // Everything is sized on the device: no bucket size returns to the host.
@@ -67,15 +72,9 @@ __device__ __forceinline__ uint32_t logk_for(uint32_t len, uint32_t target, uint
 
 __device__ __forceinline__ void set_status(Ctl* ctl, int32_t code) { atomicCAS(&ctl->status, 0, code); }
 
-// A compile-time flag passed to a generic lambda.
-template <bool B>
-struct BoolC {
-  static constexpr bool value = B;
-};
-
-// The chained scan's per-chunk status words start at zero on every level.
-__device__ __forceinline__ void scan_flags_clear(const Work& w, uint32_t t, uint32_t nt) {
-  for (uint64_t i = t; i < w.scan_blocks; i += nt) w.scan_flags[i] = 0ull;
+// Tiles of a segment of len elements.
+__device__ __forceinline__ uint32_t tiles_of(const Work& w, uint32_t len) {
+  return (uint32_t)(((uint64_t)len + (1u << w.tile_log2) - 1) >> w.tile_log2);
 }
 
 
@@ -89,6 +88,7 @@ struct RouteLds {
   uint32_t cnt[kNumClasses + 1];
   uint32_t base[kNumClasses + 1];
   unsigned long long keys[kNumClasses];
+  uint32_t tiles, entries, tile_base, entry_base;  // of the segments to split
 };
 
 __device__ __forceinline__ void route_lds_init(RouteLds& L) {
@@ -96,16 +96,25 @@ __device__ __forceinline__ void route_lds_init(RouteLds& L) {
     L.cnt[threadIdx.x] = 0;
     if (threadIdx.x < (unsigned)kNumClasses) L.keys[threadIdx.x] = 0;
   }
+  if (threadIdx.x == 0) L.tiles = L.entries = 0;
   __syncthreads();
 }
 
-__device__ __forceinline__ void route(const Work& w, RouteLds& L, uint32_t* big_counter, BigSeg* big_list,
-                                      bool active, bool to_big, uint64_t start, uint64_t ubase, uint32_t len,
-                                      uint32_t src, uint32_t cap, uint32_t ff, uint32_t target, uint32_t left,
+__device__ __forceinline__ void route(const Work& w, RouteLds& L, int next, bool active, bool to_big, FinalSeg f,
+                                      uint64_t ubase, uint32_t cap, uint32_t ff, uint32_t target, uint32_t left,
                                       uint32_t cmin) {
-  const uint32_t c = (active && !to_big) ? class_of(len, cap, ff, cmin) : 0u;
+  const uint32_t c = (active && !to_big) ? class_of(f.len, cap, ff, cmin) : 0u;
   const uint32_t dest = to_big ? (uint32_t)kNumClasses : c;
   const uint32_t li = wave_append(L.cnt, dest, active);
+  // a segment to split takes its tiles and matrix entries of the next level
+  const bool big = active && to_big;
+  uint32_t logk = 0, tb = 0, cb = 0;
+  if (big) {
+    const uint32_t nt = tiles_of(w, f.len);
+    logk = logk_for(f.len, target, left, w.spread);
+    tb = atomicAdd(&L.tiles, nt);
+    cb = atomicAdd(&L.entries, nt << logk);
+  }
   // keys per class (statistics): one LDS atomic per distinct class per wave
   const bool af = active && !to_big;
   uint64_t pending = __ballot(af);
@@ -113,7 +122,7 @@ __device__ __forceinline__ void route(const Work& w, RouteLds& L, uint32_t* big_
     const int leader = __ffsll((unsigned long long)pending) - 1;
     const uint32_t k = __shfl(c, leader, kWave);
     const bool mine = af && c == k;
-    uint64_t sum = mine ? (uint64_t)len : 0ull;
+    uint64_t sum = mine ? (uint64_t)f.len : 0ull;
     for (int d = kWave / 2; d > 0; d >>= 1) sum += __shfl_xor(sum, d, kWave);
     if (lane_id() == (uint32_t)leader) atomicAdd(&L.keys[k], (unsigned long long)sum);
     pending &= ~__ballot(mine);
@@ -121,23 +130,28 @@ __device__ __forceinline__ void route(const Work& w, RouteLds& L, uint32_t* big_
   __syncthreads();
   if (threadIdx.x <= (unsigned)kNumClasses) {
     const uint32_t t = threadIdx.x, n = L.cnt[t];
-    uint32_t* ctr = t == (uint32_t)kNumClasses ? big_counter : &w.ctl->class_count[t];
+    uint32_t* ctr = t == (uint32_t)kNumClasses ? &w.ctl->big_count[next] : &w.ctl->class_count[t];
     L.base[t] = n ? atomicAdd(ctr, n) : 0u;
     if (t < (uint32_t)kNumClasses && L.keys[t]) atomicAdd((unsigned long long*)&w.ctl->class_keys[t], L.keys[t]);
     L.cnt[t] = 0;
     if (t < (uint32_t)kNumClasses) L.keys[t] = 0;
+    if (t == (uint32_t)kNumClasses && n) {
+      L.tile_base = atomicAdd(&w.ctl->tiles[next], L.tiles);
+      L.entry_base = atomicAdd(&w.ctl->entries[next], L.entries);
+      L.tiles = L.entries = 0;
+    }
   }
   __syncthreads();
   if (active) {
     const uint32_t i = L.base[dest] + li;
     if (to_big) {
       if (i < w.big_max)
-        big_list[i] = BigSeg{start, ubase, len, logk_for(len, target, left, w.spread)};
+        w.big[next][i] = BigSeg{f.start, ubase, f.pstart, f.len, logk, f.col, f.nt, L.tile_base + tb, L.entry_base + cb};
       else
         set_status(w.ctl, -3);  // capacity bound violated: internal error
     } else {
       if (i < w.cls_cap[c])
-        w.cls[c][i] = FinalSeg{start, len, src};
+        w.cls[c][i] = f;
       else
         set_status(w.ctl, -3);
     }
@@ -172,8 +186,8 @@ __global__ void k_init(Work w, const uint64_t* seg_off, uint32_t num_segs, uint6
     }
     const uint32_t len = active ? (uint32_t)(b - a) : 0u;
     active = active && len > 0;
-    route(w, L, &w.ctl->big_count[0], w.big[0], active, len > cap && levels > 0, a, a, len, 0u, cap, ff, target,
-          levels, cmin);
+    route(w, L, 0, active, len > cap && levels > 0, FinalSeg{a, 0ull, len, 0u, 0u, 0u}, a, cap, ff, target, levels,
+          cmin);
   }
 }
 
@@ -182,9 +196,7 @@ constexpr int kSplThreads = 1024, kSplItems = 8;  // (a = 32 at k = 256, 16 at 5
 constexpr uint32_t kStartThreads = 256;
 
 // A plain sort's start in one launch: reset the control block, route the one
-// segment [0, n) (split it, or sort it in its class), and plan level 0 when
-// it is split (one segment: its tile groups and count-matrix base are
-// immediate).  With `staged` (a split sort of at least kSplThreads *
+// segment [0, n) (split it, or sort it in its class), and give it its tiles.  With `staged` (a split sort of at least kSplThreads *
 // kSplItems keys), the workgroups also draw the first level's sample, the
 // same a0 * k positions the splitter kernel would, and store the (raw key,
 // position) records at the front of buffer B, which the first level does
@@ -203,79 +215,28 @@ __global__ __launch_bounds__(kStartThreads) void k_start_plain(Work w, uint64_t 
       // level 0, segment start 0: the stream and position of k_splitters
       const uint64_t r = rand_at(seed, 0ull, j);
       const uint64_t pos = ((r >> 32) * n) >> 32;
-      BufView<K>{w.buf_rec[1]}.put(j, in_keys[pos], (uint32_t)pos);
+      BufView<K, false>{w.buf_rec[1]}.put(j, in_keys[pos], (uint32_t)pos, 0u);
     }
     if (blockIdx.x != 0) return;
   }
   uint32_t* p = reinterpret_cast<uint32_t*>(w.ctl);
   const uint32_t nw = (uint32_t)(offsetof(Ctl, l0_spl_key) / 4);
   for (uint32_t i = threadIdx.x; i < nw; i += blockDim.x) p[i] = (i == 1) ? levels : 0u;
-  if (levels > 0) scan_flags_clear(w, threadIdx.x, blockDim.x);
   __syncthreads();
   if (threadIdx.x != 0 || n == 0) return;
   const uint32_t len = (uint32_t)n;
   if (len > cap && levels > 0) {
     const uint32_t logk = logk_for(len, target, levels, w.spread);
-    w.big[0][0] = BigSeg{0ull, 0ull, len, logk};
-    const uint32_t ng = (uint32_t)((n + (1ull << w.group_log2) - 1) >> w.group_log2);
-    w.group_base[0] = 0;
-    w.group_base[1] = ng;
-    w.count_base[0] = 0;
-    w.count_base[1] = ng << logk;
+    const uint32_t nt = tiles_of(w, len);
+    w.big[0][0] = BigSeg{0ull, 0ull, 0ull, len, logk, 0u, 0u, 0u, 0u};
     w.ctl->big_count[0] = 1;
-    w.ctl->total_groups = ng;
-    w.ctl->total_counts = ng << logk;
+    w.ctl->tiles[0] = nt;
+    w.ctl->entries[0] = nt << logk;
   } else {
     const uint32_t c = class_of(len, cap, ff, cmin);
-    w.cls[c][0] = FinalSeg{0ull, len, 0u};
+    w.cls[c][0] = FinalSeg{0ull, 0ull, len, 0u, 0u, 0u};
     w.ctl->class_count[c] = 1;
     w.ctl->class_keys[c] = n;
-  }
-}
-
-// Per level: tile groups and count-matrix bases of the segments to split, by
-// one workgroup (of the splitter launch, which needs the same lists and none
-// of this).  glog_small (levels after the first of a plain sort; 0 otherwise):
-// when the first level's scatter wrote runs of fewer than kShortRun keys on
-// average (keys spread over all buckets of every tile), this level's groups
-// hold 2^glog_small keys instead of 2^group_log2, and the count and scatter
-// passes read the choice from ctl->glog.
-constexpr uint32_t kShortRun = 128;
-template <int THREADS>
-__device__ __forceinline__ void plan_level(const Work& w, int lev, uint32_t glog_small, uint32_t* tmp) {
-  const int cur = lev & 1;
-  const uint32_t m = (uint32_t)min((uint64_t)w.ctl->big_count[cur], w.big_max);
-  const BigSeg* B = w.big[cur];
-  const uint32_t runs = w.ctl->runs;
-  const uint32_t glog = glog_small && runs && w.n / runs < kShortRun ? glog_small : w.group_log2;
-  uint32_t ct = 0, cc = 0;
-  for (uint32_t base = 0; base < m; base += THREADS) {
-    const uint32_t i = base + threadIdx.x;
-    uint32_t nt = 0, nc = 0;
-    if (i < m) {
-      nt = (uint32_t)(((uint64_t)B[i].len + (1u << glog) - 1) >> glog);  // groups
-      nc = nt << B[i].logk;
-    }
-    uint32_t tt, tc;
-    const uint32_t et = block_excl_scan<THREADS>(nt, tmp, &tt);
-    const uint32_t ec = block_excl_scan<THREADS>(nc, tmp, &tc);
-    if (i < m) {
-      w.group_base[i] = ct + et;
-      w.count_base[i] = cc + ec;
-    }
-    ct += tt;
-    cc += tc;
-  }
-  if (threadIdx.x < 16) w.ctl->queue[threadIdx.x >> 3][threadIdx.x & 7] = 0;
-  scan_flags_clear(w, threadIdx.x, THREADS);
-  if (threadIdx.x == 0) {
-    if (glog_small) w.ctl->glog = glog;
-    w.ctl->scan_next = 0;
-    w.group_base[m] = ct;
-    w.count_base[m] = cc;
-    w.ctl->total_groups = ct;
-    w.ctl->total_counts = cc;
-    w.ctl->big_count[cur ^ 1] = 0;
   }
 }
 
@@ -284,16 +245,14 @@ __device__ __forceinline__ void plan_level(const Work& w, int lev, uint32_t glog
 // (key, position) pairs are sorted in LDS and every a-th becomes a splitter.
 // The k-1 splitters are stored as an implicit binary search tree: node t at
 // depth d, index q = t - 2^d within its depth, holds splitter number
-// (2q+1) * 2^(logk-1-d) (1-based, in sorted order).
+// (2q+1) * 2^(logk-1-d) (1-based, in sorted order).  The workgroup also writes
+// down, for each of the segment's tiles, the segment and (buffer levels) the
+// run that holds the tile's first element, between which its own samples are
+// then looked up.
 constexpr uint32_t kSplRankBudget = 64;  // compares per sample the ranking path may take
-// first-level bucket ids when at least 1 / kDupIdsDiv of the splitter keys
-// equal their predecessor
-constexpr uint32_t kDupIdsDiv = 16;
-
-template <typename K, bool F32, bool SRC_IN, int THREADS, int ITEMS>
+template <typename K, bool F32, bool SRC_IN, bool PAY, int THREADS, int ITEMS>
 __global__ __launch_bounds__(THREADS) void k_splitters(Work w, int lev, const K* in_keys, int src_buf,
-                                                       uint32_t a, uint64_t seed, int ids_ok, int staged,
-                                                       int plan, uint32_t glog_small) {
+                                                       uint32_t a, uint64_t seed, int staged) {
   constexpr int N = THREADS * ITEMS;
   constexpr int NP = lpad_size(N);
   constexpr int LB = 31 - __builtin_clz((unsigned)(N / 8));  // bins of the ranking path
@@ -305,23 +264,31 @@ __global__ __launch_bounds__(THREADS) void k_splitters(Work w, int lev, const K*
   __shared__ uint32_t s_bin[(1 << LB) + 1];
   __shared__ uint32_t s_red[6 * (THREADS / kWave)];
   __shared__ uint32_t s_cost;
-  __shared__ K s_spl[kMaxK];  // level 0, segment 0: the sorted splitter keys
-  __shared__ uint32_t s_dup;
   const LdsArr<K> sa{s_lo, s_hi, s_v, nullptr};
-  if (plan && blockIdx.x == gridDim.x - 1) {  // the last workgroup plans the level
-    __shared__ uint32_t s_plan[THREADS / kWave + 1];
-    plan_level<THREADS>(w, lev, glog_small, s_plan);
-    return;
-  }
   const int cur = lev & 1;
   const uint32_t m = (uint32_t)min((uint64_t)w.ctl->big_count[cur], w.big_max);
-  const BufView<K> bv{SRC_IN ? nullptr : w.buf_rec[src_buf]};
+  const BufView<K, PAY> bv{SRC_IN ? nullptr : w.buf_rec[src_buf]};
   K* tkey = (K*)w.tree_key;
-  for (uint32_t s = blockIdx.x; s < m; s += gridDim.x - (plan ? 1u : 0u)) {
+  for (uint32_t s = blockIdx.x; s < m; s += gridDim.x) {
     const BigSeg bs = w.big[cur][s];
     // a samples per bucket, fewer when a * k would exceed the LDS sample
     const uint32_t ae = min(a, (uint32_t)(THREADS * ITEMS) >> bs.logk);
     const uint32_t S = ae << bs.logk;
+    const uint32_t ntiles = tiles_of(w, bs.len);
+    if (!SRC_IN || m > 1) {  // (the tiles of an only input segment are known to be its)
+      for (uint32_t i = threadIdx.x; i < ntiles; i += THREADS) w.tile_seg[bs.tb + i] = s;
+    }
+    if constexpr (!SRC_IN) {
+      const uint32_t *o = w.offs[src_buf] + bs.col, *rn = w.runs[src_buf] + bs.col, o0 = o[0];
+      const uint32_t half = (1u << w.tile_log2) - 1u;
+      for (uint32_t t = threadIdx.x; t < bs.nt; t += THREADS) {
+        const uint32_t c = rn[t] & 0xFFFFu, f = o[t] - o0;
+        if (c == 0) continue;
+        for (uint32_t i = (uint32_t)(((uint64_t)f + half) >> w.tile_log2); i <= (f + c - 1) >> w.tile_log2; i++)
+          w.tile_run[bs.tb + i] = t;
+      }
+      __syncthreads();  // read below
+    }
     K k[ITEMS];
     uint32_t v[ITEMS], p[ITEMS];
 #pragma unroll
@@ -329,15 +296,17 @@ __global__ __launch_bounds__(THREADS) void k_splitters(Work w, int lev, const K*
       const uint32_t j = threadIdx.x * ITEMS + i;
       if (SRC_IN && staged && j < S) {
         // drawn by k_start_plain (the same positions), stored in order
-        BufView<K>{w.buf_rec[1]}.get(j, k[i], v[i]);
+        BufView<K, false>{w.buf_rec[1]}.get(j, k[i], v[i], p[i]);
       } else if (j < S) {
         const uint64_t r = rand_at(seed, ((uint64_t)lev << 40) ^ bs.start, j);
-        const uint64_t pos = bs.start + (((r >> 32) * (uint64_t)bs.len) >> 32);
+        const uint32_t off = (uint32_t)(((r >> 32) * (uint64_t)bs.len) >> 32);
         if constexpr (SRC_IN) {
-          k[i] = in_keys[pos];  // raw bits; mapped below once all loads are issued
-          v[i] = (uint32_t)(pos - bs.ubase);
+          k[i] = in_keys[bs.start + off];  // raw bits; mapped below once all loads are issued
+          v[i] = (uint32_t)(bs.start + off - bs.ubase);
         } else {
-          bv.get(pos, k[i], v[i]);
+          const uint32_t t = off >> w.tile_log2;
+          const uint32_t r0 = w.tile_run[bs.tb + t], r1 = t + 1 < ntiles ? w.tile_run[bs.tb + t + 1] : bs.nt - 1;
+          bv.get(bs.pstart + locate(w, src_buf, bs.col, r0, r1, off), k[i], v[i], p[i]);
         }
       } else {
         k[i] = KMax<K>::v;
@@ -445,7 +414,6 @@ __global__ __launch_bounds__(THREADS) void k_splitters(Work w, int lev, const K*
               if (lev == 0 && s == 0) {
                 w.ctl->l0_spl_key[j - 1] = (uint64_t)key;
                 w.ctl->l0_spl_pos[j - 1] = idx;
-                s_spl[j - 1] = key;
               }
             }
           }
@@ -469,25 +437,10 @@ __global__ __launch_bounds__(THREADS) void k_splitters(Work w, int lev, const K*
         for (uint32_t j = threadIdx.x + 1; j < kk; j += THREADS) {
           w.ctl->l0_spl_key[j - 1] = (uint64_t)sa.key(lpad(j * ae - 1u));
           w.ctl->l0_spl_pos[j - 1] = s_v[lpad(j * ae - 1u)];
-          s_spl[j - 1] = sa.key(lpad(j * ae - 1u));
         }
       }
     }
     if (lev == 0 && s == 0 && threadIdx.x == 0) w.ctl->l0_k = kk;
-    if (lev == 0 && m == 1 && ids_ok) {  // uniform
-      // Keys that tie a splitter cost the (key, position) descent.  When the
-      // one first-level segment's splitters repeat keys (few distinct keys),
-      // its count stores each key's bucket for the scatter, which then
-      // skips the second classification; otherwise the scatter classifies
-      // again, cheaper than writing and reading the ids.
-      if (threadIdx.x == 0) s_dup = 0;
-      __syncthreads();
-      uint32_t d = 0;
-      for (uint32_t j = threadIdx.x + 1; j + 1 < kk; j += THREADS) d += s_spl[j] == s_spl[j - 1] ? 1u : 0u;
-      if (d) atomicAdd(&s_dup, d);
-      __syncthreads();
-      if (threadIdx.x == 0) w.ctl->ids0 = s_dup * kDupIdsDiv >= kk ? 1u : 0u;
-    }
     __syncthreads();
   }
 }
@@ -601,204 +554,8 @@ __device__ __forceinline__ void tree_to_lds(const Work& w, uint32_t s, uint32_t 
   if (threadIdx.x == 0 && kk > 1) tk[2 * kk - 1] = tkey[o + (((kk - 1) | kk) >> 1)];
 }
 
-__device__ __forceinline__ uint32_t find_seg(const uint32_t* base, uint32_t m, uint32_t tile) {
-  uint32_t lo = 0, hi = m;  // base[0] = 0 <= tile < base[m]
-  while (lo < hi) {
-    const uint32_t mid = (lo + hi + 1) >> 1;
-    if (base[mid] <= tile)
-      lo = mid;
-    else
-      hi = mid - 1;
-  }
-  return lo;
-}
-
-// Work queue of tile groups, XCD-aware: workgroups are dispatched round-robin
-// over the 8 XCDs, so workgroup g runs on XCD g % 8.  Each XCD owns a
-// contiguous share of the groups, and its workgroups take the next group of
-// that share from the XCD's own counter: neighbouring groups write
-// neighbouring parts of each bucket's output run (which then meet in the same
-// L2), consecutive groups of a workgroup mostly belong to the same segment
-// (whose splitter tree then stays in LDS), and a workgroup that finishes
-// early takes more, so uneven segments do not leave a tail of idle CUs.
-struct GroupQueue {
-  uint32_t* ctr;
-  uint32_t lo, hi;
-  __device__ __forceinline__ GroupQueue(uint32_t* q, uint32_t G) {
-    const uint32_t x = blockIdx.x & 7u;
-    lo = (uint32_t)(((uint64_t)G * x) >> 3);
-    hi = (uint32_t)(((uint64_t)G * (x + 1)) >> 3);
-    ctr = q + x;
-  }
-  // Called by every thread; returns the next group, or hi when the share is
-  // done.  The caller's group loop must pass a __syncthreads before the next
-  // call (slot is rewritten there).  An empty share (a level with no work,
-  // as the host launches for a batch whose segments all fit the local sort)
-  // takes no atomic: a thousand workgroups on eight counters serialise.
-  __device__ __forceinline__ uint32_t next(uint32_t* slot) {
-    if (threadIdx.x == 0) {
-      const uint32_t g = lo < hi ? lo + atomicAdd(ctr, 1u) : hi;
-      *slot = g < hi ? g : hi;
-    }
-    __syncthreads();
-    return *slot;
-  }
-};
-
-// Keys per tile group (log2) of level lev: as the host planned it, unless the
-// level's plan chose smaller groups (plan_level).
-__device__ __forceinline__ uint32_t group_log2_of(const Work& w, int lev) {
-  if (lev == 0) return w.group_log2;  // (no load on the first level)
-  const uint32_t g = w.ctl->glog;
-  return g ? g : w.group_log2;
-}
-
-// Segment a tile group belongs to, cached in LDS by the group loops below.
-struct SegCache {
-  uint32_t s, gb, gb_end, cb, seg0, logk;
-  uint64_t start, ubase;
-  uint32_t len, pad;
-};
-
-// Make sc describe the segment holding `group` (reloading its splitter tree
-// into tk/ti) if the group lies outside the cached segment.  Contains
-// __syncthreads(); called by every thread of the block.
-template <typename K, int THREADS>
-__device__ __forceinline__ void seg_for_group(const Work& w, int cur, uint32_t m, uint32_t group, SegCache& sc,
-                                              K* tk, uint32_t* ti, bool need_seg0) {
-  if (group >= sc.gb && group < sc.gb_end) return;  // uniform: sc is in LDS
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const uint32_t s = find_seg(w.group_base, m, group);
-    const BigSeg bs = w.big[cur][s];
-    sc.s = s;
-    sc.gb = w.group_base[s];
-    sc.gb_end = w.group_base[s + 1];
-    sc.cb = w.count_base[s];
-    sc.seg0 = need_seg0 ? w.offsets[sc.cb] : 0u;
-    sc.logk = bs.logk;
-    sc.start = bs.start;
-    sc.ubase = bs.ubase;
-    sc.len = bs.len;
-  }
-  __syncthreads();
-  tree_to_lds<K, THREADS>(w, sc.s, sc.logk, tk, ti);
-  __syncthreads();
-}
-
-// Occupancy: 32-bit keys fit eight waves per SIMD (at most 64 VGPRs); the
-// 64-bit instances spill at that bound and keep what the compiler chooses
-// (the first level's count got faster on tied keys but 2 us slower on the
-// latency path, the buffer level's slower on every input).
-template <typename K, bool F32, bool SRC_IN, int THREADS, int ITEMS>
-__global__ __launch_bounds__(THREADS, sizeof(K) == 4 ? 8 : 1) void k_count(Work w, int lev, const K* in_keys,
-                                                                          int src_buf) {
-  constexpr uint32_t TILE = THREADS * ITEMS;
-  static_assert(TILE <= (1u << kGroupMinLog2), "tiles divide a group");
-  const uint32_t GT = (1u << group_log2_of(w, lev)) / TILE;  // tiles per group
-  __shared__ K tk[2 * kMaxK];
-  __shared__ uint32_t ti[kMaxK];
-  __shared__ uint32_t hist[kMaxK];
-  __shared__ SegCache sc;
-  const int cur = lev & 1;
-  const uint32_t m = (uint32_t)min((uint64_t)w.ctl->big_count[cur], w.big_max);
-  const uint32_t G = w.ctl->total_groups;
-  const BufView<K> bv{SRC_IN ? nullptr : w.buf_rec[src_buf]};
-  // bucket ids for the scatter: always on a level that reads a buffer; on
-  // the first level when its splitters chose so (ids0)
-  const bool put_ids = !SRC_IN || (w.ids != nullptr && w.ctl->ids0 != 0u);
-  const uint32_t lane = lane_id();
-  if (threadIdx.x == 0) {
-    sc.gb = 1;
-    sc.gb_end = 0;  // empty: forces a load
-  }
-  for (uint32_t i = threadIdx.x; i < kMaxK; i += THREADS) hist[i] = 0;
-  __syncthreads();
-  __shared__ uint32_t s_group;
-  GroupQueue gq(w.ctl->queue[0], G);
-  bool pairs = false;  // classification mode of this wave's next tile
-  for (uint32_t group = gq.next(&s_group); group < gq.hi; group = gq.next(&s_group)) {
-    seg_for_group<K, THREADS>(w, cur, m, group, sc, tk, ti, false);
-    // the segment's fields are uniform: kept in scalar registers
-    const uint32_t gl = group - uniform(sc.gb);
-    const uint32_t slen = uniform(sc.len), slogk = uniform(sc.logk);
-    const uint64_t sstart = uniform64(sc.start);
-    const uint32_t nt = (slen + TILE - 1) / TILE;
-    const uint32_t t_end = min(nt, (gl + 1) * GT);
-    // place of a thread's item i in a tile: striped over the block, or (a
-    // level that reads a buffer) striped over the thread's wave
-    const uint32_t wbase = (threadIdx.x & ~(uint32_t)(kWave - 1)) * ITEMS, wl = threadIdx.x & (kWave - 1);
-    auto place = [&](int i) -> uint32_t {
-      return SRC_IN ? i * THREADS + threadIdx.x : wbase + i * kWave + wl;
-    };
-    // the group's histogram accumulates over its tiles
-    for (uint32_t tl = gl * GT; tl < t_end; tl++) {
-      const uint64_t base = sstart + (uint64_t)tl * TILE;
-      const uint32_t cnt = min(TILE, slen - tl * TILE);
-      K key[ITEMS];
-      bool valid[ITEMS];
-      // every lane loads (lanes past the tile's end reload its last key), so
-      // the loads are issued back to back without branches.  A level that
-      // reads a buffer gives each wave ITEMS * 64 consecutive elements, so
-      // that its byte ids form one contiguous run.
-#pragma unroll
-      for (int i = 0; i < ITEMS; i++) {
-        const uint32_t jj = place(i);
-        valid[i] = jj < cnt;
-        const uint32_t jc = min(jj, cnt - 1u);
-        if constexpr (SRC_IN)
-          key[i] = in_keys[base + jc];
-        else
-          key[i] = bv.key(base + jc);
-      }
-      if constexpr (SRC_IN && F32) {
-#pragma unroll
-        for (int i = 0; i < ITEMS; i++) key[i] = ord_of<K, F32>(key[i]);
-      }
-      uint32_t b[ITEMS];
-      const uint64_t ub = sc.ubase;
-      classify_batch<K, ITEMS>(tk, ti, slogk, key, valid,
-                               [&](int i) -> uint32_t {
-                                 const uint64_t pos = base + place(i);
-                                 if constexpr (SRC_IN)
-                                   return (uint32_t)(pos - ub);
-                                 else
-                                   return bv.idx(pos);
-                               },
-                               b, pairs);
-      if (put_ids) {
-#pragma unroll
-        for (int i = 0; i < ITEMS; i++)
-          if (valid[i]) put_bucket_id(w.ids, sstart, (uint64_t)tl * TILE + place(i), slogk, b[i]);
-      }
-      // One atomic per wave when all its elements fall into one bucket
-      // (skewed inputs).  A wave's valid elements are a prefix of its lanes,
-      // so lane 0 holds one whenever any lane does.
-#pragma unroll
-      for (int i = 0; i < ITEMS; i++) {
-        const uint32_t b0 = uniform(b[i]);
-        if (__ballot(valid[i] && b[i] != b0) == 0) {
-          const uint32_t nv = (uint32_t)__popcll(__ballot(valid[i]));
-          if (lane == 0 && nv) atomicAdd(&hist[b0], nv);
-        } else if (valid[i]) {
-          atomicAdd(&hist[b[i]], 1u);
-        }
-      }
-    }
-    __syncthreads();
-    const uint32_t kk = 1u << sc.logk;
-    const uint32_t ng = sc.gb_end - sc.gb;
-    for (uint32_t bb = threadIdx.x; bb < kk; bb += THREADS) {
-      w.counts[sc.cb + bb * ng + gl] = hist[bb];
-      hist[bb] = 0;
-    }
-    __syncthreads();
-  }
-}
-
 // ---------------------------------------------------------------------------
-// Exclusive scan of counts[0 .. total_counts) into offsets in one launch: a
-// chained scan with decoupled look-back.  Workgroups take chunks of
+// Exclusive scan of a level's run lengths into offs in one launch: a chained scan with decoupled look-back.  Workgroups take chunks of
 // kScanChunk counts in order from a counter; each publishes its chunk's sum
 // at once and, after looking back at its predecessors' published sums (or
 // inclusive prefixes), its inclusive prefix.  The first wave looks back, at 64
@@ -814,10 +571,12 @@ __global__ __launch_bounds__(THREADS, sizeof(K) == 4 ? 8 : 1) void k_count(Work 
 constexpr int kScanThreads = 256, kScanItems = 16, kScanChunk = kScanThreads * kScanItems;
 constexpr uint32_t kScanSpinMax = 1u << 26;
 
-__global__ __launch_bounds__(kScanThreads) void k_scan(Work w) {
+__global__ __launch_bounds__(kScanThreads) void k_scan(Work w, int lev) {
   __shared__ uint32_t tmp[kScanThreads / kWave + 1];
   __shared__ uint32_t s_chunk, s_prefix;
-  const uint32_t M = w.ctl->total_counts;
+  const uint32_t M = w.ctl->entries[lev & 1];
+  const uint32_t *const runs = w.runs[lev & 1], len_mask = 0xFFFFu;
+  uint32_t* const offs = w.offs[lev & 1];
   const uint32_t nb = (M + kScanChunk - 1) / kScanChunk;
   // as many workgroups as chunks take part (the others would only queue for
   // the chunk counter, at about 10 ns each)
@@ -833,14 +592,14 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(Work w) {
     for (int q = 0; q < kScanItems / 4; q++) {
       const uint32_t j = b0 + 4 * q;
       if (j + 4 <= M) {
-        const uint4 x = *reinterpret_cast<const uint4*>(w.counts + j);  // j % 4 == 0: 16-byte aligned
-        v[4 * q] = x.x;
-        v[4 * q + 1] = x.y;
-        v[4 * q + 2] = x.z;
-        v[4 * q + 3] = x.w;
+        const uint4 x = *reinterpret_cast<const uint4*>(runs + j);  // j % 4 == 0: 16-byte aligned
+        v[4 * q] = x.x & len_mask;
+        v[4 * q + 1] = x.y & len_mask;
+        v[4 * q + 2] = x.z & len_mask;
+        v[4 * q + 3] = x.w & len_mask;
       } else {
 #pragma unroll
-        for (int r = 0; r < 4; r++) v[4 * q + r] = j + r < M ? w.counts[j + r] : 0u;
+        for (int r = 0; r < 4; r++) v[4 * q + r] = j + r < M ? runs[j + r] & len_mask : 0u;
       }
     }
     uint32_t sum = 0;
@@ -893,66 +652,279 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(Work w) {
     for (int q = 0; q < kScanItems / 4; q++) {
       const uint32_t j = b0 + 4 * q;
       if (j + 4 <= M) {
-        *reinterpret_cast<uint4*>(w.offsets + j) = make_uint4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+        *reinterpret_cast<uint4*>(offs + j) = make_uint4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
       } else {
 #pragma unroll
         for (int r = 0; r < 4; r++)
-          if (j + r < M) w.offsets[j + r] = v[4 * q + r];
+          if (j + r < M) offs[j + r] = v[4 * q + r];
       }
     }
     __syncthreads();  // s_chunk / s_prefix are rewritten next
   }
 }
 
-// Exclusive scan of a tile histogram: one value per thread, non-zero only
-// in the first kMaxK threads (the bins).  Waves are scanned with DPP row
-// shifts, and the at most kMaxK / 64 bin waves joined through LDS (tmp: kMaxK
-// / 64 words), with one barrier.  Called by every thread of the block.
-__device__ __forceinline__ uint32_t bins_excl_scan(uint32_t v, uint32_t* tmp) {
-  constexpr uint32_t NW = kMaxK / kWave;
-  const uint32_t lane = lane_id(), w = threadIdx.x / kWave;
-  const uint32_t inc = wave_incl_scan_dpp(v);
-  if (w < NW && lane == kWave - 1) tmp[w] = inc;
+// ---------------------------------------------------------------------------
+// Split: one tile at a time, classify, rank inside (tile, bucket), stage by
+// bucket in LDS and write the tile back as one contiguous piece, with each
+// bucket's run (its start in the tile and length) into the level's matrix.
+//
+// Tiles are dealt out so that the workgroups of an XCD (dispatch is
+// round-robin over the 8 XCDs) work on consecutive tiles: their entries of a
+// matrix row are then written through one L2, and they share the segment's
+// splitter tree and, on a buffer level, neighbouring runs.
+//
+// The next tile's elements are loaded once this tile's are staged (into the
+// same registers) and arrive while it is written out; on a buffer level their
+// places come from a RunMap that is built between this tile's barriers, from
+// descriptors loaded a tile ahead.  All LDS that a tile's first phase writes is
+// kept twice, so that no barrier closes the loop.
+template <typename K, bool F32, bool SRC_IN, bool PAY, int THREADS, int ITEMS>
+__global__ __launch_bounds__(THREADS) void k_split(Work w, int lev, const K* in_keys, const uint32_t* in_pay,
+                                                   int src_buf, int dst_buf) {
+  using View = BufView<K, PAY>;
+  constexpr uint32_t TILE = THREADS * ITEMS;
+  constexpr int W = View::W;
+  constexpr int MAPS = SRC_IN ? 1 : 2;
+  using Map = RunMap<SRC_IN ? kWave : THREADS, SRC_IN ? kWave : (int)TILE>;
+  static_assert(THREADS >= kMaxK, "one histogram bin per thread");
+  static_assert(TILE <= (1u << 14), "run starts and lengths fit 16 bits, ranks 23");
+  __shared__ K tk[2 * kMaxK];
+  __shared__ uint32_t ti[kMaxK];
+  __shared__ uint32_t hist[2][kMaxK];
+  __shared__ uint32_t tmp[THREADS / kWave + 1];
+  __shared__ Map map[MAPS];
+  __shared__ __align__(16) uint32_t stage[TILE * W];
+
+  const int cur = lev & 1;
+  const uint32_t m = (uint32_t)min((uint64_t)w.ctl->big_count[cur], w.big_max);
+  const uint32_t G = w.ctl->tiles[cur];
+  {  // for this level's scan and the next level's lists
+    const uint32_t nb = (w.ctl->entries[cur] + kScanChunk - 1) / kScanChunk;
+    for (uint32_t i = blockIdx.x * THREADS + threadIdx.x; i < nb; i += gridDim.x * THREADS) w.scan_flags[i] = 0ull;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      w.ctl->scan_next = 0;
+      w.ctl->big_count[cur ^ 1] = 0;
+      w.ctl->tiles[cur ^ 1] = 0;
+      w.ctl->entries[cur ^ 1] = 0;
+    }
+  }
+  // the XCD's share of the tiles, dealt to its workgroups in turn
+  const uint32_t x = blockIdx.x & 7u, step = gridDim.x >> 3;
+  const uint32_t hi = (uint32_t)(((uint64_t)G * (x + 1)) >> 3);
+  uint32_t g = (uint32_t)(((uint64_t)G * x) >> 3) + (blockIdx.x >> 3);
+  if (g >= hi) return;
+
+  const int t = threadIdx.x;
+  for (int i = t; i < 2 * kMaxK; i += THREADS) (&hist[0][0])[i] = 0;
+  auto seg_of = [&](uint32_t gg) -> uint32_t { return m == 1 ? 0u : uniform(w.tile_seg[gg]); };
+  const uint32_t* const runs_in = SRC_IN ? nullptr : w.runs[src_buf];
+  const uint32_t* const offs_in = SRC_IN ? nullptr : w.offs[src_buf];
+  uint32_t* const runs_out = w.runs[cur];
+  K key[ITEMS];
+  uint32_t idx[ITEMS], pay[ITEMS];
+  // a buffer level's run of this thread for the tile to be loaded
+  struct Run {
+    uint32_t run, ofs, e, c;
+  };
+  auto run_of = [&](const BigSeg& b, uint32_t first) -> Run {
+    Run r{first + (uint32_t)t, 0u, 0u, 0u};
+    if (r.run < b.nt) {
+      const uint32_t v = runs_in[b.col + r.run];
+      r.ofs = offs_in[b.col + r.run] - offs_in[b.col];
+      r.e = v >> 16;
+      r.c = v & 0xFFFFu;
+    }
+    return r;
+  };
+  auto load = [&](const BigSeg& b, uint32_t tl, const Map& mp) {
+    const uint32_t cnt = min(TILE, b.len - tl * TILE);
+    if constexpr (SRC_IN) {
+      const uint64_t base = b.start + (uint64_t)tl * TILE;
+      const K* const kin = in_keys + base;
+      const uint32_t ib = (uint32_t)(base - b.ubase);
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++) {
+        const uint32_t p = min((uint32_t)(i * THREADS + t), cnt - 1u);
+        key[i] = at32(kin, p);  // raw bits: mapped when the tile is used, so the loads are not waited for
+        idx[i] = ib + p;
+        if constexpr (PAY) pay[i] = at32(in_pay + base, p);
+      }
+    } else {
+      const View bv{w.buf_rec[src_buf]};
+      if (mp.over == 0) {  // uniform
+#pragma unroll
+        for (int i = 0; i < ITEMS; i++) {
+          // (lanes past the end read the last element's run: their wave's
+          // words hold no bit after it)
+          const uint32_t p = i * THREADS + t;
+          const uint32_t d = i * THREADS + (t & ~(kWave - 1)) < (int)cnt ? mp.at(p) - (p < cnt ? 0u : p - cnt + 1u) : 0u;
+          bv.get(b.pstart + d, key[i], idx[i], pay[i]);
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < ITEMS; i++) {
+          const uint32_t p = min((uint32_t)(i * THREADS + t), cnt - 1u);
+          bv.get(b.pstart + locate(w, src_buf, b.col, 0, b.nt - 1, tl * TILE + p), key[i], idx[i], pay[i]);
+        }
+      }
+    }
+  };
+  auto uniform_seg = [](const BigSeg& b) -> BigSeg {
+    return BigSeg{uniform64(b.start), uniform64(b.ubase), uniform64(b.pstart), uniform(b.len), uniform(b.logk),
+                  uniform(b.col),     uniform(b.nt),      uniform(b.tb),       uniform(b.cb)};
+  };
+
+  uint32_t s = seg_of(g);
+  BigSeg bs = uniform_seg(w.big[cur][s]);
+  tree_to_lds<K, THREADS>(w, s, bs.logk, tk, ti);
+  int par = 0;
+  if constexpr (!SRC_IN) {
+    const Run r = run_of(bs, uniform(w.tile_run[g]));
+    const uint32_t j0 = (g - bs.tb) * TILE, cnt = min(TILE, bs.len - j0);
+    uint64_t bal;
+    map[0].clear(t);
+    __syncthreads();
+    map[0].mark(t, r.run, bs.nt, r.ofs, r.c, j0, cnt, bal);
+    __syncthreads();
+    map[0].number(t, r.run, r.ofs, r.e, j0, w.tile_log2, bal);
+  }
   __syncthreads();
-  uint32_t off = 0;
-  for (uint32_t q = 0; q < w && q < NW; q++) off += tmp[q];
-  return off + inc - v;
+  load(bs, g - bs.tb, map[0]);
+  bool pairs = false;  // classification mode of this wave's next tile
+  uint32_t tree_of = s;
+  for (;;) {
+    const uint32_t tl = g - bs.tb, cnt = min(TILE, bs.len - tl * TILE), kk = 1u << bs.logk;
+    uint32_t* const h = hist[par];
+    if (tree_of != s) {  // uniform; every wave has classified the tile before
+      tree_to_lds<K, THREADS>(w, s, bs.logk, tk, ti);
+      tree_of = s;
+      __syncthreads();
+    }
+    // the next tile's segment, on its way while this tile is classified
+    const uint32_t gn = g + step;
+    const bool more = gn < hi;
+    uint32_t sn = s, first = 0;
+    BigSeg bn = bs;
+    if (more) {
+      if (m > 1) {
+        sn = w.tile_seg[gn];
+        bn = w.big[cur][sn];
+      }
+      if constexpr (!SRC_IN) first = w.tile_run[gn];
+    }
+    if constexpr (!SRC_IN) map[(par ^ 1) & (MAPS - 1)].clear(t);
+    if (t < kMaxK) hist[par ^ 1][t] = 0;
+    bool valid[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; i++) valid[i] = t < (int)cnt - i * THREADS;
+    if constexpr (SRC_IN && F32) {
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++) key[i] = ord_of<K, F32>(key[i]);
+    }
+    uint32_t pos[ITEMS];  // bucket, then place in the staged tile
+    classify_batch<K, ITEMS>(tk, ti, bs.logk, key, valid, [&](int i) -> uint32_t { return idx[i]; }, pos, pairs);
+    // rank inside (tile, bucket): one LDS atomic per element, or one per wave
+    // when the whole wave falls into a single bucket (skewed inputs).  A
+    // wave's valid elements are a prefix of its lanes, so lane 0 holds one
+    // whenever any lane does.
+    const uint32_t lane = lane_id();
+#pragma unroll
+    for (int i = 0; i < ITEMS; i++) {
+      const uint32_t b0 = uniform(pos[i]);
+      uint32_t r = 0;
+      if (__ballot(valid[i] && pos[i] != b0) == 0) {
+        const uint64_t act = __ballot(valid[i]);
+        uint32_t basev = 0;
+        if (lane == 0 && act) basev = atomicAdd(&h[b0], (uint32_t)__popcll(act));
+        r = uniform(basev) + (uint32_t)__popcll(act & ((1ull << lane) - 1ull));
+      } else if (valid[i]) {
+        r = atomicAdd(&h[pos[i]], 1u);
+      }
+      pos[i] = (pos[i] << 23) | r;  // bucket < 2^9, r < TILE
+    }
+    sn = uniform(sn);
+    if (m > 1) bn = uniform_seg(bn);
+    Run rn{0u, 0u, 0u, 0u};
+    uint32_t j0 = 0, cn = 0;
+    if constexpr (!SRC_IN) {
+      if (more) {
+        rn = run_of(bn, uniform(first));
+        j0 = (gn - bn.tb) * TILE;
+        cn = min(TILE, bn.len - j0);
+      }
+    }
+    __syncthreads();
+    // exclusive scan of the tile histogram -> tile-local bucket starts
+    const uint32_t hv = t < (int)kk ? h[t] : 0u;
+    const uint32_t inc = wave_incl_scan_dpp(hv);
+    if (t < kMaxK && lane == kWave - 1) tmp[t / kWave] = inc;
+    uint64_t bal = 0;
+    if constexpr (!SRC_IN) {
+      if (more) map[par ^ 1].mark(t, rn.run, bn.nt, rn.ofs, rn.c, j0, cn, bal);
+    }
+    __syncthreads();
+    if (t < kMaxK) {
+      uint32_t ex = inc - hv;
+      for (int q = 0; q < t / kWave; q++) ex += tmp[q];
+      h[t] = ex;
+      if (t < (int)kk) runs_out[bs.cb + t * tiles_of(w, bs.len) + tl] = (ex << 16) | hv;
+    }
+    if constexpr (!SRC_IN) {
+      if (more) map[par ^ 1].number(t, rn.run, rn.ofs, rn.e, j0, w.tile_log2, bal);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ITEMS; i++) pos[i] = h[pos[i] >> 23] + (pos[i] & 0x7FFFFFu);
+#pragma unroll
+    for (int i = 0; i < ITEMS; i++)
+      if (valid[i]) View{stage}.put(pos[i], key[i], idx[i], pay[i]);
+    if (more) load(bn, gn - bn.tb, map[(par ^ 1) & (MAPS - 1)]);
+    __syncthreads();
+    // the tile, as it lies
+    {
+      uint32_t* const out = w.buf_rec[dst_buf] + (bs.start + (uint64_t)tl * TILE) * W;
+      const uint32_t words = cnt * W, quads = words / 4;
+      struct __attribute__((aligned(4))) Quad {
+        uint32_t x[4];
+      };
+      for (uint32_t q = t; q < quads; q += THREADS) {
+        const uint4 v = reinterpret_cast<const uint4*>(stage)[q];
+        at32(reinterpret_cast<Quad*>(out), q) = Quad{{v.x, v.y, v.z, v.w}};
+      }
+      if (t < (int)(words & 3u)) out[4 * quads + t] = stage[4 * quads + t];
+    }
+    if (!more) break;
+    g = gn;
+    s = sn;
+    bs = bn;
+    par ^= 1;
+  }
 }
 
-// Buckets of the finished level lev: split again or sort in LDS.  This reads
-// only the level's bucket bounds (offsets) and segment list, written before
-// its scatter, and writes only the next level's segment list, the class
-// lists and statistics, none of which the scatter reads; so the scatter's
-// workgroups do it first, each taking (segment, bucket) pairs first, first +
-// stride, ... of the m * kMaxK, instead of one more dependent launch.
-// Called by every thread of the block (route synchronizes it).
+// Buckets of the finished level lev: split again or sort in LDS.
 struct LevelEnd {
   uint32_t cap, target, last, dst_code, ff, left, cmin;
 };
-__device__ __forceinline__ void level_end(const Work& w, int lev, const LevelEnd& a, RouteLds& L, uint64_t first,
-                                          uint64_t stride) {
+constexpr int kRouteThreads = kMaxK;
+__global__ __launch_bounds__(kRouteThreads) void k_route(Work w, int lev, LevelEnd a) {
+  __shared__ RouteLds L;
   const int cur = lev & 1;
   const uint32_t m = (uint32_t)min((uint64_t)w.ctl->big_count[cur], w.big_max);
-  const uint64_t total = (uint64_t)m * kMaxK;
-  for (uint64_t g0 = first; g0 < total; g0 += stride) {
-    const uint64_t g = g0 + threadIdx.x;
-    bool active = g < total;
-    const uint32_t s = active ? (uint32_t)(g / kMaxK) : 0u, b = (uint32_t)(g % kMaxK);
-    BigSeg bs{0, 0, 0, 1};
+  if (blockIdx.x >= m) return;
+  route_lds_init(L);
+  const uint32_t* const offs = w.offs[cur];
+  for (uint32_t s = blockIdx.x; s < m; s += gridDim.x) {  // a workgroup per segment, a thread per bucket
+    const uint32_t b = threadIdx.x;
+    const BigSeg bs = w.big[cur][s];
+    const uint32_t kk = 1u << bs.logk, nt = tiles_of(w, bs.len);
+    bool active = b < kk;
     uint32_t len = 0, lo = 0;
     if (active) {
-      bs = w.big[cur][s];
-      const uint32_t kk = 1u << bs.logk;
-      active = b < kk;
-      if (active) {
-        const uint32_t ng = w.group_base[s + 1] - w.group_base[s];
-        const uint32_t cb = w.count_base[s];
-        const uint32_t seg0 = w.offsets[cb];
-        lo = w.offsets[cb + b * ng] - seg0;
-        const uint32_t hi = (b + 1 < kk) ? w.offsets[cb + (b + 1) * ng] - seg0 : bs.len;
-        len = hi - lo;
-        if (lev == 0 && s == 0) w.ctl->l0_bucket[b] = len;
-      }
+      const uint32_t seg0 = offs[bs.cb];
+      lo = offs[bs.cb + b * nt] - seg0;
+      const uint32_t hi = (b + 1 < kk) ? offs[bs.cb + (b + 1) * nt] - seg0 : bs.len;
+      len = hi - lo;
+      if (lev == 0 && s == 0) w.ctl->l0_bucket[b] = len;
     }
     if (lev < kMaxLevels) {
       // per-wave maximum and count, then one atomic per wave
@@ -967,229 +939,22 @@ __device__ __forceinline__ void level_end(const Work& w, int lev, const LevelEnd
       }
     }
     active = active && len > 0;
-    route(w, L, &w.ctl->big_count[cur ^ 1], w.big[cur ^ 1], active, len > a.cap && !a.last, bs.start + lo, bs.ubase,
-          len, a.dst_code, a.cap, a.ff, a.target, a.left, a.cmin);
+    // (the debug switch for the global-memory sort holds at the last level)
+    route(w, L, cur ^ 1, active, len > a.cap && !a.last,
+          FinalSeg{bs.start + lo, bs.start, len, a.dst_code, bs.cb + b * nt, nt}, bs.ubase, a.cap, a.last ? a.ff : 0u,
+          a.target, a.left, a.cmin);
+    __syncthreads();  // L.base is rewritten next
   }
 }
 
-// ---------------------------------------------------------------------------
-// Scatter: classify, rank inside (tile, bucket), stage by bucket in LDS and
-// write each bucket's run contiguously to the destination buffer.
-template <typename K, bool F32, bool SRC_IN, bool PAY, int THREADS, int ITEMS>
-__global__ __launch_bounds__(THREADS) void k_scatter(Work w, int lev, const K* in_keys, const uint32_t* in_pay,
-                                                     int src_buf, int dst_buf, int count_runs, LevelEnd le) {
-  constexpr uint32_t TILE = THREADS * ITEMS;  // the host launches tiles no larger than a group
-  const uint32_t GT = (1u << group_log2_of(w, lev)) / TILE;  // tiles per group
-  static_assert(THREADS >= kMaxK, "one histogram bin per thread");
-  static_assert(TILE <= (1u << 23), "ranks fit 23 bits");
-  __shared__ K tk[2 * kMaxK];
-  __shared__ uint32_t ti[kMaxK];
-  __shared__ uint32_t hist[kMaxK];
-  __shared__ uint64_t gdelta[kMaxK];
-  __shared__ uint32_t tmp[THREADS / kWave + 1];
-  __shared__ SegCache sc;
-  __shared__ K stage[TILE];
-  __shared__ uint32_t stage32[TILE];
-  __shared__ uint16_t stage_b[TILE];
-
-  const int cur = lev & 1;
-  const uint32_t m = (uint32_t)min((uint64_t)w.ctl->big_count[cur], w.big_max);
-  const uint32_t G = w.ctl->total_groups;
-  const BufView<K> bv{SRC_IN ? nullptr : w.buf_rec[src_buf]};
-  const uint32_t* bpay = SRC_IN ? in_pay : w.buf_pay[src_buf];
-  const BufView<K> dv{w.buf_rec[dst_buf]};
-  uint32_t* dpay = w.buf_pay[dst_buf];
-  // the first level reads the count pass's bucket ids when it stored them
-  // (see k_count), loaded before any store; the host allows first-level ids
-  // only for calls without a payload
-  const bool ids0 = SRC_IN && !PAY && w.ids != nullptr && w.ctl->ids0 != 0u;
-  const uint32_t lane = lane_id();
-  if (threadIdx.x == 0) {
-    sc.gb = 1;
-    sc.gb_end = 0;  // empty: forces a load
-  }
-  if (threadIdx.x < kMaxK) hist[threadIdx.x] = 0;
-  {
-    __shared__ RouteLds L;
-    route_lds_init(L);  // (its barrier also orders the stores above)
-    level_end(w, lev, le, L, (uint64_t)blockIdx.x * THREADS, (uint64_t)gridDim.x * THREADS);
-  }
-
-  __shared__ uint32_t s_group;
-  GroupQueue gq(w.ctl->queue[1], G);
-  bool pairs = false;  // classification mode of this wave's next tile
-  uint32_t runs = 0;   // runs this thread's bucket got, summed once at the end
-  for (uint32_t group = gq.next(&s_group); group < gq.hi; group = gq.next(&s_group)) {
-    seg_for_group<K, THREADS>(w, cur, m, group, sc, tk, ti, true);
-    const uint32_t gl = group - sc.gb;
-    const uint32_t ng = sc.gb_end - sc.gb;
-    const uint32_t kk = 1u << sc.logk;
-    const uint32_t t_end = min((sc.len + TILE - 1) / TILE, (gl + 1) * GT);
-    // where the group's part of bucket threadIdx.x starts; advanced by each
-    // tile's count, so the tiles' runs follow each other in group order
-    uint64_t run_off = 0;
-    if (threadIdx.x < kk) run_off = sc.start + (uint64_t)(w.offsets[sc.cb + threadIdx.x * ng + gl] - sc.seg0);
-    const BigSeg bs{sc.start, sc.ubase, sc.len, sc.logk};
-    // The group's tiles, in one of two compiled forms: IDS, reading each
-    // element's bucket from the count pass (every level that reads a buffer,
-    // and the first level when it stored them), or classifying again.
-    auto tiles = [&](auto ids_c) {
-    constexpr bool IDS = !SRC_IN || decltype(ids_c)::value;
-    // the group's tiles are loaded one ahead: the loads of tile tl + 1 are in
-    // flight while tile tl is classified, ranked and written
-    K nkey[ITEMS];
-    uint32_t nidx[ITEMS], npay[ITEMS], nb[ITEMS];
-    auto load_tile = [&](uint32_t tl) {
-      const uint64_t base = bs.start + (uint64_t)tl * TILE;
-      const uint32_t cnt = min(TILE, bs.len - tl * TILE);
-#pragma unroll
-      for (int i = 0; i < ITEMS; i++) {
-        const uint32_t jj = i * THREADS + threadIdx.x;
-        nkey[i] = K(0);
-        nidx[i] = 0;
-        npay[i] = 0;
-        nb[i] = 0;
-        if (jj < cnt) {
-          if constexpr (SRC_IN) {
-            nkey[i] = in_keys[base + jj];  // raw bits: mapped when the tile is used, so the prefetch does not wait
-            nidx[i] = (uint32_t)(base + jj - bs.ubase);
-            if constexpr (IDS) nb[i] = get_bucket_id(w.ids, bs.start, (uint64_t)tl * TILE + jj, bs.logk);
-          } else {
-            bv.get(base + jj, nkey[i], nidx[i]);
-            nb[i] = get_bucket_id(w.ids, bs.start, (uint64_t)tl * TILE + jj, bs.logk);
-          }
-          if constexpr (PAY) npay[i] = bpay[base + jj];
-        }
-      }
-    };
-    if (gl * GT < t_end) load_tile(gl * GT);
-    for (uint32_t tl = gl * GT; tl < t_end; tl++) {
-      const uint32_t cnt = min(TILE, bs.len - tl * TILE);
-      K key[ITEMS];
-      uint32_t idx[ITEMS], pay[ITEMS], pos[ITEMS], b[ITEMS];
-      bool valid[ITEMS];
-#pragma unroll
-      for (int i = 0; i < ITEMS; i++) {
-        valid[i] = i * THREADS + threadIdx.x < cnt;
-        key[i] = SRC_IN ? ord_of<K, F32>(nkey[i]) : nkey[i];
-        idx[i] = nidx[i];
-        pay[i] = npay[i];
-        b[i] = nb[i];
-      }
-      if (tl + 1 < t_end) load_tile(tl + 1);
-      if constexpr (!IDS)
-        classify_batch<K, ITEMS>(tk, ti, bs.logk, key, valid, [&](int i) -> uint32_t { return idx[i]; }, b,
-                                 pairs);
-      // rank inside (tile, bucket): one LDS atomic per element, or one per wave
-      // when the whole wave falls into a single bucket (skewed inputs).  A
-      // wave's valid elements are a prefix of its lanes, so lane 0 holds one
-      // whenever any lane does.
-#pragma unroll
-      for (int i = 0; i < ITEMS; i++) {
-        const uint32_t b0 = uniform(b[i]);
-        uint32_t r = 0;
-        if (__ballot(valid[i] && b[i] != b0) == 0) {
-          const uint64_t act = __ballot(valid[i]);
-          uint32_t basev = 0;
-          if (lane == 0 && act) basev = atomicAdd(&hist[b0], (uint32_t)__popcll(act));
-          r = uniform(basev) + (uint32_t)__popcll(act & ((1ull << lane) - 1ull));
-        } else if (valid[i]) {
-          r = atomicAdd(&hist[b[i]], 1u);
-        }
-        pos[i] = valid[i] ? ((b[i] << 23) | r) : 0xFFFFFFFFu;  // b < 2^9, r < TILE <= 2^23
-      }
-      __syncthreads();
-      // exclusive scan of the tile histogram -> tile-local bucket starts
-      {
-        const uint32_t hv = threadIdx.x < kk ? hist[threadIdx.x] : 0u;
-        runs += hv != 0u ? 1u : 0u;  // one run per non-empty bucket of a tile
-        const uint32_t e = bins_excl_scan(hv, tmp);
-        if (threadIdx.x < kk) {
-          hist[threadIdx.x] = e;
-          gdelta[threadIdx.x] = run_off - e;
-          run_off += hv;
-        }
-      }
-      __syncthreads();
-      // every item's bucket start is read before any is used (an element
-      // past the tile's end reads bin 511, inside hist, and is not staged)
-      uint32_t hb[ITEMS];
-#pragma unroll
-      for (int i = 0; i < ITEMS; i++) hb[i] = hist[pos[i] >> 23];
-#pragma unroll
-      for (int i = 0; i < ITEMS; i++) {
-        if (pos[i] != 0xFFFFFFFFu) {
-          const uint32_t bb = pos[i] >> 23;
-          const uint32_t p = hb[i] + (pos[i] & 0x7FFFFFu);
-          pos[i] = p;
-          stage[p] = key[i];
-          stage32[p] = idx[i];
-          stage_b[p] = (uint16_t)bb;
-        }
-      }
-      __syncthreads();
-      if (threadIdx.x < kMaxK) hist[threadIdx.x] = 0;  // ready for the next tile
-      // the next tile's loads complete here, before this tile's stores are
-      // issued: a wait for them after the stores would wait for the stores too
-#pragma unroll
-      for (int i = 0; i < ITEMS; i++) {
-        asm volatile("" ::"v"(nkey[i]), "v"(nidx[i]));
-        if constexpr (PAY) asm volatile("" ::"v"(npay[i]));
-        if constexpr (IDS) asm volatile("" ::"v"(nb[i]));
-      }
-      if (!PAY && cnt == TILE) {
-        // a full tile: all staged reads, then all run offsets, then the
-        // stores, so that no thread waits on one LDS round trip per element
-        // (not with a payload: its instances have no registers to spare)
-        uint32_t sb[ITEMS], si[ITEMS];
-        K sk[ITEMS];
-#pragma unroll
-        for (int i = 0; i < ITEMS; i++) {
-          const uint32_t p = i * THREADS + threadIdx.x;
-          sb[i] = stage_b[p];
-          sk[i] = stage[p];
-          si[i] = stage32[p];
-        }
-        uint64_t gd[ITEMS];
-#pragma unroll
-        for (int i = 0; i < ITEMS; i++) gd[i] = gdelta[sb[i]];
-#pragma unroll
-        for (int i = 0; i < ITEMS; i++) dv.put(gd[i] + i * THREADS + threadIdx.x, sk[i], si[i]);
-      } else {
-        for (uint32_t p = threadIdx.x; p < cnt; p += THREADS) {
-          const uint64_t g = gdelta[stage_b[p]] + p;
-          dv.put(g, stage[p], stage32[p]);
-        }
-      }
-      if constexpr (PAY) {
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < ITEMS; i++)
-          if (pos[i] != 0xFFFFFFFFu) stage32[pos[i]] = pay[i];
-        __syncthreads();
-        for (uint32_t p = threadIdx.x; p < cnt; p += THREADS) dpay[gdelta[stage_b[p]] + p] = stage32[p];
-      }
-      __syncthreads();
-    }
-    };
-    if (ids0)
-      tiles(BoolC<true>{});
-    else
-      tiles(BoolC<false>{});
-  }
-  // the first level's run count, read by the next level's plan (a kernel
-  // argument: a load here would wait for the write-out stores first)
-  if (count_runs) {
-    __shared__ uint32_t s_runs;
-    if (threadIdx.x == 0) s_runs = 0;
-    __syncthreads();
-    for (int d = kWave / 2; d > 0; d >>= 1) runs += (uint32_t)__shfl_xor((int)runs, d, kWave);
-    if (lane == 0 && runs) atomicAdd(&s_runs, runs);
-    __syncthreads();
-    if (threadIdx.x == 0 && s_runs) atomicAdd(&w.ctl->runs, s_runs);  // one global atomic per workgroup
+// Before a later level reuses the buffer that holds sorted final segments
+// (three levels or more): they leave the lists, counted.
+__global__ void k_flush(Ctl* ctl) {
+  if (threadIdx.x < (unsigned)kNumClasses) {
+    ctl->class_done[threadIdx.x] += ctl->class_count[threadIdx.x];
+    ctl->class_count[threadIdx.x] = 0;
   }
 }
-
 
 // ===========================================================================
 // Host side
@@ -1227,32 +992,10 @@ uint32_t effective_cap(const Tuning& t, bool pay) {
   return std::max<uint32_t>(cap, 64u);
 }
 
-// Keys per tile group: about four groups per CU for n keys, so that a level
-// over one segment still fills the GPU, within [2^13, 2^17].
-static uint32_t group_log2_for(uint64_t n) {
-  const uint64_t want = n / ((uint64_t)num_cu_cached() * 4);
-  uint32_t lg = kGroupMinLog2;
-  while (lg < kGroupMaxLog2 && (1ull << (lg + 1)) <= want) lg++;
-  return lg;
-}
-
-// Tile groups of the levels after the first of a plain sort hold at most
-// 2^kGroupUpLog2 keys, or 2^kGroupSmallLog2 when the first level's runs were
-// short (chosen on the device, plan_level).  Such a level splits k segments of
-// about n / k keys each, and with small groups the workgroups of an XCD,
-// which take consecutive groups, work on neighbouring tiles of one segment
-// at once, so their runs of each bucket land next to each other in HBM.  A
-// new group costs a drain of the tile prefetch and a strided read of its
-// bucket offsets: the first level (one segment, whose skewed inputs already
-// write long runs) and segmented sorts (mostly short segments, so
-// neighbouring groups seldom share one) do not recover that and keep the
-// larger groups, and inputs whose runs are long already keep 2^kGroupUpLog2.
-constexpr uint32_t kGroupUpLog2 = 14, kGroupSmallLog2 = 13;
-static uint32_t group_log2_level(uint32_t glog0, uint32_t lev, bool segmented) {
-  return (lev == 0 || segmented) ? glog0 : std::min<uint32_t>(glog0, kGroupUpLog2);
-}
-static uint32_t group_log2_small(uint32_t glog0, uint32_t lev, bool segmented) {
-  return (lev == 0 || segmented) ? 0u : std::min<uint32_t>(glog0, kGroupSmallLog2);
+// Elements per tile: 2^13, or 2^12 where that would leave CUs without a tile
+// (or by the tuning's choice).
+static uint32_t tile_log2_for(uint64_t n, const Tuning& t) {
+  return (t.tile_log2 == 12 || n < (uint64_t)num_cu_cached() * 4 << 13) ? 12u : 13u;
 }
 
 // Workspace layout: returns total bytes; fills w (pointers relative to base).
@@ -1261,12 +1004,20 @@ size_t layout(int kt, uint64_t n, uint32_t num_segs, bool pay, const Tuning& t, 
   const uint64_t ks = kt == 1 ? 8 : 4;
   const uint32_t cap = effective_cap(t, pay);
   const uint32_t levels = plan_levels(n, t, cap);
-  const uint64_t big_max = levels ? n / (cap + 1) + 1 : 0;
-  const uint32_t glog = group_log2_for(n);
-  const uint64_t groups_max = levels ? (n >> std::min<uint32_t>(glog, kGroupSmallLog2)) + big_max + 1 : 0;
-  const uint64_t count_max = groups_max * kMaxK;
+  // segments to split: each longer than cap, and of a level's at most kMaxK
+  // per segment of the level before
+  uint64_t big_max = levels ? n / (cap + 1) + 1 : 0, most = num_segs;
+  for (uint32_t l = 1; l < levels && most < big_max; l++) most *= kMaxK;
+  big_max = std::min(big_max, std::max<uint64_t>(most, levels ? 1 : 0));
+  const uint32_t tlog = tile_log2_for(n, t);
+  const uint64_t tiles_max = levels ? (n >> tlog) + big_max + 1 : 0;
+  // matrix entries: tiles * k per segment, at most kMaxK per full tile and, for
+  // the partial tile of each segment, its k (2^lq < 2 len / target + 2, see logk_for)
+  // (part: a bound of all buckets of a level)
+  const uint64_t part = std::min<uint64_t>(big_max * kMaxK, 2 * (n / effective_target(t, cap)) + 4 * big_max);
+  const uint64_t count_max = levels ? (n >> tlog) * kMaxK + part + kMaxK : 0;
   const uint64_t scan_blocks = count_max / kScanChunk + 2;
-  const uint64_t final_max = (uint64_t)num_segs + (uint64_t)levels * kMaxK * big_max + 1;
+  const uint64_t final_max = (uint64_t)num_segs + (uint64_t)levels * part + 1;
   uint64_t off = 0;
   auto take = [&](uint64_t bytes) {
     uint64_t o = off;
@@ -1276,51 +1027,50 @@ size_t layout(int kt, uint64_t n, uint32_t num_segs, bool pay, const Tuning& t, 
   const uint64_t o_ctl = take(sizeof(Ctl));
   const uint64_t o_big0 = take(big_max * sizeof(BigSeg));
   const uint64_t o_big1 = take(big_max * sizeof(BigSeg));
-  const uint64_t o_tb = take((big_max + 1) * 4);
-  const uint64_t o_cb = take((big_max + 1) * 4);
   const uint64_t o_tk = take(big_max * kMaxK * ks);
   const uint64_t o_ti = take(big_max * kMaxK * 4);
-  const uint64_t o_cnt = take(count_max * 4);
-  const uint64_t o_off = take(count_max * 4);
+  uint64_t o_run[2], o_ofs[2];
+  for (int b = 0; b < 2; b++) {  // (a second pair from two levels on)
+    o_run[b] = take((uint32_t)b < levels ? count_max * 4 : 0);
+    o_ofs[b] = take((uint32_t)b < levels ? count_max * 4 : 0);
+  }
+  const uint64_t o_ts = take(tiles_max * 4);
+  const uint64_t o_tr = take(levels >= 2 ? tiles_max * 4 : 0);
   const uint64_t o_par = take(scan_blocks * 8);
   uint64_t o_cls[kNumClasses], cls_cap[kNumClasses];
   for (int c = 0; c < kNumClasses; c++) {
     const uint64_t lo = c == 0 ? 0 : h_class_max[c - 1];
     uint64_t bound = n / (lo + 1) + 1;
     if (c == kNumClasses - 1) bound = n / (std::min<uint64_t>(cap, 64) + 1) + 1;
-    // a single-level plain sort may route all its (at most kMaxK) buckets to one class
-    cls_cap[c] = std::min<uint64_t>(final_max, std::max<uint64_t>(bound, kMaxK + 1));
+    // a single-level plain sort may route all its (at most kMaxK) buckets to
+    // the class of 8192 and the one above it
+    cls_cap[c] = std::min<uint64_t>(final_max, std::max<uint64_t>(bound, c >= 7 ? kMaxK + 1 : 0));
     o_cls[c] = take(cls_cap[c] * sizeof(FinalSeg));
   }
   const uint64_t nb = (levels || t.force_fallback) ? n : 0;
-  const uint64_t o_ids = take(levels >= 2 ? 2 * n : 0);
-  uint64_t o_bk[2], o_bp[2];
-  for (int b = 0; b < 2; b++) {
-    o_bk[b] = take(nb * (ks + 4));
-    o_bp[b] = take(pay ? nb * 4 : 0);
-  }
+  uint64_t o_bk[2];
+  for (int b = 0; b < 2; b++) o_bk[b] = take(nb * (ks + 4 + (pay ? 4 : 0)));
   if (w) {
     w->ctl = (Ctl*)(base + o_ctl);
     w->big[0] = (BigSeg*)(base + o_big0);
     w->big[1] = (BigSeg*)(base + o_big1);
-    w->group_base = (uint32_t*)(base + o_tb);
-    w->count_base = (uint32_t*)(base + o_cb);
     w->tree_key = base + o_tk;
     w->tree_idx = (uint32_t*)(base + o_ti);
-    w->counts = (uint32_t*)(base + o_cnt);
-    w->offsets = (uint32_t*)(base + o_off);
+    for (int b = 0; b < 2; b++) {
+      w->runs[b] = (uint32_t*)(base + o_run[b]);
+      w->offs[b] = (uint32_t*)(base + o_ofs[b]);
+    }
+    w->tile_seg = (uint32_t*)(base + o_ts);
+    w->tile_run = (uint32_t*)(base + o_tr);
     w->scan_flags = (uint64_t*)(base + o_par);
     for (int c = 0; c < kNumClasses; c++) {
       w->cls[c] = (FinalSeg*)(base + o_cls[c]);
       w->cls_cap[c] = cls_cap[c];
     }
-    for (int b = 0; b < 2; b++) {
-      w->buf_rec[b] = (uint32_t*)(base + o_bk[b]);
-      w->buf_pay[b] = pay ? (uint32_t*)(base + o_bp[b]) : nullptr;
-    }
-    w->ids = levels >= 2 ? (uint8_t*)(base + o_ids) : nullptr;
+    for (int b = 0; b < 2; b++) w->buf_rec[b] = (uint32_t*)(base + o_bk[b]);
     w->big_max = big_max;
-    w->group_log2 = glog;
+    w->tiles_max = tiles_max;
+    w->tile_log2 = tlog;
     w->spread = t.extra_levels > 0 ? 1u : 0u;
     w->count_max = count_max;
     w->scan_blocks = scan_blocks;
@@ -1419,79 +1169,59 @@ static int enqueue_typed(const void* keys_in, const uint32_t* pay_in, const uint
               ff, cmin);
   }
 
-  const Work w0 = w;
+  // the local sorts of every final segment listed
+  auto local_sorts = [&]() -> int {
+    uint32_t ranked = 0;  // classes ranked in bins
+    for (int c = (int)cmin; c < kNumClasses - 1; c++) {
+      // (a class can only be non-empty if its lower bound is below cap)
+      if (c > 0 && h_class_max[c - 1] >= cap) break;
+      const ClassAlgo al = class_algo(c, t);
+      int rc = 0;
+      if (al == ClassAlgo::kRank)
+        ranked |= 1u << c;
+      else if (al == ClassAlgo::kRfis)
+        rc = launch_rfis_class<K, F32, PAY>(c, w, kin, pay_in, kout, perm_out, pay_out, w.cls_cap[c], st);
+      else
+        rc = launch_rquick_class<K, F32, PAY>(c, w, kin, pay_in, kout, perm_out, pay_out, w.cls_cap[c], st);
+      if (rc) return rc;
+    }
+    return launch_local_ranks<K, F32, PAY>(ranked, w, kin, pay_in, kout, perm_out, pay_out, st);
+  };
   for (uint32_t lev = 0; lev < levels; lev++) {
-    // the level's tile groups; scatter tiles are at most a tile group
-    Work w = w0;
-    w.group_log2 = group_log2_level(w0.group_log2, lev, seg_off != nullptr);
-    const uint32_t glog_small = group_log2_small(w0.group_log2, lev, seg_off != nullptr);
-    // the first level of a plain sort with more levels counts its runs for the next plan
-    const int runs = (lev == 0 && levels > 1 && !seg_off) ? 1 : 0;
-    const uint32_t tile_log2 = (t.tile_log2 == 12 || std::min(w.group_log2, glog_small ? glog_small : 99u) < 13) ? 12 : 13;
-    const uint64_t groups_max = (n >> (glog_small ? glog_small : w.group_log2)) + w.big_max + 1;
     const int dst = lev & 1;
     const int src = (lev + 1) & 1;  // buffer written by the previous level
     const bool last = lev + 1 == levels;
-    // the level's buckets are routed by the scatter's workgroups (level_end)
     const LevelEnd le{cap, target, last ? 1u : 0u, (uint32_t)(dst + 1), ff, levels - lev - 1, cmin};
-    // level 0 of a plain sort is planned at the start, the others by one more
-    // workgroup of the splitter launch
-    const int plan = (lev > 0 || seg_off) ? 1 : 0;
-    const uint32_t gs = grid_for(w.big_max, 1) + plan;
-    if (lev == 0) {
-      // first-level bucket ids need the id buffer (two levels or more) and
-      // are not taken by the payload scatter
-      const int ids_ok = (w.ids != nullptr && !PAY) ? 1 : 0;
-      RS_LAUNCH((k_splitters<K, F32, true, kSplThreads, kSplItems>), gs, kSplThreads, st, w, (int)lev, kin, src, a0,
-                t.seed, ids_ok, staged, plan, glog_small);
-    } else {
-      RS_LAUNCH((k_splitters<K, false, false, kSplThreads, kSplItems>), gs, kSplThreads, st, w, (int)lev, kin, src, a,
-                t.seed, 0, 0, plan, glog_small);
-    }
-    // count tiles: 512 threads x 8 keys; scatter tiles: 512 x 8 (tile_log2
-    // 12) or 1024 x 8 (tile_log2 13); both walk the same groups of
-    // 2^group_log2 keys.  Grids are multiples of 8 for the XCD-aware walk.
-    // resident-sized grids: the workgroups take groups from the queues
-    const uint32_t gt = std::max<uint32_t>(8u, grid_for(groups_max, 4) & ~7u);
-    const uint32_t gs_sc = std::max<uint32_t>(8u, grid_for(groups_max, tile_log2 == 12 ? 2 : 1) & ~7u);
+    const uint32_t gs = grid_for(w.big_max, 1);
     if (lev == 0)
-      RS_LAUNCH((k_count<K, F32, true, 512, 8>), gt, 512, st, w, (int)lev, kin, src);
+      RS_LAUNCH((k_splitters<K, F32, true, PAY, kSplThreads, kSplItems>), gs, kSplThreads, st, w, (int)lev, kin, src,
+                a0, t.seed, staged);
     else
-      RS_LAUNCH((k_count<K, false, false, 512, 8>), gt, 512, st, w, (int)lev, kin, src);
-    RS_LAUNCH(k_scan, grid_for(w.count_max / kScanChunk + 1, 4), kScanThreads, st, w);
-    if (tile_log2 == 12) {
-      if (lev == 0)
-        RS_LAUNCH((k_scatter<K, F32, true, PAY, 512, 8>), gs_sc, 512, st, w, (int)lev, kin, pay_in, src, dst, runs, le);
-      else
-        RS_LAUNCH((k_scatter<K, false, false, PAY, 512, 8>), gs_sc, 512, st, w, (int)lev, kin, pay_in, src, dst, 0, le);
-    } else {
-      if (lev == 0)
-        RS_LAUNCH((k_scatter<K, F32, true, PAY, 1024, 8>), gs_sc, 1024, st, w, (int)lev, kin, pay_in, src, dst, runs, le);
-      else
-        RS_LAUNCH((k_scatter<K, false, false, PAY, 1024, 8>), gs_sc, 1024, st, w, (int)lev, kin, pay_in, src, dst, 0, le);
+      RS_LAUNCH((k_splitters<K, false, false, PAY, kSplThreads, kSplItems>), gs, kSplThreads, st, w, (int)lev, kin,
+                src, a, t.seed, 0);
+    if (lev >= 2) {  // the level writes over the buffer and matrices of level lev - 2
+      const int rc = local_sorts();
+      if (rc) return rc;
+      RS_LAUNCH(k_flush, 1, kWave, st, w.ctl);
     }
+    // resident-sized grids, multiples of 8 for the XCD-aware walk
+    if (w.tile_log2 == 12) {
+      const uint32_t g = std::max<uint32_t>(8u, grid_for(w.tiles_max, 2) & ~7u);
+      if (lev == 0)
+        RS_LAUNCH((k_split<K, F32, true, PAY, 512, 8>), g, 512, st, w, (int)lev, kin, pay_in, src, dst);
+      else
+        RS_LAUNCH((k_split<K, false, false, PAY, 512, 8>), g, 512, st, w, (int)lev, kin, pay_in, src, dst);
+    } else {
+      const uint32_t g = std::max<uint32_t>(8u, grid_for(w.tiles_max, 1) & ~7u);
+      if (lev == 0)
+        RS_LAUNCH((k_split<K, F32, true, PAY, 1024, 8>), g, 1024, st, w, (int)lev, kin, pay_in, src, dst);
+      else
+        RS_LAUNCH((k_split<K, false, false, PAY, 1024, 8>), g, 1024, st, w, (int)lev, kin, pay_in, src, dst);
+    }
+    RS_LAUNCH(k_scan, grid_for(w.count_max / kScanChunk + 1, 4), kScanThreads, st, w, (int)lev);
+    RS_LAUNCH(k_route, gs, kRouteThreads, st, w, (int)lev, le);
   }
-
-  // final segments by size class (a class can only be non-empty if its lower
-  // bound is below cap)
-  uint32_t ranked = 0;  // classes ranked in bins
-  for (int c = (int)cmin; c < kNumClasses - 1; c++) {
-    if (c > 0 && h_class_max[c - 1] >= cap) break;
-    const ClassAlgo al = class_algo(c, t);
-    int rc = 0;
-    if (al == ClassAlgo::kRank)
-      ranked |= 1u << c;
-    else if (al == ClassAlgo::kRfis)
-      rc = launch_rfis_class<K, F32, PAY>(c, w, kin, pay_in, kout, perm_out, pay_out, w.cls_cap[c], st);
-    else
-      rc = launch_rquick_class<K, F32, PAY>(c, w, kin, pay_in, kout, perm_out, pay_out, w.cls_cap[c], st);
-    if (rc) return rc;
-  }
-  {
-    const int rc = launch_local_ranks<K, F32, PAY>(ranked, w, kin, pay_in, kout, perm_out, pay_out, st);
-    if (rc) return rc;
-  }
-  return 0;
+  return local_sorts();
 }
 
 int enqueue_sort(int kt, const void* keys_in, const uint32_t* pay_in, const uint64_t* seg_off, uint32_t num_segs,

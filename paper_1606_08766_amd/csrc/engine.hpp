@@ -7,6 +7,8 @@
 
 #include <type_traits>
 
+#include "device.hpp"
+
 namespace rs {
 
 constexpr int kMaxLogK = 9;               // at most 512 buckets per level
@@ -14,27 +16,37 @@ constexpr int kMaxK = 1 << kMaxLogK;
 constexpr int kMaxLevels = 8;
 constexpr int kNumClasses = 10;           // final-bucket size classes (see the class table in engine.hip)
 constexpr uint32_t kMaxOversample = 32;
-// A segment's keys are handled in aligned groups of 2^group_log2 keys (a
-// power of two between kGroupMinLog2 and kGroupMaxLog2, chosen per call so
-// that the groups of n keys occupy the whole GPU), each by one workgroup;
-// histograms and offsets are kept per (bucket, group), so the count and
-// scatter passes may use different tile sizes inside a group.
-constexpr uint32_t kGroupMinLog2 = 12, kGroupMaxLog2 = 17;
+
+// A level splits every segment tile by tile: each tile of 2^tile_log2
+// elements is sorted by bucket and written back as one contiguous piece, and
+// the level's matrices say, for every (segment, bucket, tile) in that order,
+// where in the tile the bucket's run starts and how long it is (runs: start
+// << 16 | length) and how many elements of the segment lie before it in bucket
+// order (offs, a running sum; only differences within a segment count).  A
+// bucket is read back as its runs, one per tile.
 
 // A segment that the current level splits.
 struct BigSeg {
-  uint64_t start;  // global position of the first element
-  uint64_t ubase;  // position of the user segment start (input-sourced levels: idx = pos - ubase)
-  uint32_t len;    // number of elements
-  uint32_t logk;   // this segment is split into 1 << logk buckets
+  uint64_t start;   // global position of the first element
+  uint64_t ubase;   // position of the user segment start (input-sourced levels: idx = pos - ubase)
+  uint64_t pstart;  // start of the segment it is a bucket of (buffer levels)
+  uint32_t len;     // number of elements
+  uint32_t logk;    // this segment is split into 1 << logk buckets
+  uint32_t col;     // buffer levels: its first entry in the previous level's matrices,
+  uint32_t nt;      // and its runs there
+  uint32_t tb;      // its first tile among the level's tiles
+  uint32_t cb;      // its first entry in the level's matrices
 };
 
 // A bucket (or a whole user segment) that is sorted in one workgroup.
 struct FinalSeg {
   uint64_t start;
+  uint64_t pstart;  // buffer segments: start of the segment it is a bucket of
   uint32_t len;
-  uint32_t src;  // low byte: 0 caller input (positions implicit), 1 buffer A, 2 buffer B;
+  uint32_t src;  // low byte: 0 caller input (positions implicit), 1 buffer A, 2 buffer B (and the
+                 // matrices of the same number);
                  // kPairsFlag: handed from the ranking in bins to the merge sort
+  uint32_t col, nt;  // as in BigSeg
 };
 constexpr uint32_t kPairsFlag = 0x100;
 
@@ -43,13 +55,11 @@ struct Ctl {
   int32_t status;                  // RSORT_OK or a device-detected error
   uint32_t levels;                 // levels enqueued by the host
   uint32_t big_count[2];           // ping-pong lists of segments to split
-  uint32_t total_groups;           // tile groups of the current level
-  uint32_t total_counts;           // entries of the current level's count matrix
-  uint32_t scan_next;              // next chunk of the count matrix to scan (chained scan)
-  uint32_t runs;                   // (tile, bucket) runs the first level's scatter wrote
-  uint32_t glog;                   // log2 keys per tile group of the levels after the first (0: as planned)
-  uint32_t ids0;                   // 1: the first level (one segment) passes bucket ids from count to scatter
-  uint32_t queue[2][8];            // per-XCD tile-group queues of the count and scatter passes
+  uint32_t tiles[2];               // tiles and matrix entries of the levels (ping-pong, as big_count)
+  uint32_t entries[2];
+  uint32_t scan_next;              // next chunk of the run lengths to scan (chained scan)
+  uint32_t rare_done;              // workgroups of k_local_rare that are through (if there are oversize segments)
+  uint32_t class_done[kNumClasses];   // final segments already sorted before a later level (three levels or more)
   uint32_t class_count[kNumClasses];  // final segments per size class (last = oversize)
   uint32_t level_max[kMaxLevels];  // largest bucket created per level
   uint32_t level_buckets[kMaxLevels];
@@ -66,37 +76,20 @@ struct Ctl {
 struct Work {
   Ctl* ctl;
   BigSeg* big[2];
-  uint32_t* group_base;  // [big_max + 1] first tile group of each segment
-  uint32_t* count_base;  // [big_max + 1]
   void* tree_key;        // [big_max * kMaxK] (K), node t of segment s at s*kMaxK + t
   uint32_t* tree_idx;
-  uint32_t* counts;      // [count_max]
-  uint32_t* offsets;     // [count_max]
-  uint64_t* scan_flags;  // [scan_blocks] chained-scan status of each chunk of the count matrix
+  uint32_t* runs[2];     // [count_max] matrices of the even and odd levels
+  uint32_t* offs[2];     // [count_max]
+  uint32_t* tile_seg;    // [tiles_max] segment of each of the level's tiles
+  uint32_t* tile_run;    // [tiles_max] buffer levels: the run that holds the tile's first element
+  uint64_t* scan_flags;  // [scan_blocks] chained-scan status of each chunk of the run lengths
   FinalSeg* cls[kNumClasses];     // per size class lists
   uint64_t cls_cap[kNumClasses];
-  uint32_t* buf_rec[2];  // A, B: [n] element records (ordinal key, position; see BufView)
-  uint32_t* buf_pay[2];  // [n] (payload calls only)
-  uint8_t* ids;          // [2 n] bucket of each element of a buffer level (see bucket ids below)
-  uint64_t big_max, count_max, scan_blocks, n;
-  uint32_t group_log2;   // log2 of the keys per tile group
+  uint32_t* buf_rec[2];  // A, B: [n] element records (ordinal key, position[, payload]; see BufView)
+  uint64_t big_max, tiles_max, count_max, scan_blocks, n;
+  uint32_t tile_log2;    // log2 of the elements per tile
   uint32_t spread;       // 1: the plan has extra levels, and segments spread their buckets over them
 };
-
-// Bucket ids of a level that reads a buffer: the count pass stores the
-// bucket of the element at buffer position p of a segment starting at s in
-// the segment's own byte range [2 s, 2 s + 2 len) of ids: one byte at 2 s + (p - s)
-// when the segment has at most 256 buckets, else two at 2 s + 2 (p - s).  The
-// scatter reads them instead of classifying again.
-__device__ __forceinline__ void put_bucket_id(uint8_t* ids, uint64_t s, uint64_t r, uint32_t logk, uint32_t b) {
-  if (logk <= 8)
-    ids[2 * s + r] = (uint8_t)b;
-  else
-    ((uint16_t*)(ids + 2 * s))[r] = (uint16_t)b;
-}
-__device__ __forceinline__ uint32_t get_bucket_id(const uint8_t* ids, uint64_t s, uint64_t r, uint32_t logk) {
-  return logk <= 8 ? (uint32_t)ids[2 * s + r] : (uint32_t)((const uint16_t*)(ids + 2 * s))[r];
-}
 
 // a[i] with a scalar base and a 32-bit byte offset (i * sizeof(T) < 2^32).
 template <typename T>
@@ -105,15 +98,26 @@ __device__ __forceinline__ T& at32(T* a, uint32_t i) {
   return *reinterpret_cast<T*>(reinterpret_cast<C*>(a) + (uint32_t)(i * (uint32_t)sizeof(T)));
 }
 
-// The element buffers of the levels interleave each element's ordinal key
-// and input position in one record of 32-bit words (key low, key high for
-// 64-bit keys, then the position), so that one memory instruction moves a
-// whole element; a scatter writes half as many partial lines as with
-// separate key and position arrays.
-template <typename K>
+// The element buffers of the levels interleave each element's ordinal key,
+// its input position and, in payload calls, its payload in one record of
+// 32-bit words (key low, key high for 64-bit keys, position, payload), so that
+// one memory instruction moves a whole element.
+template <typename K, bool PAY>
 struct BufView {
-  static constexpr int W = (int)(sizeof(K) / 4) + 1;  // words per record
+  static constexpr int KW = (int)(sizeof(K) / 4);
+  static constexpr int W = KW + 1 + (PAY ? 1 : 0);  // words per record
   uint32_t* p;
+  struct Rec {
+    uint32_t x[W];
+  };
+  static __device__ __forceinline__ void unpack(const Rec& r, K& k, uint32_t& v, uint32_t& y) {
+    if constexpr (sizeof(K) == 8)
+      k = ((uint64_t)r.x[1] << 32) | r.x[0];
+    else
+      k = r.x[0];
+    v = r.x[KW];
+    if constexpr (PAY) y = r.x[KW + 1];
+  }
   __device__ __forceinline__ K key(uint64_t i) const {
     const uint32_t* r = p + i * W;
     if constexpr (sizeof(K) == 8)
@@ -121,42 +125,130 @@ struct BufView {
     else
       return r[0];
   }
-  __device__ __forceinline__ uint32_t idx(uint64_t i) const { return p[i * W + W - 1]; }
-  __device__ __forceinline__ void get(uint64_t i, K& k, uint32_t& v) const {
-    const uint32_t* r = p + i * W;
-    if constexpr (sizeof(K) == 8) {
-      const uint32_t a = r[0], b = r[1], c = r[2];
-      k = ((uint64_t)b << 32) | a;
-      v = c;
-    } else {
-      const uint32_t a = r[0], c = r[1];
-      k = a;
-      v = c;
-    }
+  __device__ __forceinline__ uint32_t idx(uint64_t i) const { return p[i * W + KW]; }
+  __device__ __forceinline__ uint32_t pay(uint64_t i) const { return PAY ? p[i * W + W - 1] : 0u; }
+  __device__ __forceinline__ void get(uint64_t i, K& k, uint32_t& v, uint32_t& y) const {
+    unpack(*reinterpret_cast<const Rec*>(p + i * W), k, v, y);
   }
-  // get with a scalar base and a 32-bit byte offset
-  __device__ __forceinline__ void get32(uint32_t i, K& k, uint32_t& v) const {
-    struct Rec {
-      uint32_t x[W];
-    };
-    const Rec r = at32(reinterpret_cast<const Rec*>(p), i);
-    if constexpr (sizeof(K) == 8)
-      k = ((uint64_t)r.x[1] << 32) | r.x[0];
-    else
-      k = r.x[0];
-    v = r.x[W - 1];
-  }
-  __device__ __forceinline__ void put(uint64_t i, K k, uint32_t v) const {
-    uint32_t* r = p + i * W;
-    r[0] = (uint32_t)k;
-    if constexpr (sizeof(K) == 8) r[1] = (uint32_t)((uint64_t)k >> 32);
-    r[W - 1] = v;
+  __device__ __forceinline__ void put(uint64_t i, K k, uint32_t v, uint32_t y) const {
+    Rec r;
+    r.x[0] = (uint32_t)k;
+    if constexpr (sizeof(K) == 8) r.x[1] = (uint32_t)((uint64_t)k >> 32);
+    r.x[KW] = v;
+    if constexpr (PAY) r.x[KW + 1] = y;
+    *reinterpret_cast<Rec*>(p + i * W) = r;
   }
 };
-template <typename K>
-__device__ __forceinline__ BufView<K> buf_view(const Work& w, int b) {
-  return BufView<K>{w.buf_rec[b]};
+
+// Place, from the start of the segment it is a bucket of, of a bucket's
+// element j: in the last of its runs lo .. hi that starts at or before j.
+// (For single elements; whole buckets are read through a RunMap.)
+__device__ __forceinline__ uint32_t locate(const Work& w, int m, uint32_t col, uint32_t lo, uint32_t hi, uint32_t j) {
+  const uint32_t* o = w.offs[m] + col;
+  const uint32_t o0 = o[0];
+  while (lo < hi) {
+    const uint32_t mid = (lo + hi + 1) >> 1;
+    if (o[mid] - o0 <= j)
+      lo = mid;
+    else
+      hi = mid - 1;
+  }
+  return (lo << w.tile_log2) + (w.runs[m][col + lo] >> 16) + (j - (o[lo] - o0));
 }
+
+// Reads a final segment element by element (the rare paths and the sorts of
+// small classes).
+template <typename K, bool F32, bool PAY>
+struct SegReader {
+  const Work& w;
+  const FinalSeg& f;
+  const K* in_keys;
+  const uint32_t* in_pay;
+  __device__ __forceinline__ uint64_t at(uint32_t j) const {
+    return f.pstart + locate(w, (int)(f.src & 0xFFu) - 1, f.col, 0, f.nt - 1, j);
+  }
+  __device__ __forceinline__ void get(uint32_t j, K& k, uint32_t& v) const {
+    if (f.src & 0xFFu) {
+      uint32_t y;
+      BufView<K, PAY>{w.buf_rec[(f.src & 0xFFu) - 1]}.get(at(j), k, v, y);
+    } else {
+      k = load_ord<K, F32>(in_keys, f.start + j);
+      v = j;
+    }
+  }
+  __device__ __forceinline__ uint32_t pay(uint32_t j) const {
+    if constexpr (!PAY) return 0u;
+    return (f.src & 0xFFu) ? BufView<K, PAY>{w.buf_rec[(f.src & 0xFFu) - 1]}.pay(at(j)) : in_pay[f.start + j];
+  }
+};
+
+// Where the elements of a bucket, or of a stretch [j0, j0 + cnt) of one, lie:
+// built by a workgroup in LDS from the bucket's runs, one thread per run, in
+// three steps with a barrier after each, and then read by whole waves, each
+// over 64 consecutive elements.  mask holds a bit for each element that is the
+// first of its run (or of the stretch), base the bits before each of its
+// words, delta, by run, what added to an element's place in the stretch gives
+// its place in the segment.  A stretch of more runs than threads (elements
+// strewn thinly over many tiles) sets over, and is read through locate.
+template <int THREADS, int N>
+struct RunMap {
+  static constexpr int NW = THREADS / kWave, WORDS = N / kWave, PL = (WORDS + kWave - 1) / kWave;
+  unsigned long long mask[WORDS];
+  uint32_t base[WORDS];
+  uint32_t delta[THREADS];
+  uint32_t wcnt[NW];
+  uint32_t over;
+
+  __device__ __forceinline__ void clear(int t) {
+    for (int i = t; i < WORDS; i += THREADS) mask[i] = 0ull;
+  }
+  // Thread t's run (number run of nt): ofs elements of the bucket before it,
+  // e its start in its tile, c its length (0: none).
+  __device__ __forceinline__ void mark(int t, uint32_t run, uint32_t nt, uint32_t ofs, uint32_t c, uint32_t j0,
+                                       uint32_t cnt, uint64_t& bal) {
+    const bool in = run < nt && c > 0 && ofs < j0 + cnt && ofs + c > j0;
+    bal = __ballot(in);
+    if ((t & (kWave - 1)) == 0) wcnt[t / kWave] = (uint32_t)__popcll(bal);
+    if (in) {
+      const uint32_t s = max(ofs, j0) - j0;
+      atomicOr(&mask[s >> 6], 1ull << (s & 63u));
+    }
+    if (t == THREADS - 1) over = run + 1 < nt && ofs + c < j0 + cnt ? 1u : 0u;
+  }
+  __device__ __forceinline__ void number(int t, uint32_t run, uint32_t ofs, uint32_t e, uint32_t j0,
+                                         uint32_t tile_log2, uint64_t bal) {
+    const uint32_t lane = (uint32_t)t & (kWave - 1);
+    if ((bal >> lane) & 1ull) {
+      uint32_t ord = (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
+      for (int q = 0; q < t / kWave; q++) ord += wcnt[q];
+      delta[ord] = (run << tile_log2) + e - ofs + j0;
+    }
+    if (t < kWave) {
+      uint32_t x[PL], sum = 0;
+#pragma unroll
+      for (int k = 0; k < PL; k++) {
+        x[k] = t * PL + k < WORDS ? (uint32_t)__popcll(mask[t * PL + k]) : 0u;
+        sum += x[k];
+      }
+      uint32_t s = wave_incl_scan_dpp(sum) - sum;
+#pragma unroll
+      for (int k = 0; k < PL; k++) {
+        if (t * PL + k < WORDS) base[t * PL + k] = s;
+        s += x[k];
+      }
+    }
+  }
+  // Element p of the stretch, its place in the segment; p is the wave's first
+  // element (a multiple of 64) plus the lane.  p must lie in the stretch.
+  __device__ __forceinline__ uint32_t at(uint32_t p) const {
+    const uint32_t wd = uniform(p >> 6);
+    const uint64_t m = uniform64(mask[wd]);
+    const uint32_t b = uniform(base[wd]) + (uint32_t)(m & 1ull) - 1u;
+    const uint64_t m1 = m >> 1;  // bits up to the lane's own, less bit 0
+    const uint32_t ord = __builtin_amdgcn_mbcnt_hi((uint32_t)(m1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m1, b));
+    return delta[ord] + p;
+  }
+};
 
 // Launcher flag (or-ed into the class index): sort the whole input of a
 // plain call as one segment in a single launch.  The kernels then receive a
@@ -168,7 +260,7 @@ __device__ __forceinline__ uint32_t final_count(const Work& w, int cls) {
   return (uint32_t)min((uint64_t)w.ctl->class_count[cls], w.cls_cap[cls]);
 }
 __device__ __forceinline__ FinalSeg final_at(const Work& w, int cls, uint32_t q) {
-  if (cls < 0) return FinalSeg{0ull, (uint32_t)w.n, 0u};
+  if (cls < 0) return FinalSeg{0ull, 0ull, (uint32_t)w.n, 0u, 0u, 0u};
   return w.cls[cls][q];
 }
 // In the direct mode no reset kernel runs: the first thread clears the status
@@ -181,6 +273,7 @@ __device__ __forceinline__ void direct_reset(const Work& w) {
     w.ctl->l0_k = 0;
     for (int c = 0; c < kNumClasses; c++) {
       w.ctl->class_count[c] = 0;
+      w.ctl->class_done[c] = 0;
       w.ctl->class_keys[c] = 0;
     }
   }

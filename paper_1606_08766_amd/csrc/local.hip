@@ -24,8 +24,7 @@ template <typename K, bool F32, bool PAY, int THREADS, int ITEMS>
 __device__ __forceinline__ void sort_pairs(const Work& w, const FinalSeg& f, const LdsArr<K>& sa, const K* in_keys,
                                            const uint32_t* in_pay, K* keys_out, uint32_t* perm_out,
                                            uint32_t* pay_out) {
-  const BufView<K> sb{f.src ? w.buf_rec[f.src - 1] : nullptr};
-  const uint32_t* srcp = f.src ? w.buf_pay[f.src - 1] : in_pay;
+  const SegReader<K, F32, PAY> rd{w, f, in_keys, in_pay};
   K k[ITEMS];
   uint32_t v[ITEMS], p[ITEMS];
 #pragma unroll
@@ -37,24 +36,9 @@ __device__ __forceinline__ void sort_pairs(const Work& w, const FinalSeg& f, con
     v[i] = j < f.len ? j : kPadIdx;
     p[i] = j;
   }
-  // one source per segment (uniform), so each branch issues all its loads
-  // before any is used
-  if (f.src) {
 #pragma unroll
-    for (int i = 0; i < ITEMS; i++)
-      if (i * THREADS + threadIdx.x < f.len) sb.get(f.start + i * THREADS + threadIdx.x, k[i], v[i]);
-  } else {
-#pragma unroll
-    for (int i = 0; i < ITEMS; i++)
-      if (i * THREADS + threadIdx.x < f.len) k[i] = in_keys[f.start + i * THREADS + threadIdx.x];  // raw bits
-  }
-  if constexpr (F32) {
-    if (!f.src) {
-#pragma unroll
-      for (int i = 0; i < ITEMS; i++)
-        if (i * THREADS + threadIdx.x < f.len) k[i] = ord_of<K, F32>(k[i]);
-    }
-  }
+  for (int i = 0; i < ITEMS; i++)
+    if (i * THREADS + threadIdx.x < f.len) rd.get(i * THREADS + threadIdx.x, k[i], v[i]);
   lds_merge_sort<K, THREADS, ITEMS, PAY>(k, v, p, sa);
 #pragma unroll
   for (int i = 0; i < ITEMS; i++) {
@@ -70,7 +54,7 @@ __device__ __forceinline__ void sort_pairs(const Work& w, const FinalSeg& f, con
 #pragma unroll
     for (int i = 0; i < ITEMS; i++) {
       const uint32_t j = i * THREADS + threadIdx.x;
-      pv[i] = j < f.len ? srcp[f.start + sa.p[lpad(j)]] : 0u;
+      pv[i] = j < f.len ? rd.pay(sa.p[lpad(j)]) : 0u;
     }
 #pragma unroll
     for (int i = 0; i < ITEMS; i++) {
@@ -217,6 +201,7 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
   __shared__ uint32_t s_red[6 * (THREADS / kWave)];
   __shared__ uint32_t s_tmp[2 * (THREADS / kWave)];
   __shared__ uint32_t s_sum;
+  __shared__ RunMap<DIRECT ? kWave : THREADS, DIRECT ? kWave : N> map;  // of the next segment, if it lies in a buffer
   uint32_t* const fr = s_mem;           // N words, and 3 beyond
   uint32_t* const bin = s_mem + N + 4;  // 2^LB + 1 bins
   uint64_t* const st = reinterpret_cast<uint64_t*>(s_mem);
@@ -235,43 +220,94 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
   uint32_t idx[ITEMS], pay[ITEMS];
   // Thread t takes elements i * THREADS + t.  One source per segment
   // (uniform), every lane loads (lanes past the end reload the last element),
-  // so that all loads go out before any is used.  Bases are scalar, elements
-  // 32-bit byte offsets.
-  auto load = [&](uint32_t len, uint32_t src, uint64_t start, int t) {
-    const uint32_t* const psrc = PAY ? (src ? w.buf_pay[src - 1] : in_pay) + start : nullptr;
-    if (src) {
-      const BufView<K> sb{w.buf_rec[src - 1] + start * BufView<K>::W};
+  // so that all loads go out before any is used.  Input segments: scalar
+  // bases, 32-bit byte offsets.
+  auto load = [&](const FinalSeg& f, int t) {
+    if (!DIRECT && f.src) {
+      const BufView<K, PAY> bv{w.buf_rec[f.src - 1] + f.pstart * BufView<K, PAY>::W};
+      if (map.over == 0) {  // uniform
 #pragma unroll
-      for (int i = 0; i < ITEMS; i++) {
-        const uint32_t j = min((uint32_t)(i * THREADS + t), len - 1);
-        sb.get32(j, key[i], idx[i]);
-        if constexpr (PAY) pay[i] = at32(psrc, j);
+        for (int i = 0; i < ITEMS; i++) {
+          const uint32_t p = i * THREADS + t;
+          // (a wave past the end: the segment's first element)
+          const uint32_t d = i * THREADS + (t & ~(kWave - 1)) < (int)f.len
+                                 ? map.at(p) - (p < f.len ? 0u : p - f.len + 1u)
+                                 : map.delta[0];
+          bv.get(d, key[i], idx[i], pay[i]);
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < ITEMS; i++)
+          bv.get(locate(w, (int)f.src - 1, f.col, 0, f.nt - 1, min((uint32_t)(i * THREADS + t), f.len - 1)), key[i],
+                 idx[i], pay[i]);
       }
     } else {
-      const K* const kin = in_keys + start;
+      const K* const kin = in_keys + f.start;
 #pragma unroll
       for (int i = 0; i < ITEMS; i++) {
-        const uint32_t j = min((uint32_t)(i * THREADS + t), len - 1);
+        const uint32_t j = min((uint32_t)(i * THREADS + t), f.len - 1);
         key[i] = at32(kin, j);  // raw bits
         idx[i] = j;
-        if constexpr (PAY) pay[i] = at32(psrc, j);
+        if constexpr (PAY) pay[i] = at32(in_pay + f.start, j);
       }
     }
+  };
+  auto uniform_seg = [](const FinalSeg& f) -> FinalSeg {
+    return FinalSeg{uniform64(f.start), uniform64(f.pstart), uniform(f.len), uniform(f.src), uniform(f.col),
+                    uniform(f.nt)};
+  };
+  // this thread's run of a buffer segment
+  struct Run {
+    uint32_t ofs, e, c;
+  };
+  auto run_of = [&](const FinalSeg& f, uint32_t t) -> Run {
+    Run r{0u, 0u, 0u};
+    if (f.src && t < f.nt) {
+      const uint32_t *o = w.offs[f.src - 1] + f.col, v = w.runs[f.src - 1][f.col + t];
+      r.ofs = o[t] - o[0];
+      r.e = v >> 16;
+      r.c = v & 0xFFFFu;
+    }
+    return r;
   };
   uint32_t q = blockIdx.x;
   if (q >= total) return;
   if constexpr (DIRECT) direct_reset(w);
-  FinalSeg f = DIRECT ? FinalSeg{0ull, (uint32_t)w.n, 0u} : *seg_at(q);
-  load(uniform(f.len), uniform(f.src), uniform64(f.start), threadIdx.x);
+  FinalSeg f = DIRECT ? FinalSeg{0ull, 0ull, (uint32_t)w.n, 0u, 0u, 0u} : uniform_seg(*seg_at(q));
+  if constexpr (!DIRECT) {
+    if (f.src) {
+      const int t = threadIdx.x;
+      const Run r = run_of(f, t);
+      uint64_t bal;
+      map.clear(t);
+      __syncthreads();
+      map.mark(t, t, f.nt, r.ofs, r.c, 0u, f.len, bal);
+      __syncthreads();
+      map.number(t, t, r.ofs, r.e, 0u, w.tile_log2, bal);
+      __syncthreads();
+    }
+  }
+  load(f, threadIdx.x);
+  FinalSeg f_ahead = f;  // the next segment's descriptor, loaded an iteration ahead
+  if constexpr (!DIRECT) f_ahead = *seg_at(q + gridDim.x < total ? q + gridDim.x : q);
+  __syncthreads();  // every wave has read the map
   for (;;) {
-    const uint32_t len = uniform(f.len), src = uniform(f.src);
-    const uint64_t start = uniform64(f.start);
-    // the next segment's descriptor now, its elements before the last output
-    // of this one (whose registers they take): a load that follows stores
-    // waits for them, and so would the start of every segment
+    const uint32_t len = f.len, src = f.src;
+    const uint64_t start = f.start;
+    // the next segment's runs now, its elements before the last output of
+    // this one (whose registers they take): a load that follows stores waits
+    // for them, and so would the start of every segment
     const uint32_t qn = q + gridDim.x;
     const bool more = qn < total;
-    if constexpr (!DIRECT) f = *seg_at(more ? qn : q);
+    FinalSeg fn = f;
+    Run rn{0u, 0u, 0u};
+    if constexpr (!DIRECT) {
+      fn = uniform_seg(f_ahead);
+      f_ahead = *seg_at(qn + gridDim.x < total ? qn + gridDim.x : q);
+      rn = run_of(fn, threadIdx.x);
+      map.clear(threadIdx.x);
+    }
+    uint64_t bal = 0;
     // an opaque copy of the thread index: per-thread addresses are recomputed
     // per segment rather than hoisted out of the loop and kept live
     int t = threadIdx.x;
@@ -342,7 +378,13 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
       rank[i] = 0;  // first the place in the bin
       if (t < (int)len - i * THREADS) rank[i] = atomicAdd(&bin[wd[i] >> bsh], 1u);
     }
+    if constexpr (!DIRECT) {
+      if (fn.src) map.mark(t, t, fn.nt, rn.ofs, rn.c, 0u, fn.len, bal);
+    }
     __syncthreads();
+    if constexpr (!DIRECT) {
+      if (fn.src) map.number(t, t, rn.ofs, rn.e, 0u, w.tile_log2, bal);
+    }
     const bool rare = bins_scan<THREADS, BPT>(bin, len, s_tmp, t) > kRankBudget * len;  // uniform
     if (rare) {
       if constexpr (!DIRECT) {
@@ -441,7 +483,7 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
     }
     }
     __syncthreads();
-    if (more) load(uniform(f.len), uniform(f.src), uniform64(f.start), t);
+    if (more) load(fn, t);
     if (!rare) {
 #pragma unroll
       for (int i = 0; i < ITEMS; i++) {
@@ -465,6 +507,7 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
     }
     if (!more) break;
     q = qn;
+    f = fn;
     __syncthreads();  // the next segment clears its bins in the staging area
   }
 }
@@ -472,71 +515,54 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
 // ---------------------------------------------------------------------------
 // Fallback for final segments longer than cap (the balance guarantee of the
 // sampling holds only with high probability): bottom-up merge sort through
-// global memory by one workgroup, ping-ponging between the two buffers over
-// the segment's own range (that range of the other buffer is never used by
-// another segment).  Slow, exact, rare.
+// global memory by one workgroup, for one segment after the other.  First
+// chunks of every segment are gathered, sorted and written to the segment's own
+// range of the buffer that does not hold its level's elements (which no final
+// segment needs any more), then the chunks are merged, ping-ponging between
+// the buffers over that range.  Slow, exact, rare.
 // sk, sv, sp: LDS arrays of THREADS * ITEMS values (sp: payload calls only).
 template <typename K, bool F32, bool PAY, int THREADS, int ITEMS>
 __device__ __forceinline__ void sort_oversize(const Work& w, const K* in_keys, const uint32_t* in_pay, K* keys_out,
                                               uint32_t* perm_out, uint32_t* pay_out, K* sk, uint32_t* sv,
                                               uint32_t* sp) {
   constexpr int C = THREADS * ITEMS;
+  using View = BufView<K, PAY>;
   const int cls = kNumClasses - 1;
   const uint32_t cnt = (uint32_t)min((uint64_t)w.ctl->class_count[cls], w.cls_cap[cls]);
-  for (uint32_t q = blockIdx.x; q < cnt; q += gridDim.x) {
+  for (uint32_t q = 0; q < cnt; q++) {
     const FinalSeg f = w.cls[cls][q];
-    // buffers used: data source code f.src; first target is the other buffer
-    // pass 0 writes into the buffer that does not hold the data
-    int cur = f.src == 0 ? 0 : ((int)f.src - 1) ^ 1;
-    const BufView<K> sb{f.src ? w.buf_rec[f.src - 1] : nullptr};
-    const uint32_t* srcp = f.src ? w.buf_pay[f.src - 1] : in_pay;
-    // pass 0: sort chunks of C in LDS
+    const SegReader<K, F32, PAY> rd{w, f, in_keys, in_pay};
+    const View db{w.buf_rec[f.src == 0 ? 0 : ((int)f.src - 1) ^ 1]};
     for (uint32_t c0 = 0; c0 < f.len; c0 += C) {
       K k[ITEMS];
       uint32_t v[ITEMS], p[ITEMS];
 #pragma unroll
       for (int i = 0; i < ITEMS; i++) {
         const uint32_t j = c0 + threadIdx.x * ITEMS + i;
+        k[i] = KMax<K>::v;
+        v[i] = kPadIdx;
+        p[i] = 0;
         if (j < f.len) {
-          if (f.src) {
-            sb.get(f.start + j, k[i], v[i]);
-          } else {
-            k[i] = in_keys[f.start + j];  // raw bits; mapped below once all loads are issued
-            v[i] = j;
-          }
-          p[i] = PAY ? srcp[f.start + j] : 0u;
-        } else {
-          k[i] = KMax<K>::v;
-          v[i] = kPadIdx;
-          p[i] = 0;
-        }
-      }
-      if constexpr (F32) {
-        if (!f.src) {
-#pragma unroll
-          for (int i = 0; i < ITEMS; i++)
-            if (c0 + threadIdx.x * ITEMS + i < f.len) k[i] = ord_of<K, F32>(k[i]);
+          rd.get(j, k[i], v[i]);
+          if constexpr (PAY) p[i] = rd.pay(j);
         }
       }
       block_merge_sort<K, THREADS, ITEMS, PAY>(k, v, p, sk, sv, sp);
-      const BufView<K> db{w.buf_rec[cur]};
-      uint32_t* dp = w.buf_pay[cur];
 #pragma unroll
       for (int i = 0; i < ITEMS; i++) {
         const uint32_t j = c0 + threadIdx.x * ITEMS + i;
-        if (j < f.len) {
-          db.put(f.start + j, k[i], v[i]);
-          if constexpr (PAY) dp[f.start + j] = p[i];
-        }
+        if (j < f.len) db.put(f.start + j, k[i], v[i], p[i]);
       }
       __syncthreads();
     }
+  }
+  for (uint32_t q = 0; q < cnt; q++) {
+    const FinalSeg f = w.cls[cls][q];
+    int cur = f.src == 0 ? 0 : ((int)f.src - 1) ^ 1;
     // merge passes
     for (uint32_t run = C; run < f.len; run <<= 1) {
-      const BufView<K> ab{w.buf_rec[cur] + f.start * BufView<K>::W};
-      const uint32_t* ap = PAY ? w.buf_pay[cur] + f.start : nullptr;
-      const BufView<K> db{w.buf_rec[cur ^ 1] + f.start * BufView<K>::W};
-      uint32_t* dp = PAY ? w.buf_pay[cur ^ 1] + f.start : nullptr;
+      const View ab{w.buf_rec[cur] + f.start * View::W};
+      const View db{w.buf_rec[cur ^ 1] + f.start * View::W};
       for (uint32_t o0 = 0; o0 < f.len; o0 += THREADS) {
         const uint32_t o = o0 + threadIdx.x;  // output position handled by this thread
         if (o < f.len) {
@@ -564,20 +590,18 @@ __device__ __forceinline__ void sort_oversize(const Work& w, const K* in_keys, c
           else
             takeA = !pair_less(ab.key(b0 + bi), ab.idx(b0 + bi), ab.key(first + ai), ab.idx(first + ai));
           const uint32_t sidx = takeA ? first + ai : b0 + bi;
-          db.put(o, ab.key(sidx), ab.idx(sidx));
-          if constexpr (PAY) dp[o] = ap[sidx];
+          db.put(o, ab.key(sidx), ab.idx(sidx), ab.pay(sidx));
         }
       }
       __syncthreads();
       cur ^= 1;
     }
     // output
-    const BufView<K> rb{w.buf_rec[cur] + f.start * BufView<K>::W};
-    const uint32_t* rp = PAY ? w.buf_pay[cur] + f.start : nullptr;
+    const View rb{w.buf_rec[cur] + f.start * View::W};
     for (uint32_t j = threadIdx.x; j < f.len; j += THREADS) {
       keys_out[f.start + j] = to_output<K, F32>(rb.key(j));
       if (perm_out) perm_out[f.start + j] = rb.idx(j);
-      if constexpr (PAY) pay_out[f.start + j] = rp[j];
+      if constexpr (PAY) pay_out[f.start + j] = rb.pay(j);
     }
     __syncthreads();
   }
@@ -605,7 +629,7 @@ __global__ __launch_bounds__(THREADS) void k_local_rare(Work w, const K* in_keys
   const LdsArr<K> sa{s_lo, s_hi, s_v, s_p};
   if (direct) {  // a plain call's whole input
     if (w.ctl->direct_rare)
-      sort_pairs<K, F32, PAY, THREADS, ITEMS>(w, FinalSeg{0ull, (uint32_t)w.n, 0u}, sa, in_keys, in_pay, keys_out,
+      sort_pairs<K, F32, PAY, THREADS, ITEMS>(w, FinalSeg{0ull, 0ull, (uint32_t)w.n, 0u, 0u, 0u}, sa, in_keys, in_pay, keys_out,
                                               perm_out, pay_out);
     return;
   }
@@ -633,6 +657,14 @@ __global__ __launch_bounds__(THREADS) void k_local_rare(Work w, const K* in_keys
       __syncthreads();
     }
   }
+  // The oversize sort writes over the buffers, so it waits for every
+  // workgroup's segments: the last workgroup to come here does it.
+  if (w.ctl->class_count[kNumClasses - 1] == 0) return;  // uniform
+  __syncthreads();
+  if (threadIdx.x == 0) s_n = atomicAdd(&w.ctl->rare_done, 1u) + 1u;
+  __syncthreads();
+  if (s_n != gridDim.x) return;
+  if (threadIdx.x == 0) w.ctl->rare_done = 0;
   sort_oversize<K, F32, PAY, THREADS, 4>(w, in_keys, in_pay, keys_out, perm_out, pay_out, reinterpret_cast<K*>(s_lo),
                                          s_v, s_p);
 }

@@ -66,15 +66,15 @@ __global__ __launch_bounds__(THREADS) void k_rfis(Work w, int cls, const K* in_k
   const uint32_t cnt = final_count(w, cls);
   for (uint32_t q = blockIdx.x; q < cnt; q += gridDim.x) {
     const FinalSeg f = final_at(w, cls, q);
-    const BufView<K> sb{f.src ? w.buf_rec[f.src - 1] : nullptr};
-    const uint32_t* srcp = f.src ? w.buf_pay[f.src - 1] : in_pay;
+    const SegReader<K, F32, PAY> rd{w, f, in_keys, in_pay};
     T mine[PER];
 #pragma unroll
     for (int r = 0; r < PER; r++) {
       const uint32_t j = r * THREADS + threadIdx.x;
       if (j < f.len) {
-        const K key = f.src ? sb.key(f.start + j) : load_ord<K, F32>(in_keys, f.start + j);
-        const uint32_t idx = f.src ? sb.idx(f.start + j) : j;
+        K key;
+        uint32_t idx;
+        rd.get(j, key, idx);
         mine[r] = RK::make(key, idx);
         sx[j] = mine[r];
       }
@@ -120,7 +120,7 @@ __global__ __launch_bounds__(THREADS) void k_rfis(Work w, int cls, const K* in_k
         idx = x.i;
       }
       uint32_t pv = 0;  // loaded before the stores (a load issued after stores waits for them)
-      if constexpr (PAY) pv = srcp[f.start + j];
+      if constexpr (PAY) pv = rd.pay(j);
       keys_out[f.start + r] = to_output<K, F32>(key);
       if (perm_out) perm_out[f.start + r] = idx;
       if constexpr (PAY) pay_out[f.start + r] = pv;
@@ -231,14 +231,12 @@ __global__ __launch_bounds__(THREADS) void k_rquick(Work w, int cls, const K* in
   const uint32_t cnt = final_count(w, cls);
   for (uint32_t q = blockIdx.x; q < cnt; q += gridDim.x) {
     const FinalSeg f = final_at(w, cls, q);
-    const BufView<K> sb{f.src ? w.buf_rec[f.src - 1] : nullptr};
-    const uint32_t* srcp = f.src ? w.buf_pay[f.src - 1] : in_pay;
+    const SegReader<K, F32, PAY> rd{w, f, in_keys, in_pay};
     const uint32_t n = f.len;
     const uint64_t rstream = f.start * 0x9E3779B97F4A7C15ull + 0x52515549434Bull;
     // stage the input in buffer 1 (coalesced)
     for (uint32_t j = threadIdx.x; j < n; j += THREADS) {
-      bk[1][j] = f.src ? sb.key(f.start + j) : load_ord<K, F32>(in_keys, f.start + j);
-      bv[1][j] = f.src ? sb.idx(f.start + j) : j;
+      rd.get(j, bk[1][j], bv[1][j]);
     }
     if (threadIdx.x < P) {
       off[threadIdx.x] = (uint32_t)((uint64_t)threadIdx.x * n / P);
@@ -407,7 +405,7 @@ __global__ __launch_bounds__(THREADS) void k_rquick(Work w, int cls, const K* in
     // runs are now in wave order and globally sorted
     for (uint32_t r = threadIdx.x; r < n; r += THREADS) {
       uint32_t pv = 0;  // loaded before the stores (a load issued after stores waits for them)
-      if constexpr (PAY) pv = srcp[f.start + bp[cur][r]];
+      if constexpr (PAY) pv = rd.pay(bp[cur][r]);
       keys_out[f.start + r] = to_output<K, F32>(bk[cur][r]);
       if (perm_out) perm_out[f.start + r] = bv[cur][r];
       if constexpr (PAY) pay_out[f.start + r] = pv;

@@ -1,0 +1,69 @@
+"""The split levels (tiles sorted by bucket and written back as one piece,
+buckets read back as their runs): tile and level edges, buckets whose elements
+lie in more tiles than a workgroup has threads, payloads through several
+levels; bit-exact against the oracle (whole numbers, zero tolerance)."""
+import numpy as np
+import pytest
+
+from gen import gen
+from oracle import oracle as O
+from paper_1606_08766_amd import rsort as R
+from tests.gpu_util import gpu_segmented, gpu_sort, same_bits
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(x, threads=8):
+    ek, ep, _ = O.sort(x, threads=threads)
+    ko, po = gpu_sort(x)
+    assert same_bits(ko, ek) and np.array_equal(po, ep)
+
+
+@pytest.mark.parametrize("kt", ["u64", "u32"])
+@pytest.mark.parametrize("n", [4096 * 4, 4096 * 4 + 1, 4096 * 5 - 1, 64 * 4096 + 63, 3145729, (1 << 23) - 1, 1 << 23,
+                               (1 << 23) + 8191])
+def test_tile_and_level_edges(kt, n):
+    _check(gen.keys(kt, "uniform", n, seed=n))
+
+
+@pytest.mark.parametrize("kt", ["u64", "f32"])
+@pytest.mark.parametrize("n,tile_log2", [((1 << 22) + 5, 12), ((1 << 24) + 5, 13)])
+@pytest.mark.parametrize("thin", [200, 3000])
+def test_buckets_strewn_over_more_tiles_than_threads(kt, n, tile_log2, thin):
+    """In the first three quarters one key in `thin` is small, in the last all
+    are: the first elements of the buckets of small keys lie in more tiles than
+    a workgroup has threads, a few or none in each."""
+    rng = np.random.default_rng(thin)
+    k = rng.random(n)
+    small = (np.arange(n) >= 3 * n // 4) | (rng.random(n) < 1.0 / thin)
+    k = np.where(small, k * 0.001, 0.5 + 0.5 * k)
+    x = k.astype(np.float32) if kt == "f32" else (k * float(1 << 62)).astype(np.uint64)
+    with R.tuned(tile_log2=tile_log2):
+        _check(x)
+
+
+@pytest.mark.parametrize("kt", ["u64", "u32"])
+@pytest.mark.parametrize("cap", [256, 12288])
+def test_payload_through_levels(kt, cap):
+    """Segments split by no, one, two or three levels in one call, all with a
+    payload; the local sorts of early levels run before a later level reuses
+    their buffer."""
+    sizes = np.array([5, 700000, 250, 0, 3400000, 257, 64, 13000, 90000, 300], dtype=np.uint64)
+    keys, pay, off = gen.segmented(kt, sizes, ["uniform", "deterdupl", "zero", "zero", "gaussian", "uniform", "reverse",
+                                               "uniform", "zero", "uniform"], seed=17)
+    with R.tuned(cap=cap):
+        ko, po, plo, _ = gpu_segmented(keys, off, pay)
+    ek, ep, epl = O.segmented(keys, off, pay)
+    assert same_bits(ko, ek) and np.array_equal(po, ep) and np.array_equal(plo, epl)
+
+
+@pytest.mark.parametrize("kt", ["u64", "u32"])
+def test_oversize_buckets_of_several_segments(kt):
+    """One level only: many buckets exceed the LDS sort and are merge sorted
+    through the buffers, next to segments that need no level."""
+    sizes = np.array([400000, 100, 900000, 5000, 300000], dtype=np.uint64)
+    keys, pay, off = gen.segmented(kt, sizes, ["uniform", "zero", "deterdupl", "uniform", "reverse"], seed=9)
+    with R.tuned(max_levels=1, cap=1024, oversample=1, target=512):
+        ko, po, plo, _ = gpu_segmented(keys, off, pay)
+    ek, ep, epl = O.segmented(keys, off, pay)
+    assert same_bits(ko, ek) and np.array_equal(po, ep) and np.array_equal(plo, epl)
