@@ -72,6 +72,14 @@ __device__ __forceinline__ uint64_t rand_at(uint64_t seed, uint64_t stream, uint
   return mix64(seed + mix64(stream + 0x632BE59BD9B4E019ull) + (i + 1) * 0x9E3779B97F4A7C15ull);
 }
 
+// The 32-bit finaliser of MurmurHash3 (Appleby 2011): a cheaper mixer where
+// many draws are made and 32 bits do.
+__device__ __forceinline__ uint32_t mix32(uint32_t z) {
+  z = (z ^ (z >> 16)) * 0x85EBCA6Bu;
+  z = (z ^ (z >> 13)) * 0xC2B2AE35u;
+  return z ^ (z >> 16);
+}
+
 // ---------------------------------------------------------------------------
 // Wave / block scans.
 // ---------------------------------------------------------------------------
@@ -117,26 +125,6 @@ __device__ __forceinline__ T block_excl_scan(T v, typename NoDeduce<T>::type* tm
   if (total) *total = tmp[NW];
   __syncthreads();
   return r;
-}
-
-// Wave-aggregated append: every active lane obtains a slot from
-// counters[key] with one atomic per distinct key per wave.  Must be reached by
-// all lanes of the wave (inactive lanes pass active = false).
-__device__ __forceinline__ uint32_t wave_append(uint32_t* counters, uint32_t key, bool active) {
-  uint32_t slot = 0;
-  const uint32_t lane = lane_id();
-  uint64_t pending = __ballot(active);
-  while (pending) {
-    const int leader = __ffsll((unsigned long long)pending) - 1;
-    const uint32_t k = __shfl(key, leader, kWave);
-    const uint64_t m = __ballot(active && key == k) & pending;
-    uint32_t base = 0;
-    if (lane == (uint32_t)leader) base = atomicAdd(&counters[k], (uint32_t)__popcll(m));
-    base = __shfl(base, leader, kWave);
-    if ((m >> lane) & 1ull) slot = base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-    pending &= ~m;
-  }
-  return slot;
 }
 
 // ---------------------------------------------------------------------------

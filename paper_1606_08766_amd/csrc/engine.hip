@@ -80,8 +80,8 @@ __device__ __forceinline__ uint32_t tiles_of(const Work& w, uint32_t len) {
 
 // Routing of a block's segments to the list of segments to split (index
 // kNumClasses) or to the final lists by size class, aggregated per block:
-// slots are counted in LDS (one LDS atomic per list and wave), then one
-// global atomic per list and block reserves them.  Every thread of the block
+// slots are counted in LDS (one LDS atomic per segment), then one global
+// atomic per list and block reserves them.  Every thread of the block
 // calls once per iteration of a block-uniform loop; `lds` is zeroed before
 // the first call (route_lds_init) and is left zeroed.
 struct RouteLds {
@@ -105,7 +105,7 @@ __device__ __forceinline__ void route(const Work& w, RouteLds& L, int next, bool
                                       uint32_t cmin) {
   const uint32_t c = (active && !to_big) ? class_of(f.len, cap, ff, cmin) : 0u;
   const uint32_t dest = to_big ? (uint32_t)kNumClasses : c;
-  const uint32_t li = wave_append(L.cnt, dest, active);
+  const uint32_t li = active ? atomicAdd(&L.cnt[dest], 1u) : 0u;
   // a segment to split takes its tiles and matrix entries of the next level
   const bool big = active && to_big;
   uint32_t logk = 0, tb = 0, cb = 0;
@@ -115,18 +115,7 @@ __device__ __forceinline__ void route(const Work& w, RouteLds& L, int next, bool
     tb = atomicAdd(&L.tiles, nt);
     cb = atomicAdd(&L.entries, nt << logk);
   }
-  // keys per class (statistics): one LDS atomic per distinct class per wave
-  const bool af = active && !to_big;
-  uint64_t pending = __ballot(af);
-  while (pending) {
-    const int leader = __ffsll((unsigned long long)pending) - 1;
-    const uint32_t k = __shfl(c, leader, kWave);
-    const bool mine = af && c == k;
-    uint64_t sum = mine ? (uint64_t)f.len : 0ull;
-    for (int d = kWave / 2; d > 0; d >>= 1) sum += __shfl_xor(sum, d, kWave);
-    if (lane_id() == (uint32_t)leader) atomicAdd(&L.keys[k], (unsigned long long)sum);
-    pending &= ~__ballot(mine);
-  }
+  if (active && !to_big) atomicAdd(&L.keys[c], (unsigned long long)f.len);  // (statistics)
   __syncthreads();
   if (threadIdx.x <= (unsigned)kNumClasses) {
     const uint32_t t = threadIdx.x, n = L.cnt[t];
@@ -247,8 +236,7 @@ __global__ __launch_bounds__(kStartThreads) void k_start_plain(Work w, uint64_t 
 // depth d, index q = t - 2^d within its depth, holds splitter number
 // (2q+1) * 2^(logk-1-d) (1-based, in sorted order).  The workgroup also writes
 // down, for each of the segment's tiles, the segment and (buffer levels) the
-// run that holds the tile's first element, between which its own samples are
-// then looked up.
+// run that holds the tile's first element.
 constexpr uint32_t kSplRankBudget = 64;  // compares per sample the ranking path may take
 template <typename K, bool F32, bool SRC_IN, bool PAY, int THREADS, int ITEMS>
 __global__ __launch_bounds__(THREADS) void k_splitters(Work w, int lev, const K* in_keys, int src_buf,
@@ -271,23 +259,52 @@ __global__ __launch_bounds__(THREADS) void k_splitters(Work w, int lev, const K*
   K* tkey = (K*)w.tree_key;
   for (uint32_t s = blockIdx.x; s < m; s += gridDim.x) {
     const BigSeg bs = w.big[cur][s];
-    // a samples per bucket, fewer when a * k would exceed the LDS sample
-    const uint32_t ae = min(a, (uint32_t)(THREADS * ITEMS) >> bs.logk);
+    // a samples per bucket, fewer when a * k would exceed the LDS sample (or a
+    // short segment's length)
+    uint32_t ae = min(a, (uint32_t)(THREADS * ITEMS) >> bs.logk);
+    if constexpr (!SRC_IN) ae = min(ae, max(bs.len >> bs.logk, 1u));
     const uint32_t S = ae << bs.logk;
     const uint32_t ntiles = tiles_of(w, bs.len);
     if (!SRC_IN || m > 1) {  // (the tiles of an only input segment are known to be its)
       for (uint32_t i = threadIdx.x; i < ntiles; i += THREADS) w.tile_seg[bs.tb + i] = s;
     }
     if constexpr (!SRC_IN) {
-      const uint32_t *o = w.offs[src_buf] + bs.col, *rn = w.runs[src_buf] + bs.col, o0 = o[0];
+      // One walk over the segment's runs finds the run that holds each tile's
+      // first element and the places of the samples, which are drawn one from
+      // each of S equal stretches of the segment (the first rem of them are
+      // one element longer), so that a run need only look at its own
+      // stretches.  (Looking each sample's run up took 8 or more dependent
+      // loads: 187 us for the 256 segments of 2^28 keys.)
+      constexpr int U = 8;  // runs a thread has in flight
+      const uint32_t *o = w.offs[src_buf] + bs.col, *rr = w.runs[src_buf] + bs.col, o0 = o[0];
+      const uint32_t wd = bs.len / S, rem = bs.len - wd * S, wide = rem * (wd + 1u);
       const uint32_t half = (1u << w.tile_log2) - 1u;
-      for (uint32_t t = threadIdx.x; t < bs.nt; t += THREADS) {
-        const uint32_t c = rn[t] & 0xFFFFu, f = o[t] - o0;
-        if (c == 0) continue;
-        for (uint32_t i = (uint32_t)(((uint64_t)f + half) >> w.tile_log2); i <= (f + c - 1) >> w.tile_log2; i++)
-          w.tile_run[bs.tb + i] = t;
+      const uint32_t stream = (uint32_t)rand_at(seed, ((uint64_t)lev << 40) ^ bs.start, 0);
+      for (uint32_t t0 = threadIdx.x; t0 < bs.nt; t0 += THREADS * U) {
+        uint32_t fs[U], rs_[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+          const uint32_t t = min(t0 + u * THREADS, bs.nt - 1u);
+          fs[u] = o[t];
+          rs_[u] = rr[t];
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+          const uint32_t t = t0 + u * THREADS, f = fs[u] - o0, c = rs_[u] & 0xFFFFu;
+          if (t >= bs.nt || c == 0) continue;
+          for (uint32_t i = (uint32_t)(((uint64_t)f + half) >> w.tile_log2); i <= (f + c - 1) >> w.tile_log2; i++)
+            w.tile_run[bs.tb + i] = t;
+          const uint32_t place = (t << w.tile_log2) + (rs_[u] >> 16) - f;
+          uint32_t j = f < wide ? f / (wd + 1u) : rem + (f - wide) / wd;
+          for (; j < S; j++) {
+            const uint32_t lo = j * wd + min(j, rem);
+            if (lo >= f + c) break;
+            const uint32_t pos = lo + __umulhi(mix32(stream + j * 0x9E3779B9u), wd + (j < rem ? 1u : 0u));
+            if (pos >= f && pos < f + c) s_v[j] = place + pos;
+          }
+        }
       }
-      __syncthreads();  // read below
+      __syncthreads();
     }
     K k[ITEMS];
     uint32_t v[ITEMS], p[ITEMS];
@@ -298,15 +315,13 @@ __global__ __launch_bounds__(THREADS) void k_splitters(Work w, int lev, const K*
         // drawn by k_start_plain (the same positions), stored in order
         BufView<K, false>{w.buf_rec[1]}.get(j, k[i], v[i], p[i]);
       } else if (j < S) {
-        const uint64_t r = rand_at(seed, ((uint64_t)lev << 40) ^ bs.start, j);
-        const uint32_t off = (uint32_t)(((r >> 32) * (uint64_t)bs.len) >> 32);
         if constexpr (SRC_IN) {
+          const uint64_t r = rand_at(seed, ((uint64_t)lev << 40) ^ bs.start, j);
+          const uint32_t off = (uint32_t)(((r >> 32) * (uint64_t)bs.len) >> 32);
           k[i] = in_keys[bs.start + off];  // raw bits; mapped below once all loads are issued
           v[i] = (uint32_t)(bs.start + off - bs.ubase);
         } else {
-          const uint32_t t = off >> w.tile_log2;
-          const uint32_t r0 = w.tile_run[bs.tb + t], r1 = t + 1 < ntiles ? w.tile_run[bs.tb + t + 1] : bs.nt - 1;
-          bv.get(bs.pstart + locate(w, src_buf, bs.col, r0, r1, off), k[i], v[i], p[i]);
+          bv.get(bs.pstart + s_v[j], k[i], v[i], p[i]);
         }
       } else {
         k[i] = KMax<K>::v;
@@ -536,48 +551,69 @@ __device__ __forceinline__ void classify_batch(const K* tk, const uint32_t* ti, 
   for (int i = 0; i < ITEMS; i++) b[i] = j[i] - kk;
 }
 
-// Copies the splitter tree of segment s (2^logk buckets) from global memory
-// into tk[1, k) / ti[1, k) and fills tk's leaf row tk[k, 2k) (see
-// classify_batch): splitter j (1-based, in sorted order) is tree node
-// (j | k) >> (ctz(j) + 1).  Called by every thread; the caller synchronizes.
-template <typename K, int THREADS>
-__device__ __forceinline__ void tree_to_lds(const Work& w, uint32_t s, uint32_t logk, K* tk, uint32_t* ti) {
-  const K* tkey = (const K*)w.tree_key;
-  const uint32_t kk = 1u << logk;
-  const uint64_t o = (uint64_t)s * kMaxK;
-  for (uint32_t i = threadIdx.x + 1; i < kk; i += THREADS) {
-    tk[i] = tkey[o + i];
-    ti[i] = w.tree_idx[o + i];
-    const uint32_t node = (i | kk) >> (__builtin_ctz(i) + 1);
-    tk[kk + i - 1] = tkey[o + node];
+// Splitter tree of a segment (2^logk buckets): nodes tk[1, k) / ti[1, k) and
+// the leaf row tk[k, 2k) (see classify_batch); splitter j (1-based, in sorted
+// order) is tree node (j | k) >> (ctz(j) + 1).  A thread's part of the copy
+// from global memory, at least kMaxK threads: fetch, then store.
+template <typename K>
+struct TreePart {
+  K node, leaf;
+  uint32_t pos;
+  __device__ __forceinline__ void fetch(const Work& w, uint32_t s, uint32_t logk, uint32_t i) {
+    const K* tkey = (const K*)w.tree_key;
+    const uint32_t kk = 1u << logk;
+    const uint64_t o = (uint64_t)s * kMaxK;
+    node = leaf = K(0);
+    pos = 0;
+    if (i >= kk) return;
+    const uint32_t j = i ? i : kk - 1;  // thread 0: the last leaf repeats the largest
+    leaf = tkey[o + ((j | kk) >> (__builtin_ctz(j) + 1))];
+    if (i) {
+      node = tkey[o + i];
+      pos = w.tree_idx[o + i];
+    }
   }
-  if (threadIdx.x == 0 && kk > 1) tk[2 * kk - 1] = tkey[o + (((kk - 1) | kk) >> 1)];
-}
+  __device__ __forceinline__ void store(uint32_t logk, uint32_t i, K* tk, uint32_t* ti) const {
+    const uint32_t kk = 1u << logk;
+    if (i >= kk) return;
+    tk[i ? kk + i - 1 : 2 * kk - 1] = leaf;
+    if (i) {
+      tk[i] = node;
+      ti[i] = pos;
+    }
+  }
+};
 
 // ---------------------------------------------------------------------------
-// Exclusive scan of a level's run lengths into offs in one launch: a chained scan with decoupled look-back.  Workgroups take chunks of
-// kScanChunk counts in order from a counter; each publishes its chunk's sum
-// at once and, after looking back at its predecessors' published sums (or
-// inclusive prefixes), its inclusive prefix.  The first wave looks back, at 64
-// predecessors at a time: by one thread, a predecessor at a time, the scan of
-// a 2^20-key sort took 9.3 us and larger ones were better off in three
-// launches.  A status word holds all that is passed on (flag << 32 | value,
-// flag 1 = the chunk's sum, 2 = the inclusive prefix through the chunk; zeroed
-// before each level), so relaxed loads and stores do.  A chunk's predecessors
-// are held by workgroups that are already running, so every wait ends; the
-// wait is bounded all the same (status set to an internal error after
-// kScanSpinMax polls).  Sums are taken modulo 2^32: offsets are only ever
-// subtracted from offsets of the same segment, which is shorter than 2^32.
-constexpr int kScanThreads = 256, kScanItems = 16, kScanChunk = kScanThreads * kScanItems;
+// Exclusive scan of a level's run lengths into offs in one launch: a chained
+// scan with decoupled look-back.  Workgroups take chunks of run lengths in
+// order from a counter; each publishes its chunk's sum at once and, after
+// looking back at its predecessors' published sums (or inclusive prefixes),
+// its inclusive prefix.  The first wave looks back, at 64 predecessors at a
+// time: by one thread, a predecessor at a time, the scan of a 2^20-key sort
+// took 9.3 us and larger ones were better off in three launches.  A status
+// word holds all that is passed on (flag << 32 | value, flag 1 = the chunk's
+// sum, 2 = the inclusive prefix through the chunk; zeroed before each level),
+// so relaxed loads and stores do.  A chunk's predecessors are held by
+// workgroups that are already running, so every wait ends; the wait is bounded
+// all the same (status set to an internal error after kScanSpinMax polls).
+// Sums are taken modulo 2^32: offsets are only ever subtracted from offsets of
+// the same segment, which is shorter than 2^32.
+// Chunks: 16 run lengths per thread of 256 threads, or of 1024 for matrices of
+// more than 2^21 entries (two of 2^23: 74 instead of 109 us; one of 2^17 entries:
+// 7.7 instead of 5.5 us).
+constexpr int kScanItems = 16, kScanChunk = 256 * kScanItems;  // (the smallest)
 constexpr uint32_t kScanSpinMax = 1u << 26;
 
-__global__ __launch_bounds__(kScanThreads) void k_scan(Work w, int lev) {
-  __shared__ uint32_t tmp[kScanThreads / kWave + 1];
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_scan(Work w, int lev) {
+  constexpr uint32_t CHUNK = THREADS * kScanItems;
+  __shared__ uint32_t tmp[THREADS / kWave + 1];
   __shared__ uint32_t s_chunk, s_prefix;
   const uint32_t M = w.ctl->entries[lev & 1];
   const uint32_t *const runs = w.runs[lev & 1], len_mask = 0xFFFFu;
   uint32_t* const offs = w.offs[lev & 1];
-  const uint32_t nb = (M + kScanChunk - 1) / kScanChunk;
+  const uint32_t nb = (M + CHUNK - 1) / CHUNK;
   // as many workgroups as chunks take part (the others would only queue for
   // the chunk counter, at about 10 ns each)
   if (blockIdx.x >= nb) return;
@@ -586,7 +622,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(Work w, int lev) {
     __syncthreads();
     const uint32_t c = s_chunk;
     if (c >= nb) break;
-    const uint32_t b0 = c * kScanChunk + threadIdx.x * kScanItems;
+    const uint32_t b0 = c * CHUNK + threadIdx.x * kScanItems;
     uint32_t v[kScanItems];
 #pragma unroll
     for (int q = 0; q < kScanItems / 4; q++) {
@@ -606,7 +642,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(Work w, int lev) {
 #pragma unroll
     for (int i = 0; i < kScanItems; i++) sum += v[i];
     uint32_t tot;
-    uint32_t e = block_excl_scan<kScanThreads>(sum, tmp, &tot);
+    uint32_t e = block_excl_scan<THREADS>(sum, tmp, &tot);
     if (threadIdx.x < kWave) {  // the first wave
       const uint32_t lane = threadIdx.x;
       auto publish = [&](uint64_t flag, uint32_t v) {
@@ -675,9 +711,11 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(Work w, int lev) {
 //
 // The next tile's elements are loaded once this tile's are staged (into the
 // same registers) and arrive while it is written out; on a buffer level their
-// places come from a RunMap that is built between this tile's barriers, from
-// descriptors loaded a tile ahead.  All LDS that a tile's first phase writes is
-// kept twice, so that no barrier closes the loop.
+// places come from a RunMap that is built between this tile's barriers.  The
+// tile after that has its segment's descriptor loaded meanwhile, and a new
+// segment's splitter tree is fetched a tile ahead.  All LDS that a tile's
+// first phase writes is kept twice, so that no barrier closes the loop (one
+// tree only where two do not fit, with its load and a barrier exposed).
 template <typename K, bool F32, bool SRC_IN, bool PAY, int THREADS, int ITEMS>
 __global__ __launch_bounds__(THREADS) void k_split(Work w, int lev, const K* in_keys, const uint32_t* in_pay,
                                                    int src_buf, int dst_buf) {
@@ -688,8 +726,9 @@ __global__ __launch_bounds__(THREADS) void k_split(Work w, int lev, const K* in_
   using Map = RunMap<SRC_IN ? kWave : THREADS, SRC_IN ? kWave : (int)TILE>;
   static_assert(THREADS >= kMaxK, "one histogram bin per thread");
   static_assert(TILE <= (1u << 14), "run starts and lengths fit 16 bits, ranks 23");
-  __shared__ K tk[2 * kMaxK];
-  __shared__ uint32_t ti[kMaxK];
+  constexpr int TREES = SRC_IN || W < 4 ? 2 : 1;
+  __shared__ K tk[TREES][2 * kMaxK];
+  __shared__ uint32_t ti[TREES][kMaxK];
   __shared__ uint32_t hist[2][kMaxK];
   __shared__ uint32_t tmp[THREADS / kWave + 1];
   __shared__ Map map[MAPS];
@@ -750,22 +789,17 @@ __global__ __launch_bounds__(THREADS) void k_split(Work w, int lev, const K* in_
         if constexpr (PAY) pay[i] = at32(in_pay + base, p);
       }
     } else {
-      const View bv{w.buf_rec[src_buf]};
-      if (mp.over == 0) {  // uniform
-#pragma unroll
-        for (int i = 0; i < ITEMS; i++) {
-          // (lanes past the end read the last element's run: their wave's
-          // words hold no bit after it)
-          const uint32_t p = i * THREADS + t;
-          const uint32_t d = i * THREADS + (t & ~(kWave - 1)) < (int)cnt ? mp.at(p) - (p < cnt ? 0u : p - cnt + 1u) : 0u;
-          bv.get(b.pstart + d, key[i], idx[i], pay[i]);
-        }
-      } else {
+      const View bv{w.buf_rec[src_buf] + b.pstart * W};
+      if (mp.over != 0) {  // uniform
 #pragma unroll
         for (int i = 0; i < ITEMS; i++) {
           const uint32_t p = min((uint32_t)(i * THREADS + t), cnt - 1u);
-          bv.get(b.pstart + locate(w, src_buf, b.col, 0, b.nt - 1, tl * TILE + p), key[i], idx[i], pay[i]);
+          bv.get(locate(w, src_buf, b.col, 0, b.nt - 1, tl * TILE + p), key[i], idx[i], pay[i]);
         }
+      } else if (((uint64_t)b.nt << w.tile_log2) * (4 * W) <= 0xFFFFFFFFull) {  // uniform: 32-bit offsets do
+        mp.each(t, cnt, [&](int i, uint32_t d) { bv.get32(d, key[i], idx[i], pay[i]); });
+      } else {
+        mp.each(t, cnt, [&](int i, uint32_t d) { bv.get(d, key[i], idx[i], pay[i]); });
       }
     }
   };
@@ -776,8 +810,10 @@ __global__ __launch_bounds__(THREADS) void k_split(Work w, int lev, const K* in_
 
   uint32_t s = seg_of(g);
   BigSeg bs = uniform_seg(w.big[cur][s]);
-  tree_to_lds<K, THREADS>(w, s, bs.logk, tk, ti);
-  int par = 0;
+  TreePart<K> tree;
+  tree.fetch(w, s, bs.logk, t);
+  tree.store(bs.logk, t, tk[0], ti[0]);
+  int par = 0, tp = 0;
   if constexpr (!SRC_IN) {
     const Run r = run_of(bs, uniform(w.tile_run[g]));
     const uint32_t j0 = (g - bs.tb) * TILE, cnt = min(TILE, bs.len - j0);
@@ -788,29 +824,39 @@ __global__ __launch_bounds__(THREADS) void k_split(Work w, int lev, const K* in_
     __syncthreads();
     map[0].number(t, r.run, r.ofs, r.e, j0, w.tile_log2, bal);
   }
+  // the next tile's segment and first run
+  uint32_t sn = s, first = 0;
+  BigSeg bn = bs;
+  if (g + step < hi) {
+    sn = seg_of(g + step);
+    if (m > 1) bn = uniform_seg(w.big[cur][sn]);
+    if constexpr (!SRC_IN) first = uniform(w.tile_run[g + step]);
+  }
   __syncthreads();
   load(bs, g - bs.tb, map[0]);
   bool pairs = false;  // classification mode of this wave's next tile
-  uint32_t tree_of = s;
   for (;;) {
     const uint32_t tl = g - bs.tb, cnt = min(TILE, bs.len - tl * TILE), kk = 1u << bs.logk;
     uint32_t* const h = hist[par];
-    if (tree_of != s) {  // uniform; every wave has classified the tile before
-      tree_to_lds<K, THREADS>(w, s, bs.logk, tk, ti);
-      tree_of = s;
-      __syncthreads();
-    }
-    // the next tile's segment, on its way while this tile is classified
-    const uint32_t gn = g + step;
-    const bool more = gn < hi;
-    uint32_t sn = s, first = 0;
-    BigSeg bn = bs;
-    if (more) {
-      if (m > 1) {
-        sn = w.tile_seg[gn];
-        bn = w.big[cur][sn];
+    const uint32_t gn = g + step, g2 = gn + step;
+    const bool more = gn < hi, more2 = g2 < hi;
+    // on their way while this tile is classified: the next tile's runs and, if
+    // it is of another segment, tree; the segment of the tile after that
+    Run rn{0u, 0u, 0u, 0u};
+    uint32_t j0 = 0, cn = 0;
+    if constexpr (!SRC_IN) {
+      if (more) {
+        rn = run_of(bn, first);
+        j0 = (gn - bn.tb) * TILE;
+        cn = min(TILE, bn.len - j0);
       }
-      if constexpr (!SRC_IN) first = w.tile_run[gn];
+    }
+    const bool new_tree = sn != s;  // uniform
+    if (TREES == 2 && new_tree) tree.fetch(w, sn, bn.logk, t);
+    uint32_t s2 = sn, first2 = 0;
+    if (more2) {
+      if (m > 1) s2 = w.tile_seg[g2];
+      if constexpr (!SRC_IN) first2 = w.tile_run[g2];
     }
     if constexpr (!SRC_IN) map[(par ^ 1) & (MAPS - 1)].clear(t);
     if (t < kMaxK) hist[par ^ 1][t] = 0;
@@ -822,7 +868,7 @@ __global__ __launch_bounds__(THREADS) void k_split(Work w, int lev, const K* in_
       for (int i = 0; i < ITEMS; i++) key[i] = ord_of<K, F32>(key[i]);
     }
     uint32_t pos[ITEMS];  // bucket, then place in the staged tile
-    classify_batch<K, ITEMS>(tk, ti, bs.logk, key, valid, [&](int i) -> uint32_t { return idx[i]; }, pos, pairs);
+    classify_batch<K, ITEMS>(tk[tp], ti[tp], bs.logk, key, valid, [&](int i) -> uint32_t { return idx[i]; }, pos, pairs);
     // rank inside (tile, bucket): one LDS atomic per element, or one per wave
     // when the whole wave falls into a single bucket (skewed inputs).  A
     // wave's valid elements are a prefix of its lanes, so lane 0 holds one
@@ -842,17 +888,24 @@ __global__ __launch_bounds__(THREADS) void k_split(Work w, int lev, const K* in_
       }
       pos[i] = (pos[i] << 23) | r;  // bucket < 2^9, r < TILE
     }
-    sn = uniform(sn);
-    if (m > 1) bn = uniform_seg(bn);
-    Run rn{0u, 0u, 0u, 0u};
-    uint32_t j0 = 0, cn = 0;
+    // the next tile's runs are touched line by line, so that their elements
+    // come from the L2 when they are loaded, after this tile is staged (second
+    // level of 2^28 u64 keys: 2034 -> 1901 us)
+    constexpr int TOUCH = SRC_IN ? 1 : 5;
+    uint32_t touched[TOUCH];
     if constexpr (!SRC_IN) {
-      if (more) {
-        rn = run_of(bn, uniform(first));
-        j0 = (gn - bn.tb) * TILE;
-        cn = min(TILE, bn.len - j0);
-      }
+      const bool in = rn.c > 0 && rn.ofs < j0 + cn && rn.ofs + rn.c > j0;
+      const uint32_t bytes = in ? rn.c * (4 * W) : 4u;
+      const char* line = reinterpret_cast<const char*>(w.buf_rec[src_buf] +
+                                                       (bn.pstart + (in ? (rn.run << w.tile_log2) + rn.e : 0u)) * W);
+#pragma unroll
+      for (int k = 0; k < TOUCH; k++)
+        touched[k] = *reinterpret_cast<const uint32_t*>(line + min((uint32_t)k * 128u, bytes - 4u));
     }
+    s2 = uniform(s2);
+    BigSeg b2 = bn;
+    if (m > 1) b2 = w.big[cur][s2];
+    if (TREES == 2 && new_tree) tree.store(bn.logk, t, tk[(tp ^ 1) & (TREES - 1)], ti[(tp ^ 1) & (TREES - 1)]);
     __syncthreads();
     // exclusive scan of the tile histogram -> tile-local bucket starts
     const uint32_t hv = t < (int)kk ? h[t] : 0u;
@@ -878,6 +931,10 @@ __global__ __launch_bounds__(THREADS) void k_split(Work w, int lev, const K* in_
 #pragma unroll
     for (int i = 0; i < ITEMS; i++)
       if (valid[i]) View{stage}.put(pos[i], key[i], idx[i], pay[i]);
+    if constexpr (!SRC_IN) {
+#pragma unroll
+      for (int k = 0; k < TOUCH; k++) asm volatile("" ::"v"(touched[k]));
+    }
     if (more) load(bn, gn - bn.tb, map[(par ^ 1) & (MAPS - 1)]);
     __syncthreads();
     // the tile, as it lies
@@ -894,9 +951,21 @@ __global__ __launch_bounds__(THREADS) void k_split(Work w, int lev, const K* in_
       if (t < (int)(words & 3u)) out[4 * quads + t] = stage[4 * quads + t];
     }
     if (!more) break;
+    if (new_tree) {
+      if constexpr (TREES == 2) {
+        tp ^= 1;
+      } else {  // (every wave has classified this tile)
+        tree.fetch(w, sn, bn.logk, t);
+        tree.store(bn.logk, t, tk[0], ti[0]);
+        __syncthreads();
+      }
+    }
     g = gn;
     s = sn;
     bs = bn;
+    sn = s2;
+    if (m > 1) bn = uniform_seg(b2);
+    first = uniform(first2);
     par ^= 1;
   }
 }
@@ -1218,8 +1287,11 @@ static int enqueue_typed(const void* keys_in, const uint32_t* pay_in, const uint
       else
         RS_LAUNCH((k_split<K, false, false, PAY, 1024, 8>), g, 1024, st, w, (int)lev, kin, pay_in, src, dst);
     }
-    RS_LAUNCH(k_scan, grid_for(w.count_max / kScanChunk + 1, 4), kScanThreads, st, w, (int)lev);
-    RS_LAUNCH(k_route, gs, kRouteThreads, st, w, (int)lev, le);
+    if (w.count_max > 1ull << 21)
+      RS_LAUNCH(k_scan<1024>, grid_for(w.count_max / (1024 * kScanItems) + 1, 2), 1024, st, w, (int)lev);
+    else
+      RS_LAUNCH(k_scan<256>, grid_for(w.count_max / kScanChunk + 1, 4), 256, st, w, (int)lev);
+    RS_LAUNCH(k_route, grid_for(w.big_max, 4), kRouteThreads, st, w, (int)lev, le);
   }
   return local_sorts();
 }

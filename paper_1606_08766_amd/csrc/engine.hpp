@@ -130,6 +130,10 @@ struct BufView {
   __device__ __forceinline__ void get(uint64_t i, K& k, uint32_t& v, uint32_t& y) const {
     unpack(*reinterpret_cast<const Rec*>(p + i * W), k, v, y);
   }
+  // get with a scalar base and a 32-bit byte offset
+  __device__ __forceinline__ void get32(uint32_t i, K& k, uint32_t& v, uint32_t& y) const {
+    unpack(at32(reinterpret_cast<const Rec*>(p), i), k, v, y);
+  }
   __device__ __forceinline__ void put(uint64_t i, K k, uint32_t v, uint32_t y) const {
     Rec r;
     r.x[0] = (uint32_t)k;
@@ -185,7 +189,7 @@ struct SegReader {
 // Where the elements of a bucket, or of a stretch [j0, j0 + cnt) of one, lie:
 // built by a workgroup in LDS from the bucket's runs, one thread per run, in
 // three steps with a barrier after each, and then read by whole waves, each
-// over 64 consecutive elements.  mask holds a bit for each element that is the
+// over 64 consecutive elements at a time.  mask holds a bit for each element that is the
 // first of its run (or of the stretch), base the bits before each of its
 // words, delta, by run, what added to an element's place in the stretch gives
 // its place in the segment.  A stretch of more runs than threads (elements
@@ -238,15 +242,43 @@ struct RunMap {
       }
     }
   }
-  // Element p of the stretch, its place in the segment; p is the wave's first
-  // element (a multiple of 64) plus the lane.  p must lie in the stretch.
-  __device__ __forceinline__ uint32_t at(uint32_t p) const {
-    const uint32_t wd = uniform(p >> 6);
-    const uint64_t m = uniform64(mask[wd]);
-    const uint32_t b = uniform(base[wd]) + (uint32_t)(m & 1ull) - 1u;
-    const uint64_t m1 = m >> 1;  // bits up to the lane's own, less bit 0
-    const uint32_t ord = __builtin_amdgcn_mbcnt_hi((uint32_t)(m1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m1, b));
+  // A wave's words: lane i holds what its element i * THREADS + t (one of
+  // N / THREADS per thread) needs, read with one LDS access for all of them.
+  struct Words {
+    uint32_t lo, hi, first;
+  };
+  __device__ __forceinline__ Words words(int t) const {
+    const int wd = min(t & (kWave - 1), N / THREADS - 1) * NW + t / kWave;
+    const uint64_t m = mask[wd];
+    // run of the word's first element; the bits after it, moved down one
+    return Words{(uint32_t)(m >> 1), (uint32_t)(m >> 33), base[wd] + (uint32_t)(m & 1ull) - 1u};
+  }
+  // Place in the segment of element p = i * THREADS + t of the stretch.
+  __device__ __forceinline__ uint32_t at(const Words& w, int i, uint32_t p) const {
+    const uint32_t ord = __builtin_amdgcn_mbcnt_hi(
+        lane_u32(w.hi, i), __builtin_amdgcn_mbcnt_lo(lane_u32(w.lo, i), lane_u32(w.first, i)));
     return delta[ord] + p;
+  }
+  // Loads a thread's elements of the stretch (its first cnt; a thread past the
+  // end gets some element of the stretch): get(i, place).  Every lane of
+  // every wave calls.
+  template <typename F>
+  __device__ __forceinline__ void each(int t, uint32_t cnt, F&& get) const {
+    constexpr int ITEMS = N / THREADS;
+    const Words w = words(t);
+    if (cnt == (uint32_t)N) {  // uniform
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++) get(i, at(w, i, i * THREADS + t));
+    } else {
+      const uint32_t d0 = delta[0];
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++) {
+        const uint32_t p = i * THREADS + t;
+        // past the end: the wave's last element, or the stretch's first
+        const uint32_t d = i * THREADS + (t & ~(kWave - 1)) < (int)cnt ? at(w, i, p) - (p < cnt ? 0u : p - cnt + 1u) : d0;
+        get(i, d);
+      }
+    }
   }
 };
 

@@ -225,21 +225,15 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
   auto load = [&](const FinalSeg& f, int t) {
     if (!DIRECT && f.src) {
       const BufView<K, PAY> bv{w.buf_rec[f.src - 1] + f.pstart * BufView<K, PAY>::W};
-      if (map.over == 0) {  // uniform
-#pragma unroll
-        for (int i = 0; i < ITEMS; i++) {
-          const uint32_t p = i * THREADS + t;
-          // (a wave past the end: the segment's first element)
-          const uint32_t d = i * THREADS + (t & ~(kWave - 1)) < (int)f.len
-                                 ? map.at(p) - (p < f.len ? 0u : p - f.len + 1u)
-                                 : map.delta[0];
-          bv.get(d, key[i], idx[i], pay[i]);
-        }
-      } else {
+      if (map.over != 0) {  // uniform
 #pragma unroll
         for (int i = 0; i < ITEMS; i++)
           bv.get(locate(w, (int)f.src - 1, f.col, 0, f.nt - 1, min((uint32_t)(i * THREADS + t), f.len - 1)), key[i],
                  idx[i], pay[i]);
+      } else if (((uint64_t)f.nt << w.tile_log2) * (4 * BufView<K, PAY>::W) <= 0xFFFFFFFFull) {  // 32-bit offsets do
+        map.each(t, f.len, [&](int i, uint32_t d) { bv.get32(d, key[i], idx[i], pay[i]); });
+      } else {
+        map.each(t, f.len, [&](int i, uint32_t d) { bv.get(d, key[i], idx[i], pay[i]); });
       }
     } else {
       const K* const kin = in_keys + f.start;
