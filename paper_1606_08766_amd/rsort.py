@@ -156,12 +156,16 @@ def _check(rc: int, what: str):
 
 
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    """The raw stream handle (ctypes takes it as an int): of the given stream,
+    else of the current device's current one, without building a Stream
+    object."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _kt(keys: torch.Tensor, kt=None) -> int:
@@ -224,21 +228,25 @@ def sort(keys: torch.Tensor, with_perm: bool = True, kt=None, workspace: torch.T
 
     Returns (keys_out, perm_out or None); perm_out[r] is the input position of
     the element of rank r (equal keys keep input order)."""
+    # (a call of a few thousand keys takes the GPU about 7 us: what is made
+    # here needs none of the checks a caller's tensors get)
+    L = _lib or lib()
     kt = _kt(keys, kt)
     _require_cuda(keys)
     n = keys.numel()
+    device = keys.device
     if out is not None:
         ko, po = out
+        _require_like(ko, "keys_out", device, n, keys.element_size())
+        _require_like(po, "perm_out", device, n, 4, _U32_LIKE)
     else:
         ko = torch.empty_like(keys)
-        po = torch.empty(n, dtype=torch.uint32, device=keys.device) if with_perm else None
-    _require_like(ko, "keys_out", keys.device, n, keys.element_size())
-    _require_like(po, "perm_out", keys.device, n, 4, _U32_LIKE)
-    wsb = plain_workspace_bytes(kt, n)
+        po = torch.empty(n, dtype=torch.uint32, device=device) if with_perm else None
     if workspace is None:
-        workspace = torch.empty(max(wsb, 256), dtype=torch.uint8, device=keys.device)
-    _require_cuda(workspace)
-    rc = lib().rsort_plain(kt, _ptr(keys), n, _ptr(ko), _ptr(po), _ptr(workspace), workspace.numel(), _stream(stream))
+        workspace = torch.empty(max(L.rsort_plain_workspace(kt, n), 256), dtype=torch.uint8, device=device)
+    else:
+        _require_cuda(workspace)
+    rc = L.rsort_plain(kt, _ptr(keys), n, _ptr(ko), _ptr(po), _ptr(workspace), workspace.numel(), _stream(stream))
     _check(rc, "rsort_plain")
     _keep_alive(stream, keys, ko, po, workspace)
     return ko, po
@@ -284,6 +292,7 @@ def segmented_sort(keys: torch.Tensor, offsets: torch.Tensor, payload: torch.Ten
 
     offsets: device u64 (or int64) tensor of num_segs + 1 entries.  Returns
     (keys_out, perm_out or None, payload_out or None); perm is segment-local."""
+    L = _lib or lib()
     kt = _kt(keys, kt)
     _require_cuda(keys, offsets, payload)
     n = keys.numel()
@@ -294,20 +303,21 @@ def segmented_sort(keys: torch.Tensor, offsets: torch.Tensor, payload: torch.Ten
     _require_like(payload, "payload", keys.device, n, 4, _U32_LIKE)
     if out is not None:
         ko, po, plo = out
+        _require_like(ko, "keys_out", keys.device, n, keys.element_size())
+        _require_like(po, "perm_out", keys.device, n, 4, _U32_LIKE)
+        _require_like(plo, "payload_out", keys.device, n, 4, _U32_LIKE)
+        if (payload is None) != (plo is None):
+            raise ValueError("payload and payload_out go together")
     else:
         ko = torch.empty_like(keys)
         po = torch.empty(n, dtype=torch.uint32, device=keys.device) if with_perm else None
         plo = torch.empty_like(payload) if payload is not None else None
-    _require_like(ko, "keys_out", keys.device, n, keys.element_size())
-    _require_like(po, "perm_out", keys.device, n, 4, _U32_LIKE)
-    _require_like(plo, "payload_out", keys.device, n, 4, _U32_LIKE)
-    if (payload is None) != (plo is None):
-        raise ValueError("payload and payload_out go together")
-    wsb = segmented_workspace_bytes(kt, n, ns, payload is not None)
     if workspace is None:
+        wsb = L.rsort_segmented_workspace(kt, n, ns, 1 if payload is not None else 0)
         workspace = torch.empty(max(wsb, 256), dtype=torch.uint8, device=keys.device)
-    _require_cuda(workspace)
-    rc = lib().rsort_segmented(kt, _ptr(keys), _ptr(payload), _ptr(offsets), ns, n, _ptr(ko), _ptr(plo), _ptr(po),
+    else:
+        _require_cuda(workspace)
+    rc = L.rsort_segmented(kt, _ptr(keys), _ptr(payload), _ptr(offsets), ns, n, _ptr(ko), _ptr(plo), _ptr(po),
                                _ptr(workspace), workspace.numel(), _stream(stream))
     _check(rc, "rsort_segmented")
     _keep_alive(stream, keys, offsets, payload, ko, po, plo, workspace)
