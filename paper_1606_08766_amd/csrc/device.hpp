@@ -384,6 +384,17 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
   return ((uint64_t)uniform((uint32_t)(x >> 32)) << 32) | uniform((uint32_t)x);
 }
 
+// LDS addresses as numbers (32 bits on the device): a walk over a table whose
+// base is only known at run time then needs no addition per step.
+template <typename T>
+__device__ __forceinline__ uint32_t lds_address(const T* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const T*)p;
+}
+template <typename T>
+__device__ __forceinline__ T lds_at(uint32_t a) {
+  return *(__attribute__((address_space(3))) const T*)(uintptr_t)a;
+}
+
 // Inclusive scan across each row of 16 lanes, all lanes active (DPP row
 // shifts; lanes without a source add 0).
 __device__ __forceinline__ uint32_t row_incl_scan_dpp(uint32_t v) {

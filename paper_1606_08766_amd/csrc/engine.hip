@@ -516,20 +516,24 @@ __device__ __forceinline__ void classify_batch(const K* tk, const uint32_t* ti, 
     }
     pairs = !__any(untied);
   } else {
-    const char* tb = reinterpret_cast<const char*>(tk);
-    uint32_t a[ITEMS];  // byte offset of the current node
+    // the current node's LDS address; twice it, less the tree's (once) and
+    // plus a node's size for the right child, is the child's: no addition of
+    // the tree's base per step (with the ranks below, the second level of 2^28
+    // u64 keys, bound by its vector instructions: 1869 -> 1806 us)
+    const uint32_t tb = uniform(lds_address(tk)), left = 0u - tb, right = KB - tb;
+    uint32_t a[ITEMS];
 #pragma unroll
-    for (int i = 0; i < ITEMS; i++) a[i] = KB;
+    for (int i = 0; i < ITEMS; i++) a[i] = tb + KB;
     for (uint32_t l = 0; l < logk; l++) {
 #pragma unroll
       for (int i = 0; i < ITEMS; i++) {
-        const K t = *reinterpret_cast<const K*>(tb + a[i]);
-        a[i] = 2u * a[i] + (key[i] > t ? KB : 0u);
+        const K t = lds_at<K>(a[i]);
+        a[i] = 2u * a[i] + (key[i] > t ? right : left);
       }
     }
     K leaf[ITEMS];
 #pragma unroll
-    for (int i = 0; i < ITEMS; i++) leaf[i] = *reinterpret_cast<const K*>(tb + a[i]);
+    for (int i = 0; i < ITEMS; i++) leaf[i] = lds_at<K>(a[i]);
     bool eq[ITEMS];
     bool tie = false, untied = false;
 #pragma unroll
@@ -537,7 +541,7 @@ __device__ __forceinline__ void classify_batch(const K* tk, const uint32_t* ti, 
       eq[i] = (key[i] == leaf[i]) & valid[i];
       tie = tie | eq[i];
       untied = untied | (valid[i] & !eq[i]);
-      j[i] = a[i] / KB;
+      j[i] = (a[i] - tb) / KB;
     }
     if (__any(tie)) {
       uint32_t q[ITEMS];
@@ -725,7 +729,7 @@ __global__ __launch_bounds__(THREADS) void k_split(Work w, int lev, const K* in_
   constexpr int MAPS = SRC_IN ? 1 : 2;
   using Map = RunMap<SRC_IN ? kWave : THREADS, SRC_IN ? kWave : (int)TILE>;
   static_assert(THREADS >= kMaxK, "one histogram bin per thread");
-  static_assert(TILE <= (1u << 14), "run starts and lengths fit 16 bits, ranks 23");
+  static_assert(TILE <= (1u << 14), "run starts, lengths and ranks fit 16 bits");
   constexpr int TREES = SRC_IN || W < 4 ? 2 : 1;
   __shared__ K tk[TREES][2 * kMaxK];
   __shared__ uint32_t ti[TREES][kMaxK];
@@ -869,24 +873,34 @@ __global__ __launch_bounds__(THREADS) void k_split(Work w, int lev, const K* in_
     }
     uint32_t pos[ITEMS];  // bucket, then place in the staged tile
     classify_batch<K, ITEMS>(tk[tp], ti[tp], bs.logk, key, valid, [&](int i) -> uint32_t { return idx[i]; }, pos, pairs);
-    // rank inside (tile, bucket): one LDS atomic per element, or one per wave
-    // when the whole wave falls into a single bucket (skewed inputs).  A
+    // rank inside (tile, bucket): one LDS atomic per element; where the
+    // wave's first 64 elements all fall into one bucket (skewed inputs), it
+    // looks for one bucket among each 64 and takes one atomic for them.  A
     // wave's valid elements are a prefix of its lanes, so lane 0 holds one
     // whenever any lane does.
     const uint32_t lane = lane_id();
+    if (__ballot(valid[0] && pos[0] != uniform(pos[0])) != 0) {
 #pragma unroll
-    for (int i = 0; i < ITEMS; i++) {
-      const uint32_t b0 = uniform(pos[i]);
-      uint32_t r = 0;
-      if (__ballot(valid[i] && pos[i] != b0) == 0) {
-        const uint64_t act = __ballot(valid[i]);
-        uint32_t basev = 0;
-        if (lane == 0 && act) basev = atomicAdd(&h[b0], (uint32_t)__popcll(act));
-        r = uniform(basev) + (uint32_t)__popcll(act & ((1ull << lane) - 1ull));
-      } else if (valid[i]) {
-        r = atomicAdd(&h[pos[i]], 1u);
+      for (int i = 0; i < ITEMS; i++) {
+        uint32_t r = 0;
+        if (valid[i]) r = atomicAdd(&h[pos[i]], 1u);
+        pos[i] = (pos[i] << 18) | r;  // 4 * bucket << 16, r < TILE
       }
-      pos[i] = (pos[i] << 23) | r;  // bucket < 2^9, r < TILE
+    } else {
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++) {
+        const uint32_t b0 = uniform(pos[i]);
+        uint32_t r = 0;
+        if (__ballot(valid[i] && pos[i] != b0) == 0) {
+          const uint64_t act = __ballot(valid[i]);
+          uint32_t basev = 0;
+          if (lane == 0 && act) basev = atomicAdd(&h[b0], (uint32_t)__popcll(act));
+          r = uniform(basev) + (uint32_t)__popcll(act & ((1ull << lane) - 1ull));
+        } else if (valid[i]) {
+          r = atomicAdd(&h[pos[i]], 1u);
+        }
+        pos[i] = (pos[i] << 18) | r;
+      }
     }
     // the next tile's runs are touched line by line, so that their elements
     // come from the L2 when they are loaded, after this tile is staged (second
@@ -927,7 +941,7 @@ __global__ __launch_bounds__(THREADS) void k_split(Work w, int lev, const K* in_
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < ITEMS; i++) pos[i] = h[pos[i] >> 23] + (pos[i] & 0x7FFFFFu);
+    for (int i = 0; i < ITEMS; i++) pos[i] = at32(h, pos[i] >> 18) + (pos[i] & 0xFFFFu);
 #pragma unroll
     for (int i = 0; i < ITEMS; i++)
       if (valid[i]) View{stage}.put(pos[i], key[i], idx[i], pay[i]);
