@@ -67,3 +67,19 @@ def test_oversize_buckets_of_several_segments(kt):
         ko, po, plo, _ = gpu_segmented(keys, off, pay)
     ek, ep, epl = O.segmented(keys, off, pay)
     assert same_bits(ko, ek) and np.array_equal(po, ep) and np.array_equal(plo, epl)
+
+
+@pytest.mark.parametrize("m", [511, 1025, 5000])
+@pytest.mark.parametrize("wide", [0, 7, 600])
+def test_routing_of_many_segments(m, wide):
+    """Segments to split in numbers around what the routing workgroups take at
+    once: all of them narrow (64 buckets at most), or one in `wide` wider."""
+    sizes = np.full(m, 300, dtype=np.uint64) + np.arange(m, dtype=np.uint64) % 700
+    if wide:
+        sizes[::wide] = 12000
+    keys, pay, off = gen.segmented("u32", sizes, ["uniform", "zero", "gaussian"] * (m // 3) + ["uniform"] * (m % 3),
+                                   seed=m)
+    with R.tuned(cap=256):
+        ko, po, plo, _ = gpu_segmented(keys, off, pay)
+    ek, ep, epl = O.segmented(keys, off, pay)
+    assert same_bits(ko, ek) and np.array_equal(po, ep) and np.array_equal(plo, epl)
