@@ -243,14 +243,15 @@ __global__ __launch_bounds__(THREADS) void k_splitters(Work w, int lev, const K*
                                                        uint32_t a, uint64_t seed, int staged) {
   constexpr int N = THREADS * ITEMS;
   constexpr int NP = lpad_size(N);
-  constexpr int LB = 31 - __builtin_clz((unsigned)(N / 8));  // bins of the ranking path
-  constexpr int PL = (1 << LB) / kWave;
-  static_assert(PL >= 1, "one bin per lane at least");
+  constexpr int LB = 31 - __builtin_clz((unsigned)N);  // bins of the ranking path
+  constexpr int PL = (1 << LB) / THREADS;
+  static_assert(PL >= 1, "one bin per thread at least");
   __shared__ uint32_t s_lo[NP];
   __shared__ uint32_t s_hi[sizeof(K) == 8 ? NP : 1];
   __shared__ uint32_t s_v[NP];
   __shared__ uint32_t s_bin[(1 << LB) + 1];
   __shared__ uint32_t s_red[6 * (THREADS / kWave)];
+  __shared__ uint32_t s_tmp[THREADS / kWave + 1];
   __shared__ uint32_t s_cost;
   const LdsArr<K> sa{s_lo, s_hi, s_v, nullptr};
   const int cur = lev & 1;
@@ -336,12 +337,17 @@ __global__ __launch_bounds__(THREADS) void k_splitters(Work w, int lev, const K*
     }
     const uint32_t kk = 1u << bs.logk;
     // The splitters are the samples of rank j * ae - 1 (j = 1 .. kk - 1) in
-    // (key, position) order.  Ranks come from bins, as in the word sort:
+    // (key, position) order.  Ranks come from bins:
     // samples are counted into bins by the top bits of (key - min) (or, for a
     // narrow key range, key offset then position bits), and a sample's rank
     // is its bin's start plus the number of smaller samples in its bin.  If
-    // that would cost more than kRankBudget compares per sample, the samples
-    // are merge sorted instead.
+    // that would cost more than kSplRankBudget compares per sample, the samples
+    // are merge sorted instead.  As many bins as samples: the compares are a
+    // serial chain per thread and the ranking's bound, so bins are small and
+    // read four samples at a time (from an eighth of the bins, a sample at a
+    // time: first and second level of 2^26 gaussian f32 38 + 63 -> 25 + 49 us,
+    // of 2^28 u64 30 + 134 -> 20 + 120, of 2^25 u64 with duplicates 11 + 58 ->
+    // 11 + 30; what is left of the second level is the samples' loads).
     bool ranked = false;
     {
       K kmn = KMax<K>::v, kmx = K(0);
@@ -356,6 +362,7 @@ __global__ __launch_bounds__(THREADS) void k_splitters(Work w, int lev, const K*
         }
       }
       for (int b = threadIdx.x; b <= (1 << LB); b += THREADS) s_bin[b] = 0;
+      if (threadIdx.x == 0) s_cost = 0;
       const Range4 br = block_range<K, THREADS>(kmn, kmx, imn, imx, s_red, threadIdx.x);
       kmn = (K)br.kmn;
       const uint64_t kr = (uint64_t)((K)br.kmx - kmn);
@@ -380,23 +387,23 @@ __global__ __launch_bounds__(THREADS) void k_splitters(Work w, int lev, const K*
         if (threadIdx.x * ITEMS + i < S) r[i] = atomicAdd(&s_bin[bin_of(k[i], v[i])], 1u);
       }
       __syncthreads();
-      if (threadIdx.x < kWave) {  // one wave scans the bins and sums their squared sizes
-        uint64_t acc = 0;
+      {  // the bins' starts and the sum of their squared sizes
+        uint32_t x[PL], sum = 0, sq = 0;
+#pragma unroll
         for (int q = 0; q < PL; q++) {
-          const uint32_t x = s_bin[threadIdx.x * PL + q];
-          acc += ((uint64_t)(x * x) << 32) | x;
+          x[q] = s_bin[threadIdx.x * PL + q];
+          sum += x[q];
+          sq += x[q] * x[q];
         }
-        const uint64_t inc = wave_incl_scan<uint64_t>(acc);
-        uint32_t e = (uint32_t)(inc - acc);
+        sq = lane_u32(wave_incl_scan_dpp(sq), kWave - 1);
+        if (lane_id() == 0 && sq) atomicAdd(&s_cost, sq);
+        uint32_t tot, b = block_excl_scan<THREADS>(sum, s_tmp, &tot);
+#pragma unroll
         for (int q = 0; q < PL; q++) {
-          const uint32_t x = s_bin[threadIdx.x * PL + q];
-          s_bin[threadIdx.x * PL + q] = e;
-          e += x;
+          s_bin[threadIdx.x * PL + q] = b;
+          b += x[q];
         }
-        if (threadIdx.x == kWave - 1) {
-          s_bin[1 << LB] = S;
-          s_cost = (uint32_t)(inc >> 32);
-        }
+        if (threadIdx.x == 0) s_bin[1 << LB] = S;
       }
       __syncthreads();
       if (s_cost <= kSplRankBudget * S) {  // uniform
@@ -406,6 +413,7 @@ __global__ __launch_bounds__(THREADS) void k_splitters(Work w, int lev, const K*
           if (threadIdx.x * ITEMS + i < S) sa.put(s_bin[bin_of(k[i], v[i])] + r[i], k[i], v[i]);
         }
         __syncthreads();
+        constexpr uint32_t U = 4;  // samples of a bin read at a time
         for (uint32_t pq = threadIdx.x; pq < S; pq += THREADS) {
           const K key = sa.key(pq);
           const uint32_t idx = s_v[pq];
@@ -414,10 +422,19 @@ __global__ __launch_bounds__(THREADS) void k_splitters(Work w, int lev, const K*
           // samples are drawn with replacement: equal samples are ranked by
           // their place in the bin, so that every rank is taken once
           uint32_t less = 0;
-          for (uint32_t q = s0; q < s1; q++) {
-            const K kq = sa.key(q);
-            const uint32_t iq = s_v[q];
-            less += (pair_less(kq, iq, key, idx) || (kq == key && iq == idx && q < pq)) ? 1u : 0u;
+          for (uint32_t q = s0; q < s1; q += U) {
+            K kq[U];
+            uint32_t iq[U];
+#pragma unroll
+            for (uint32_t u = 0; u < U; u++) {
+              kq[u] = sa.key(min(q + u, s1 - 1u));
+              iq[u] = s_v[min(q + u, s1 - 1u)];
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < U; u++) {
+              const bool below = (kq[u] < key) | ((kq[u] == key) & ((iq[u] < idx) | ((iq[u] == idx) & (q + u < pq))));
+              less += (q + u < s1) & below ? 1u : 0u;
+            }
           }
           const uint32_t rank = s0 + less;
           if ((rank + 1) % ae == 0) {
