@@ -230,12 +230,12 @@ typedef struct {
   uint32_t rfis_max;     /* segments <= rfis_max use RFIS (default 64; 0 keeps, 1 disables) */
   uint32_t rquick_max;   /* segments <= rquick_max (and > rfis_max) use RQuick */
   uint64_t seed;         /* seed of the sample positions and coin flips */
-  uint32_t tile_log2;    /* log2 of keys per scatter tile (12 or 13; counting uses 12) */
+  uint32_t tile_log2;    /* log2 of keys per tile of a split level (12 or 13) */
   uint32_t force_fallback; /* debug: 1 = every final bucket > 64 takes the
                               global-memory fallback sort, 2 = off (0 keeps) */
   uint32_t extra_levels;   /* levels beyond the fewest that reach the target
                               bucket size (at most 4): more, smaller levels
-                              shorten nothing but lengthen each scatter's runs;
+                              shorten nothing but lengthen each tile's runs;
                               the value is stored plus one (1 = none, 0 keeps) */
   uint32_t class_shape;    /* bit c: a hint for final-size class c (0..8), stored
                               and returned; the local sorts have one workgroup

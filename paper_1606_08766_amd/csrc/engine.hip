@@ -55,7 +55,7 @@ __device__ __forceinline__ uint32_t class_of(uint32_t len, uint32_t cap, uint32_
 // levels (this one included) to reach buckets of about `target` keys: the
 // 2^lq buckets needed are shared out over the levels the segment needs, the
 // upper levels taking the smaller share (fewer buckets where the data is
-// largest keeps the scatter's runs long).  Only a plan with extra levels
+// largest keeps the runs of a tile long).  Only a plan with extra levels
 // (`spread`) spreads them over more levels than the fewest that reach the
 // target, at least 4 buckets per level; otherwise a segment of a batch that
 // needs one level takes one, however many the batch's largest needs.
@@ -185,12 +185,13 @@ constexpr int kSplThreads = 1024, kSplItems = 8;  // (a = 32 at k = 256, 16 at 5
 constexpr uint32_t kStartThreads = 256;
 
 // A plain sort's start in one launch: reset the control block, route the one
-// segment [0, n) (split it, or sort it in its class), and give it its tiles.  With `staged` (a split sort of at least kSplThreads *
-// kSplItems keys), the workgroups also draw the first level's sample, the
-// same a0 * k positions the splitter kernel would, and store the (raw key,
-// position) records at the front of buffer B, which the first level does
-// not touch before its scatter: the random loads are spread over many CUs
-// instead of coming from the splitter kernel's one workgroup.
+// segment [0, n) (split it, or sort it in its class), and give it its tiles.
+// With `staged` (a split sort of at least kSplThreads * kSplItems keys), the
+// workgroups also draw the first level's sample, the same a0 * k positions
+// the splitter kernel would, and store the (raw key, position) records at the
+// front of buffer B, which the first level does not touch before its split:
+// the random loads are spread over many CUs instead of coming from the
+// splitter kernel's one workgroup.
 template <typename K>
 __global__ __launch_bounds__(kStartThreads) void k_start_plain(Work w, uint64_t n, uint32_t cap, uint32_t target,
                                                               uint32_t levels, uint32_t ff, uint32_t cmin,

@@ -17,7 +17,7 @@ struct Tuning {
   uint32_t rfis_max = 64;     // classes with upper bound <= rfis_max use RFIS
   uint32_t rquick_max = 1;    // classes with upper bound <= rquick_max use RQuick
   uint64_t seed = 0x5EED5EED12345678ull;
-  uint32_t tile_log2 = 13;  // scatter tile: 2^tile_log2 keys
+  uint32_t tile_log2 = 13;  // tile of a split level: 2^tile_log2 keys
   uint32_t force_fallback = 0;
   uint32_t extra_levels = 0;  // sample-sort levels beyond the fewest needed
   uint32_t class_shape = 0;   // stored for the caller only (rsort.h)
