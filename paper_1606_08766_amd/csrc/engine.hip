@@ -238,6 +238,11 @@ __global__ __launch_bounds__(kStartThreads) void k_start_plain(Work w, uint64_t 
 // (2q+1) * 2^(logk-1-d) (1-based, in sorted order).  The workgroup also writes
 // down, for each of the segment's tiles, the segment and (buffer levels) the
 // run that holds the tile's first element.
+// Plain sorts of at least this many keys launch both forms of the first split
+// (see k_split): the empty one costs 3 us, 0.15 % of such a sort (2^28 uniform
+// u64 keys 4697 us with and without it), and the tiled one saves a fifth of
+// the launch where splitters repeat keys.
+constexpr uint64_t kTiledMin = 1ull << 27;
 constexpr uint32_t kSplRankBudget = 64;  // compares per sample the ranking path may take
 template <typename K, bool F32, bool SRC_IN, bool PAY, int THREADS, int ITEMS>
 __global__ __launch_bounds__(THREADS) void k_splitters(Work w, int lev, const K* in_keys, int src_buf,
@@ -475,6 +480,12 @@ __global__ __launch_bounds__(THREADS) void k_splitters(Work w, int lev, const K*
     }
     if (lev == 0 && s == 0 && threadIdx.x == 0) w.ctl->l0_k = kk;
     __syncthreads();
+    if (SRC_IN && m == 1 && bs.len >= kTiledMin) {  // uniform
+      const uint32_t j = threadIdx.x;
+      const int rep =
+          __syncthreads_or(j > 0 && j + 1 < kk && w.ctl->l0_spl_key[j] == w.ctl->l0_spl_key[j - 1]);
+      if (j == 0) w.ctl->l0_repeats = rep != 0;
+    }
   }
 }
 
@@ -572,6 +583,50 @@ __device__ __forceinline__ void classify_batch(const K* tk, const uint32_t* ti, 
 #pragma unroll
   for (int i = 0; i < ITEMS; i++) b[i] = j[i] - kk;
 }
+
+// Classification of a tile whose splitters lie in order of (key, position)
+// all before or all after its elements' positions wherever keys are equal
+// (see TileTree): u holds at node t the least key that goes right.
+template <typename K, int ITEMS>
+__device__ __forceinline__ void classify_tile(const K* u, uint32_t logk, const K (&key)[ITEMS], uint32_t (&b)[ITEMS]) {
+  constexpr uint32_t KB = (uint32_t)sizeof(K);
+  const uint32_t ub = uniform(lds_address(u)), left = 0u - ub, right = KB - ub;
+  uint32_t a[ITEMS];
+#pragma unroll
+  for (int i = 0; i < ITEMS; i++) a[i] = ub + KB;
+  for (uint32_t l = 0; l < logk; l++) {
+#pragma unroll
+    for (int i = 0; i < ITEMS; i++) {
+      const K t = lds_at<K>(a[i]);
+      a[i] = 2u * a[i] + (key[i] >= t ? right : left);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < ITEMS; i++) b[i] = (a[i] - ub) / KB - (1u << logk);
+}
+
+// The elements of an input tile have consecutive positions p0 .. last, and a
+// splitter's position is seldom among them: then "(key, position) above the
+// splitter (t, q)" is "key >= t" for the whole tile if q < p0 and "key >= t +
+// 1" if q >= last, and ties need no positions.  set() writes the tree of such
+// thresholds; flags gets kBuilt, and kInside if one threshold does not exist.
+// First level of 2^28 u64 keys, all equal 1470 -> 1124 us, of 16 values
+// 1882 -> 1498.
+template <typename K>
+struct TileTree {
+  static constexpr uint32_t kBuilt = 1, kInside = 2;
+  // Thread i of at least k.
+  static __device__ __forceinline__ void set(const K* tk, const uint32_t* ti, uint32_t logk, uint32_t i, uint32_t p0,
+                                             uint32_t last, K* u, uint32_t* flags) {
+    const bool node = i > 0 && i < (1u << logk);
+    const K t = node ? tk[i] : K(0);
+    const uint32_t q = node ? ti[i] : 0u;
+    if (node) u[i] = q < p0 ? t : t + 1;
+    const bool inside = node && q >= p0 && (q < last || t == KMax<K>::v);
+    const uint32_t f = (i == 0 ? kBuilt : 0u) | (__any(inside) ? kInside : 0u);
+    if (f && lane_id() == 0) atomicOr(flags, f);
+  }
+};
 
 // Splitter tree of a segment (2^logk buckets): nodes tk[1, k) / ti[1, k) and
 // the leaf row tk[k, 2k) (see classify_batch); splitter j (1-based, in sorted
@@ -738,9 +793,13 @@ __global__ __launch_bounds__(THREADS) void k_scan(Work w, int lev) {
 // segment's splitter tree is fetched a tile ahead.  All LDS that a tile's
 // first phase writes is kept twice, so that no barrier closes the loop (one
 // tree only where two do not fit, with its load and a barrier exposed).
-template <typename K, bool F32, bool SRC_IN, bool PAY, int THREADS, int ITEMS>
+// With TILED, an input tile's keys are classified by a TileTree.  That form is
+// a kernel of its own because a branch on it in the loop costs other inputs
+// 3 % of the launch, and is launched beside the ordinary one (`both`): the one
+// that does not suit the tree returns at once.
+template <typename K, bool F32, bool SRC_IN, bool PAY, int THREADS, int ITEMS, bool TILED = false>
 __global__ __launch_bounds__(THREADS) void k_split(Work w, int lev, const K* in_keys, const uint32_t* in_pay,
-                                                   int src_buf, int dst_buf) {
+                                                   int src_buf, int dst_buf, int both) {
   using View = BufView<K, PAY>;
   constexpr uint32_t TILE = THREADS * ITEMS;
   constexpr int W = View::W;
@@ -751,11 +810,14 @@ __global__ __launch_bounds__(THREADS) void k_split(Work w, int lev, const K* in_
   constexpr int TREES = SRC_IN || W < 4 ? 2 : 1;
   __shared__ K tk[TREES][2 * kMaxK];
   __shared__ uint32_t ti[TREES][kMaxK];
+  __shared__ K tile_tree[TILED ? kMaxK : 1];
+  __shared__ uint32_t tile_flags[2];
   __shared__ uint32_t hist[2][kMaxK];
   __shared__ uint32_t tmp[THREADS / kWave + 1];
   __shared__ Map map[MAPS];
   __shared__ __align__(16) uint32_t stage[TILE * W];
 
+  if (SRC_IN && both && (w.ctl->l0_repeats != 0) != TILED) return;
   const int cur = lev & 1;
   const uint32_t m = (uint32_t)min((uint64_t)w.ctl->big_count[cur], w.big_max);
   const uint32_t G = w.ctl->tiles[cur];
@@ -835,6 +897,17 @@ __global__ __launch_bounds__(THREADS) void k_split(Work w, int lev, const K* in_
   TreePart<K> tree;
   tree.fetch(w, s, bs.logk, t);
   tree.store(bs.logk, t, tk[0], ti[0]);
+  if constexpr (TILED) {
+    if (t < 2) tile_flags[t] = 0;
+    __syncthreads();
+  }
+  auto tile_thresholds = [&](uint32_t tl, int at) {
+    const uint32_t p0 = (uint32_t)(bs.start - bs.ubase) + tl * TILE;
+    if (t < kMaxK)
+      TileTree<K>::set(tk[0], ti[0], bs.logk, t, p0, p0 + min(TILE, bs.len - tl * TILE) - 1u, tile_tree,
+                       &tile_flags[at]);
+  };
+  if constexpr (TILED) tile_thresholds(g - bs.tb, 0);
   int par = 0, tp = 0;
   if constexpr (!SRC_IN) {
     const Run r = run_of(bs, uniform(w.tile_run[g]));
@@ -890,7 +963,11 @@ __global__ __launch_bounds__(THREADS) void k_split(Work w, int lev, const K* in_
       for (int i = 0; i < ITEMS; i++) key[i] = ord_of<K, F32>(key[i]);
     }
     uint32_t pos[ITEMS];  // bucket, then place in the staged tile
-    classify_batch<K, ITEMS>(tk[tp], ti[tp], bs.logk, key, valid, [&](int i) -> uint32_t { return idx[i]; }, pos, pairs);
+    if (TILED && tile_flags[par] == TileTree<K>::kBuilt)  // uniform
+      classify_tile<K, ITEMS>(tile_tree, bs.logk, key, pos);
+    else
+      classify_batch<K, ITEMS>(tk[tp], ti[tp], bs.logk, key, valid, [&](int i) -> uint32_t { return idx[i]; }, pos,
+                               pairs);
     // rank inside (tile, bucket): one LDS atomic per element; where the
     // wave's first 64 elements all fall into one bucket (skewed inputs), it
     // looks for one bucket among each 64 and takes one atomic for them.  A
@@ -939,6 +1016,10 @@ __global__ __launch_bounds__(THREADS) void k_split(Work w, int lev, const K* in_
     if (m > 1) b2 = w.big[cur][s2];
     if (TREES == 2 && new_tree) tree.store(bn.logk, t, tk[(tp ^ 1) & (TREES - 1)], ti[(tp ^ 1) & (TREES - 1)]);
     __syncthreads();
+    if constexpr (TILED) {  // every wave has classified this tile
+      if (more) tile_thresholds(gn - bs.tb, par ^ 1);
+      if (t == 0) tile_flags[par] = 0;  // (for the tile after the next)
+    }
     // exclusive scan of the tile histogram -> tile-local bucket starts
     const uint32_t hv = t < (int)kk ? h[t] : 0u;
     const uint32_t inc = wave_incl_scan_dpp(hv);
@@ -1332,15 +1413,21 @@ static int enqueue_typed(const void* keys_in, const uint32_t* pay_in, const uint
     if (w.tile_log2 == 12) {
       const uint32_t g = std::max<uint32_t>(8u, grid_for(w.tiles_max, 2) & ~7u);
       if (lev == 0)
-        RS_LAUNCH((k_split<K, F32, true, PAY, 512, 8>), g, 512, st, w, (int)lev, kin, pay_in, src, dst);
+        RS_LAUNCH((k_split<K, F32, true, PAY, 512, 8>), g, 512, st, w, (int)lev, kin, pay_in, src, dst, 0);
       else
-        RS_LAUNCH((k_split<K, false, false, PAY, 512, 8>), g, 512, st, w, (int)lev, kin, pay_in, src, dst);
+        RS_LAUNCH((k_split<K, false, false, PAY, 512, 8>), g, 512, st, w, (int)lev, kin, pay_in, src, dst, 0);
     } else {
       const uint32_t g = std::max<uint32_t>(8u, grid_for(w.tiles_max, 1) & ~7u);
-      if (lev == 0)
-        RS_LAUNCH((k_split<K, F32, true, PAY, 1024, 8>), g, 1024, st, w, (int)lev, kin, pay_in, src, dst);
-      else
-        RS_LAUNCH((k_split<K, false, false, PAY, 1024, 8>), g, 1024, st, w, (int)lev, kin, pay_in, src, dst);
+      if (lev == 0) {
+        const int both = !PAY && seg_off == nullptr && n >= kTiledMin;
+        RS_LAUNCH((k_split<K, F32, true, PAY, 1024, 8>), g, 1024, st, w, (int)lev, kin, pay_in, src, dst, both);
+        if constexpr (!PAY) {
+          if (both)
+            RS_LAUNCH((k_split<K, F32, true, false, 1024, 8, true>), g, 1024, st, w, (int)lev, kin, nullptr, src, dst,
+                      1);
+        }
+      } else
+        RS_LAUNCH((k_split<K, false, false, PAY, 1024, 8>), g, 1024, st, w, (int)lev, kin, pay_in, src, dst, 0);
     }
     if (w.count_max > 1ull << 21)
       RS_LAUNCH(k_scan<1024>, grid_for(w.count_max / (1024 * kScanItems) + 1, 2), 1024, st, w, (int)lev);

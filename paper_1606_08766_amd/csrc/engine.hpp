@@ -66,6 +66,7 @@ struct Ctl {
   uint64_t class_keys[kNumClasses];  // keys routed to each size class
   // diagnostics of level 0, segment 0
   uint32_t l0_k;
+  uint32_t l0_repeats;  // the level-0 splitters repeat keys (looked at from kTiledMin keys on)
   uint32_t direct_rare;            // 1: a direct plain call's input is left to the merge sort
   uint64_t l0_spl_key[kMaxK];      // ordinal keys, sorted
   uint32_t l0_spl_pos[kMaxK];

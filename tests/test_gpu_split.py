@@ -83,3 +83,30 @@ def test_routing_of_many_segments(m, wide):
         ko, po, plo, _ = gpu_segmented(keys, off, pay)
     ek, ep, epl = O.segmented(keys, off, pay)
     assert same_bits(ko, ek) and np.array_equal(po, ep) and np.array_equal(plo, epl)
+
+
+@pytest.mark.parametrize("kt,n,values", [("u64", (1 << 20) + 77, 2), ("f32", (1 << 24) + 8191, 300),
+                                         ("u64", (1 << 27) - 1, 5), ("u64", 1 << 27, 5), ("u64", (1 << 27) + 8191, 1),
+                                         ("u32", (1 << 27) + 1, 2), ("f32", (1 << 27) + 8193, 300)])
+def test_equal_splitters_of_all_values(kt, n, values):
+    """Few distinct keys, the lowest and the highest bit pattern among them:
+    equal splitters, their positions before, inside and after the tiles, below
+    and above the size from which the tiles get thresholds of their own."""
+    rng = np.random.default_rng(values)
+    ut = np.uint64 if kt == "u64" else np.uint32
+    top = np.iinfo(ut).max
+    v = np.concatenate([np.array([top, 0, top - 1, 1], dtype=ut), rng.integers(0, top, 296, dtype=ut)])[:values]
+    x = v[rng.integers(0, values, n, dtype=np.uint32)]
+    _check(x.view(np.float32) if kt == "f32" else x, threads=16)
+
+
+@pytest.mark.parametrize("kt", ["u64", "u32"])
+def test_equal_splitters_of_several_segments(kt):
+    """The same with a payload and a change of segments between tiles."""
+    sizes = np.array([700000, 13000, 90000, 300, 1500000, 14000, 14001], dtype=np.uint64)
+    keys, pay, off = gen.segmented(kt, sizes, ["zero", "deterdupl", "uniform", "zero", "deterdupl", "zero", "zero"],
+                                   seed=23)
+    keys[int(off[0]):int(off[1]):3] = np.iinfo(keys.dtype).max
+    ko, po, plo, _ = gpu_segmented(keys, off, pay)
+    ek, ep, epl = O.segmented(keys, off, pay)
+    assert same_bits(ko, ek) and np.array_equal(po, ep) and np.array_equal(plo, epl)
