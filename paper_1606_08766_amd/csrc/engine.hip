@@ -1203,6 +1203,15 @@ static uint32_t tile_log2_for(uint64_t n, const Tuning& t) {
   return (t.tile_log2 == 12 || n < (uint64_t)num_cu_cached() * 4 << 13) ? 12u : 13u;
 }
 
+// The class that takes every bucket of a single-level plain sort of few
+// buckets: the first that holds cap, at most that of 8192 (what is longer goes
+// to the next).
+static int few_class(uint32_t cap) {
+  int c = 0;
+  while (c < 7 && h_class_max[c] < cap) c++;
+  return c;
+}
+
 // Workspace layout: returns total bytes; fills w (pointers relative to base).
 size_t layout(int kt, uint64_t n, uint32_t num_segs, bool pay, const Tuning& t, char* base, Work* w,
               uint32_t* levels_out) {
@@ -1247,9 +1256,13 @@ size_t layout(int kt, uint64_t n, uint32_t num_segs, bool pay, const Tuning& t, 
     const uint64_t lo = c == 0 ? 0 : h_class_max[c - 1];
     uint64_t bound = n / (lo + 1) + 1;
     if (c == kNumClasses - 1) bound = n / (std::min<uint64_t>(cap, 64) + 1) + 1;
-    // a single-level plain sort may route all its (at most kMaxK) buckets to
-    // the class of 8192 and the one above it
-    cls_cap[c] = std::min<uint64_t>(final_max, std::max<uint64_t>(bound, c >= 7 ? kMaxK + 1 : 0));
+    // a single-level plain sort of few buckets routes all of them (at most
+    // kMaxK, however short) to few_class(cap).  Plain sorts that leave out the
+    // classes below 2048 fill no list beyond its bound: a split segment has at
+    // most 2 len / target <= len / 2048 buckets, and with those of the levels
+    // above (512 at most of the first, 512 for each of the second) they are
+    // fewer than n / 1025.
+    cls_cap[c] = std::min<uint64_t>(final_max, std::max<uint64_t>(bound, c >= few_class(cap) ? kMaxK + 1 : 0));
     o_cls[c] = take(cls_cap[c] * sizeof(FinalSeg));
   }
   const uint64_t nb = (levels || t.force_fallback) ? n : 0;
@@ -1355,7 +1368,7 @@ static int enqueue_typed(const void* keys_in, const uint32_t* pay_in, const uint
   uint32_t cmin = 0;
   const bool few = !seg_off && levels == 1 && n <= (uint64_t)target * 2 * num_cu();
   if (few) {
-    while (cmin < 7 && h_class_max[cmin] < cap) cmin++;
+    cmin = (uint32_t)few_class(cap);
   } else if (!seg_off && levels > 0 && target >= 4096 && t.rfis_max <= 64 && t.rquick_max <= 64) {
     cmin = 3;
   }
