@@ -154,7 +154,10 @@ __global__ void k_reset(Ctl* ctl, uint32_t levels) {
   for (uint32_t i = threadIdx.x; i < nw; i += blockDim.x) p[i] = (i == 1) ? levels : 0u;
 }
 
-// Route every user segment: split it (big list 0) or sort it directly.
+// Route every user segment: split it (big list 0) or sort it directly.  With
+// bad offsets (status -1) no segment is split: overlapping ones would take more
+// tiles and matrix entries than the workspace has room for.  The last workgroup
+// to come through sees the status of all.
 __global__ void k_init(Work w, const uint64_t* seg_off, uint32_t num_segs, uint64_t n_total, uint32_t cap,
                        uint32_t target, uint32_t levels, uint32_t ff, uint32_t cmin) {
   __shared__ RouteLds L;
@@ -169,7 +172,7 @@ __global__ void k_init(Work w, const uint64_t* seg_off, uint32_t num_segs, uint6
       b = seg_off ? seg_off[s + 1] : n_total;
       if (b < a || b > n_total || (s == 0 && a != 0) || (s + 1 == num_segs && b != n_total) ||
           b - a >= 0xFFFFFFFFull) {
-        set_status(w.ctl, -1);
+        atomicExch(&w.ctl->status, -1);  // (whatever else was found)
         active = false;
       }
     }
@@ -177,6 +180,14 @@ __global__ void k_init(Work w, const uint64_t* seg_off, uint32_t num_segs, uint6
     active = active && len > 0;
     route(w, L, 0, active, len > cap && levels > 0, FinalSeg{a, 0ull, len, 0u, 0u, 0u}, a, cap, ff, target, levels,
           cmin);
+  }
+  __threadfence();  // the workgroup's status and counts, before it is counted
+  __syncthreads();
+  if (threadIdx.x != 0 || atomicAdd(&w.ctl->init_done, 1u) + 1u != gridDim.x) return;
+  if (atomicAdd(&w.ctl->status, 0) != 0) {
+    atomicExch(&w.ctl->big_count[0], 0u);
+    atomicExch(&w.ctl->tiles[0], 0u);
+    atomicExch(&w.ctl->entries[0], 0u);
   }
 }
 

@@ -68,6 +68,7 @@ struct Ctl {
   uint32_t l0_k;
   uint32_t l0_repeats;  // the level-0 splitters repeat keys (looked at from kTiledMin keys on)
   uint32_t direct_rare;            // 1: a direct plain call's input is left to the merge sort
+  uint32_t init_done;              // workgroups of k_init that are through
   uint64_t l0_spl_key[kMaxK];      // ordinal keys, sorted
   uint32_t l0_spl_pos[kMaxK];
   uint32_t l0_bucket[kMaxK];
