@@ -1170,6 +1170,7 @@ __global__ void k_flush(Ctl* ctl) {
     ctl->class_done[threadIdx.x] += ctl->class_count[threadIdx.x];
     ctl->class_count[threadIdx.x] = 0;
   }
+  if (threadIdx.x < 2) ctl->pairs_in[threadIdx.x] = 0;
 }
 
 // ===========================================================================

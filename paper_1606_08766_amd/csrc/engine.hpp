@@ -58,7 +58,7 @@ struct Ctl {
   uint32_t tiles[2];               // tiles and matrix entries of the levels (ping-pong, as big_count)
   uint32_t entries[2];
   uint32_t scan_next;              // next chunk of the run lengths to scan (chained scan)
-  uint32_t rare_done;              // workgroups of k_local_rare that are through (if there are oversize segments)
+  uint32_t pairs_in[2];            // 1: a segment of buffer A, B was handed to k_local_rare
   uint32_t class_done[kNumClasses];   // final segments already sorted before a later level (three levels or more)
   uint32_t class_count[kNumClasses];  // final segments per size class (last = oversize)
   uint32_t level_max[kMaxLevels];  // largest bucket created per level
@@ -162,8 +162,31 @@ __device__ __forceinline__ uint32_t locate(const Work& w, int m, uint32_t col, u
   return (lo << w.tile_log2) + (w.runs[m][col + lo] >> 16) + (j - (o[lo] - o0));
 }
 
-// Reads a final segment element by element (the rare paths and the sorts of
-// small classes).
+// The same for N elements of a bucket of nt runs: all of a step's loads go out
+// before any is used.
+template <int N>
+__device__ __forceinline__ void locate_all(const Work& w, int m, uint32_t col, uint32_t nt, const uint32_t (&j)[N],
+                                           uint32_t (&place)[N]) {
+  const uint32_t *o = w.offs[m] + col, *r = w.runs[m] + col, o0 = o[0];
+  uint32_t lo[N];
+#pragma unroll
+  for (int i = 0; i < N; i++) lo[i] = 0;
+#pragma unroll 1
+  for (uint32_t n = nt; n > 1;) {
+    const uint32_t half = n >> 1;
+    uint32_t x[N];
+#pragma unroll
+    for (int i = 0; i < N; i++) x[i] = o[lo[i] + half];
+#pragma unroll
+    for (int i = 0; i < N; i++) lo[i] += x[i] - o0 <= j[i] ? half : 0u;
+    n -= half;
+  }
+#pragma unroll
+  for (int i = 0; i < N; i++) place[i] = (lo[i] << w.tile_log2) + (r[lo[i]] >> 16) + (j[i] - (o[lo[i]] - o0));
+}
+
+// Reads a final segment by elements (the rare paths and the sorts of small
+// classes).
 template <typename K, bool F32, bool PAY>
 struct SegReader {
   const Work& w;
@@ -185,6 +208,27 @@ struct SegReader {
   __device__ __forceinline__ uint32_t pay(uint32_t j) const {
     if constexpr (!PAY) return 0u;
     return (f.src & 0xFFu) ? BufView<K, PAY>{w.buf_rec[(f.src & 0xFFu) - 1]}.pay(at(j)) : in_pay[f.start + j];
+  }
+  // N elements at a time, payloads included; every j is below f.len.
+  template <int N>
+  __device__ __forceinline__ void get_all(const uint32_t (&j)[N], K (&k)[N], uint32_t (&v)[N], uint32_t (&y)[N]) const {
+    if (f.src & 0xFFu) {  // uniform
+      const int m = (int)(f.src & 0xFFu) - 1;
+      uint32_t place[N];
+      locate_all<N>(w, m, f.col, f.nt, j, place);
+      const BufView<K, PAY> bv{w.buf_rec[m]};
+#pragma unroll
+      for (int i = 0; i < N; i++) bv.get(f.pstart + place[i], k[i], v[i], y[i]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < N; i++) {
+        k[i] = in_keys[f.start + j[i]];
+        v[i] = j[i];
+        if constexpr (PAY) y[i] = in_pay[f.start + j[i]];
+      }
+#pragma unroll
+      for (int i = 0; i < N; i++) k[i] = ord_of<K, F32>(k[i]);
+    }
   }
 };
 

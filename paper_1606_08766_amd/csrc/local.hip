@@ -17,28 +17,27 @@ static inline uint32_t grid_for(uint64_t work, uint32_t per_cu) {
 }
 
 // ---------------------------------------------------------------------------
-// One segment sorted in LDS as (key, position) pairs by the merge sort: exact
-// for every input, whatever its keys.  len <= THREADS * ITEMS.  Called by
-// every thread of the block; ends with a barrier.
+// The stretch [c0, c0 + cnt) of a segment sorted in LDS as (key, position)
+// pairs by the merge sort: exact for every input, whatever its keys.  cnt <=
+// THREADS * ITEMS.  Rank r ends at place lpad(r) of sa, its payload in sa.p.
+// Called by every thread of the block; ends with a barrier.
 template <typename K, bool F32, bool PAY, int THREADS, int ITEMS>
-__device__ __forceinline__ void sort_pairs(const Work& w, const FinalSeg& f, const LdsArr<K>& sa, const K* in_keys,
-                                           const uint32_t* in_pay, K* keys_out, uint32_t* perm_out,
-                                           uint32_t* pay_out) {
-  const SegReader<K, F32, PAY> rd{w, f, in_keys, in_pay};
+__device__ __forceinline__ void sort_stretch(const SegReader<K, F32, PAY>& rd, uint32_t c0, uint32_t cnt,
+                                             const LdsArr<K>& sa) {
   K k[ITEMS];
-  uint32_t v[ITEMS], p[ITEMS];
+  uint32_t v[ITEMS], p[ITEMS], j[ITEMS];
+  // thread t takes logical elements t*ITEMS+i; load striped for coalescing
+  // and let the first sort round place them (any input order is valid).
+#pragma unroll
+  for (int i = 0; i < ITEMS; i++) j[i] = c0 + min((uint32_t)(i * THREADS) + threadIdx.x, cnt - 1);
+  rd.get_all(j, k, v, p);
 #pragma unroll
   for (int i = 0; i < ITEMS; i++) {
-    // thread t takes logical elements t*ITEMS+i; load striped for coalescing
-    // and let the first sort round place them (any input order is valid).
-    const uint32_t j = i * THREADS + threadIdx.x;
-    k[i] = KMax<K>::v;
-    v[i] = j < f.len ? j : kPadIdx;
-    p[i] = j;
+    if (i * THREADS + threadIdx.x >= cnt) {
+      k[i] = KMax<K>::v;
+      v[i] = kPadIdx;
+    }
   }
-#pragma unroll
-  for (int i = 0; i < ITEMS; i++)
-    if (i * THREADS + threadIdx.x < f.len) rd.get(i * THREADS + threadIdx.x, k[i], v[i]);
   lds_merge_sort<K, THREADS, ITEMS, PAY>(k, v, p, sa);
 #pragma unroll
   for (int i = 0; i < ITEMS; i++) {
@@ -47,31 +46,20 @@ __device__ __forceinline__ void sort_pairs(const Work& w, const FinalSeg& f, con
     if constexpr (PAY) sa.p[q] = p[i];
   }
   __syncthreads();
-  if constexpr (PAY) {
-    // the payloads are gathered before any output store (a load issued
-    // after stores waits for them)
-    uint32_t pv[ITEMS];
-#pragma unroll
-    for (int i = 0; i < ITEMS; i++) {
-      const uint32_t j = i * THREADS + threadIdx.x;
-      pv[i] = j < f.len ? rd.pay(sa.p[lpad(j)]) : 0u;
-    }
-#pragma unroll
-    for (int i = 0; i < ITEMS; i++) {
-      const uint32_t j = i * THREADS + threadIdx.x;
-      if (j < f.len) {
-        const int q = lpad(j);
-        keys_out[f.start + j] = to_output<K, F32>(sa.key(q));
-        if (perm_out) perm_out[f.start + j] = sa.v[q];
-        pay_out[f.start + j] = pv[i];
-      }
-    }
-  } else {
-    for (uint32_t j = threadIdx.x; j < f.len; j += THREADS) {
-      const int q = lpad(j);
-      keys_out[f.start + j] = to_output<K, F32>(sa.key(q));
-      if (perm_out) perm_out[f.start + j] = sa.v[q];
-    }
+}
+
+// A whole segment so, and to the output.
+template <typename K, bool F32, bool PAY, int THREADS, int ITEMS>
+__device__ __forceinline__ void sort_pairs(const Work& w, const FinalSeg& f, const LdsArr<K>& sa, const K* in_keys,
+                                           const uint32_t* in_pay, K* keys_out, uint32_t* perm_out,
+                                           uint32_t* pay_out) {
+  const SegReader<K, F32, PAY> rd{w, f, in_keys, in_pay};
+  sort_stretch<K, F32, PAY, THREADS, ITEMS>(rd, 0, f.len, sa);
+  for (uint32_t j = threadIdx.x; j < f.len; j += THREADS) {
+    const int q = lpad(j);
+    keys_out[f.start + j] = to_output<K, F32>(sa.key(q));
+    if (perm_out) perm_out[f.start + j] = sa.v[q];
+    if constexpr (PAY) pay_out[f.start + j] = sa.p[q];
   }
   __syncthreads();
 }
@@ -382,7 +370,10 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
     const bool rare = bins_scan<THREADS, BPT>(bin, len, s_tmp, t) > kRankBudget * len;  // uniform
     if (rare) {
       if constexpr (!DIRECT) {
-        if (t == 0) seg_at(q)->src = src | kPairsFlag;
+        if (t == 0) {
+          seg_at(q)->src = src | kPairsFlag;
+          if (src) w.ctl->pairs_in[src - 1] = 1;
+        }
       } else if constexpr (N > kDirectPairs) {
         if (t == 0) w.ctl->direct_rare = 1;
       } else {
@@ -507,98 +498,72 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
 }
 
 // ---------------------------------------------------------------------------
-// Fallback for final segments longer than cap (the balance guarantee of the
-// sampling holds only with high probability): bottom-up merge sort through
-// global memory by one workgroup, for one segment after the other.  First
-// chunks of every segment are gathered, sorted and written to the segment's own
-// range of the buffer that does not hold its level's elements (which no final
-// segment needs any more), then the chunks are merged, ping-ponging between
-// the buffers over that range.  Slow, exact, rare.
-// sk, sv, sp: LDS arrays of THREADS * ITEMS values (sp: payload calls only).
+// Fallback for a final segment longer than cap (the balance guarantee of the
+// sampling holds only with high probability): one workgroup sorts chunks of C
+// elements in LDS into the segment's own range of the buffer that does not hold
+// its level's elements, and then finds every element's rank by a binary search
+// in each other chunk and writes it out.  Nothing else reads or writes that
+// range, so that segments are independent of each other, unless segments of
+// that buffer were handed over (they may be read at the same time): then a
+// sorted chunk takes the places its elements had in their own buffer, which
+// costs a search for every place.  A segment seldom has more than two chunks;
+// the searches (a chain of dependent loads) run for U elements at a time.
 template <typename K, bool F32, bool PAY, int THREADS, int ITEMS>
-__device__ __forceinline__ void sort_oversize(const Work& w, const K* in_keys, const uint32_t* in_pay, K* keys_out,
-                                              uint32_t* perm_out, uint32_t* pay_out, K* sk, uint32_t* sv,
-                                              uint32_t* sp) {
-  constexpr int C = THREADS * ITEMS;
+__device__ __forceinline__ void sort_oversize(const Work& w, const FinalSeg& f, const LdsArr<K>& sa, const K* in_keys,
+                                              const uint32_t* in_pay, K* keys_out, uint32_t* perm_out,
+                                              uint32_t* pay_out) {
   using View = BufView<K, PAY>;
-  const int cls = kNumClasses - 1;
-  const uint32_t cnt = (uint32_t)min((uint64_t)w.ctl->class_count[cls], w.cls_cap[cls]);
-  for (uint32_t q = 0; q < cnt; q++) {
-    const FinalSeg f = w.cls[cls][q];
-    const SegReader<K, F32, PAY> rd{w, f, in_keys, in_pay};
-    const View db{w.buf_rec[f.src == 0 ? 0 : ((int)f.src - 1) ^ 1]};
-    for (uint32_t c0 = 0; c0 < f.len; c0 += C) {
-      K k[ITEMS];
-      uint32_t v[ITEMS], p[ITEMS];
-#pragma unroll
-      for (int i = 0; i < ITEMS; i++) {
-        const uint32_t j = c0 + threadIdx.x * ITEMS + i;
-        k[i] = KMax<K>::v;
-        v[i] = kPadIdx;
-        p[i] = 0;
-        if (j < f.len) {
-          rd.get(j, k[i], v[i]);
-          if constexpr (PAY) p[i] = rd.pay(j);
-        }
-      }
-      block_merge_sort<K, THREADS, ITEMS, PAY>(k, v, p, sk, sv, sp);
-#pragma unroll
-      for (int i = 0; i < ITEMS; i++) {
-        const uint32_t j = c0 + threadIdx.x * ITEMS + i;
-        if (j < f.len) db.put(f.start + j, k[i], v[i], p[i]);
-      }
-      __syncthreads();
-    }
-  }
-  for (uint32_t q = 0; q < cnt; q++) {
-    const FinalSeg f = w.cls[cls][q];
-    int cur = f.src == 0 ? 0 : ((int)f.src - 1) ^ 1;
-    // merge passes
-    for (uint32_t run = C; run < f.len; run <<= 1) {
-      const View ab{w.buf_rec[cur] + f.start * View::W};
-      const View db{w.buf_rec[cur ^ 1] + f.start * View::W};
-      for (uint32_t o0 = 0; o0 < f.len; o0 += THREADS) {
-        const uint32_t o = o0 + threadIdx.x;  // output position handled by this thread
-        if (o < f.len) {
-          const uint32_t first = o / (2 * run) * (2 * run);
-          const uint32_t alen = min(run, f.len - first);
-          const uint32_t b0 = first + alen;
-          const uint32_t blen = b0 < f.len ? min(run, f.len - b0) : 0u;
-          const uint32_t d = o - first;
-          // number of A elements among the first d outputs (ties prefer A)
-          uint32_t lo = d > blen ? d - blen : 0u, hi = d < alen ? d : alen;
-          while (lo < hi) {
-            const uint32_t mid = (lo + hi) >> 1;
-            const uint32_t bj = b0 + d - 1 - mid;
-            if (pair_less(ab.key(bj), ab.idx(bj), ab.key(first + mid), ab.idx(first + mid)))
-              hi = mid;
-            else
-              lo = mid + 1;
-          }
-          const uint32_t ai = lo, bi = d - lo;
-          bool takeA;
-          if (ai >= alen)
-            takeA = false;
-          else if (bi >= blen)
-            takeA = true;
-          else
-            takeA = !pair_less(ab.key(b0 + bi), ab.idx(b0 + bi), ab.key(first + ai), ab.idx(first + ai));
-          const uint32_t sidx = takeA ? first + ai : b0 + bi;
-          db.put(o, ab.key(sidx), ab.idx(sidx), ab.pay(sidx));
-        }
-      }
-      __syncthreads();
-      cur ^= 1;
-    }
-    // output
-    const View rb{w.buf_rec[cur] + f.start * View::W};
-    for (uint32_t j = threadIdx.x; j < f.len; j += THREADS) {
-      keys_out[f.start + j] = to_output<K, F32>(rb.key(j));
-      if (perm_out) perm_out[f.start + j] = rb.idx(j);
-      if constexpr (PAY) pay_out[f.start + j] = rb.pay(j);
+  constexpr uint32_t C = THREADS * ITEMS;
+  const SegReader<K, F32, PAY> rd{w, f, in_keys, in_pay};
+  const bool own = f.src && uniform(w.ctl->pairs_in[(f.src - 1) ^ 1]) != 0;  // uniform
+  const View b{w.buf_rec[f.src == 0 ? 0u : own ? f.src - 1 : (f.src - 1) ^ 1]};
+  auto at = [&](uint32_t q) -> uint64_t { return own ? rd.at(q) : f.start + q; };
+  for (uint32_t c0 = 0; c0 < f.len; c0 += C) {
+    const uint32_t cnt = min(C, f.len - c0);
+    sort_stretch<K, F32, PAY, THREADS, ITEMS>(rd, c0, cnt, sa);
+    for (uint32_t j = threadIdx.x; j < cnt; j += THREADS) {
+      const int q = lpad(j);
+      b.put(at(c0 + j), sa.key(q), sa.v[q], PAY ? sa.p[q] : 0u);
     }
     __syncthreads();
   }
+  constexpr int U = 4;
+  for (uint32_t j0 = threadIdx.x; j0 < f.len; j0 += THREADS * U) {
+    K k[U];
+    uint32_t v[U], y[U], rank[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) b.get(at(min(j0 + u * THREADS, f.len - 1)), k[u], v[u], y[u]);
+#pragma unroll
+    for (int u = 0; u < U; u++) rank[u] = (j0 + u * THREADS) % C;
+#pragma unroll 1
+    for (uint32_t c0 = 0; c0 < f.len; c0 += C) {
+      // elements of the chunk below each: the first lo are, those from lo + n on are not
+      uint32_t lo[U];
+#pragma unroll
+      for (int u = 0; u < U; u++) lo[u] = 0;
+#pragma unroll 1
+      for (uint32_t n = min(C, f.len - c0); n > 0;) {
+        const uint32_t half = n >> 1;
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+          const uint64_t q = at(c0 + lo[u] + half);
+          lo[u] += pair_less(b.key(q), b.idx(q), k[u], v[u]) ? n - half : 0u;
+        }
+        n = half;
+      }
+#pragma unroll
+      for (int u = 0; u < U; u++) rank[u] += (j0 + u * THREADS) / C * C == c0 ? 0u : lo[u];
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      if (j0 + u * THREADS < f.len) {
+        keys_out[f.start + rank[u]] = to_output<K, F32>(k[u]);
+        if (perm_out) perm_out[f.start + rank[u]] = v[u];
+        if constexpr (PAY) pay_out[f.start + rank[u]] = y[u];
+      }
+    }
+  }
+  __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
@@ -612,14 +577,12 @@ template <typename K, bool F32, bool PAY, int THREADS, int ITEMS>
 __global__ __launch_bounds__(THREADS) void k_local_rare(Work w, const K* in_keys, const uint32_t* in_pay, K* keys_out,
                                                         uint32_t* perm_out, uint32_t* pay_out, int direct) {
   constexpr int NP = lpad_size(THREADS * ITEMS);
-  constexpr int C = THREADS * 4;  // chunk of the oversize sort
-  __shared__ __align__(8) uint32_t s_lo[NP];
+  __shared__ uint32_t s_lo[NP];
   __shared__ uint32_t s_hi[sizeof(K) == 8 ? NP : 1];
   __shared__ uint32_t s_v[NP];
   __shared__ uint32_t s_p[PAY ? NP : 1];
   __shared__ uint32_t s_list[THREADS];
   __shared__ uint32_t s_n;
-  static_assert(C * sizeof(K) <= NP * 4, "the chunk's keys fit s_lo");
   const LdsArr<K> sa{s_lo, s_hi, s_v, s_p};
   if (direct) {  // a plain call's whole input
     if (w.ctl->direct_rare)
@@ -651,16 +614,16 @@ __global__ __launch_bounds__(THREADS) void k_local_rare(Work w, const K* in_keys
       __syncthreads();
     }
   }
-  // The oversize sort writes over the buffers, so it waits for every
-  // workgroup's segments: the last workgroup to come here does it.
-  if (w.ctl->class_count[kNumClasses - 1] == 0) return;  // uniform
-  __syncthreads();
-  if (threadIdx.x == 0) s_n = atomicAdd(&w.ctl->rare_done, 1u) + 1u;
-  __syncthreads();
-  if (s_n != gridDim.x) return;
-  if (threadIdx.x == 0) w.ctl->rare_done = 0;
-  sort_oversize<K, F32, PAY, THREADS, 4>(w, in_keys, in_pay, keys_out, perm_out, pay_out, reinterpret_cast<K*>(s_lo),
-                                         s_v, s_p);
+  // a workgroup per oversize segment (8e8 u32 keys, whose mean bucket is half the
+  // capacity: 13.6 ms; 225 when one workgroup took them all)
+  const uint32_t cnt = final_count(w, kNumClasses - 1);
+  for (uint32_t q = blockIdx.x; q < cnt; q += gridDim.x) {
+    const FinalSeg f = w.cls[kNumClasses - 1][q];
+    if (f.len <= THREADS * ITEMS)  // (the debug switch: smaller chunks, so that there are several)
+      sort_oversize<K, F32, PAY, THREADS, ITEMS / 4>(w, f, sa, in_keys, in_pay, keys_out, perm_out, pay_out);
+    else
+      sort_oversize<K, F32, PAY, THREADS, ITEMS>(w, f, sa, in_keys, in_pay, keys_out, perm_out, pay_out);
+  }
 }
 
 // A plain call that fits one workgroup.  Many threads with few elements each:
