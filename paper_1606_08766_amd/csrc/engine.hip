@@ -173,6 +173,7 @@ __global__ void k_init(Work w, const uint64_t* seg_off, uint32_t num_segs, uint6
       if (b < a || b > n_total || (s == 0 && a != 0) || (s + 1 == num_segs && b != n_total) ||
           b - a >= 0xFFFFFFFFull) {
         atomicExch(&w.ctl->status, -1);  // (whatever else was found)
+        __threadfence();                 // before the workgroup is counted below
         active = false;
       }
     }
@@ -181,8 +182,7 @@ __global__ void k_init(Work w, const uint64_t* seg_off, uint32_t num_segs, uint6
     route(w, L, 0, active, len > cap && levels > 0, FinalSeg{a, 0ull, len, 0u, 0u, 0u}, a, cap, ff, target, levels,
           cmin);
   }
-  __threadfence();  // the workgroup's status and counts, before it is counted
-  __syncthreads();
+  __syncthreads();  // (the counts' atomics have returned their values)
   if (threadIdx.x != 0 || atomicAdd(&w.ctl->init_done, 1u) + 1u != gridDim.x) return;
   if (atomicAdd(&w.ctl->status, 0) != 0) {
     atomicExch(&w.ctl->big_count[0], 0u);
