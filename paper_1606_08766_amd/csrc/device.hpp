@@ -128,7 +128,8 @@ __device__ __forceinline__ T block_excl_scan(T v, typename NoDeduce<T>::type* tm
 }
 
 // ---------------------------------------------------------------------------
-// Register sorting network (bitonic) on ITEMS (power of two) pairs, ascending.
+// Register sorting network on ITEMS pairs, ascending: bitonic, or odd-even
+// transposition if ITEMS is no power of two.
 // The compare-exchange swaps with a mask and XORs rather than selecting
 // between two array elements: a select of two array loads can be folded into
 // a load at a select-computed index, which keeps the arrays out of registers.
@@ -143,6 +144,20 @@ __device__ __forceinline__ void cx_swap(K& a, K& b, bool sw) {
 
 template <typename K, int ITEMS, bool CARRY>
 __device__ __forceinline__ void reg_sort_impl(K (&k)[ITEMS], uint32_t (&v)[ITEMS], uint32_t (&p)[ITEMS]) {
+  if constexpr ((ITEMS & (ITEMS - 1)) != 0) {
+#pragma unroll
+    for (int round = 0; round < ITEMS; round++) {
+#pragma unroll
+      for (int i = round & 1; i + 1 < ITEMS; i += 2) {
+        const bool sw = pair_less(k[i + 1], v[i + 1], k[i], v[i]);
+        cx_swap(k[i], k[i + 1], sw);
+        cx_swap(v[i], v[i + 1], sw);
+        if constexpr (CARRY) cx_swap(p[i], p[i + 1], sw);
+      }
+      __builtin_amdgcn_sched_barrier(0);  // (rounds one after the other: fewer registers)
+    }
+    return;
+  }
 #pragma unroll
   for (int size = 2; size <= ITEMS; size <<= 1) {
 #pragma unroll
@@ -260,7 +275,8 @@ __device__ __forceinline__ void block_merge_sort(K (&k)[ITEMS], uint32_t (&v)[IT
 // for u64 keys, position, optional carried value) with one pad word after
 // every 32 words: logical index i is stored at i + i/32.  In the merge rounds
 // lane t reads around logical index t * ITEMS / 2, and in the store phase at
-// t * ITEMS; with the pad both patterns spread a wave over all 32 banks.
+// t * ITEMS; with the pad both patterns spread a wave over all 32 banks.  ITEMS
+// need not be a power of two here.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int lpad(int i) { return i + (i >> 5); }
 __host__ __device__ constexpr int lpad_size(int n) { return n + (n >> 5) + 1; }
@@ -302,7 +318,7 @@ __device__ __forceinline__ void lds_merge_sort(K (&k)[ITEMS], uint32_t (&v)[ITEM
       if constexpr (CARRY) s.p[q] = p[i];
     }
     __syncthreads();
-    const int first = (t * ITEMS) & ~(2 * run - 1);
+    const int first = (t & ~(2 * (run / ITEMS) - 1)) * ITEMS;  // run / ITEMS is a power of two
     const int a0 = first, b0 = first + run;
     const int alen = (N - a0) < run ? (N - a0) : run;
     const int blen = (N - b0) <= 0 ? 0 : ((N - b0) < run ? (N - b0) : run);

@@ -45,7 +45,7 @@ struct FinalSeg {
   uint32_t len;
   uint32_t src;  // low byte: 0 caller input (positions implicit), 1 buffer A, 2 buffer B (and the
                  // matrices of the same number);
-                 // kPairsFlag: handed from the ranking in bins to the merge sort
+                 // kPairsFlag: handed from the ranking in bins to k_local_rare
   uint32_t col, nt;  // as in BigSeg
 };
 constexpr uint32_t kPairsFlag = 0x100;
@@ -67,7 +67,6 @@ struct Ctl {
   // diagnostics of level 0, segment 0
   uint32_t l0_k;
   uint32_t l0_repeats;  // the level-0 splitters repeat keys (looked at from kTiledMin keys on)
-  uint32_t direct_rare;            // 1: a direct plain call's input is left to the merge sort
   uint32_t init_done;              // workgroups of k_init that are through
   uint64_t l0_spl_key[kMaxK];      // ordinal keys, sorted
   uint32_t l0_spl_pos[kMaxK];
@@ -345,7 +344,6 @@ __device__ __forceinline__ FinalSeg final_at(const Work& w, int cls, uint32_t q)
 // and statistics of the workspace.
 __device__ __forceinline__ void direct_reset(const Work& w) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    w.ctl->direct_rare = 0;
     w.ctl->status = 0;
     w.ctl->levels = 0;
     w.ctl->l0_k = 0;

@@ -17,23 +17,17 @@ static inline uint32_t grid_for(uint64_t work, uint32_t per_cu) {
 }
 
 // ---------------------------------------------------------------------------
-// The stretch [c0, c0 + cnt) of a segment sorted in LDS as (key, position)
-// pairs by the merge sort: exact for every input, whatever its keys.  cnt <=
+// The merge sort of (key, position) pairs in LDS: exact for every input,
+// whatever its keys.  Thread t holds elements i * THREADS + t of len <=
 // THREADS * ITEMS.  Rank r ends at place lpad(r) of sa, its payload in sa.p.
 // Called by every thread of the block; ends with a barrier.
-template <typename K, bool F32, bool PAY, int THREADS, int ITEMS>
-__device__ __forceinline__ void sort_stretch(const SegReader<K, F32, PAY>& rd, uint32_t c0, uint32_t cnt,
-                                             const LdsArr<K>& sa) {
-  K k[ITEMS];
-  uint32_t v[ITEMS], p[ITEMS], j[ITEMS];
-  // thread t takes logical elements t*ITEMS+i; load striped for coalescing
-  // and let the first sort round place them (any input order is valid).
-#pragma unroll
-  for (int i = 0; i < ITEMS; i++) j[i] = c0 + min((uint32_t)(i * THREADS) + threadIdx.x, cnt - 1);
-  rd.get_all(j, k, v, p);
+template <typename K, bool PAY, int THREADS, int ITEMS>
+__device__ __forceinline__ void merge_pairs(K (&k)[ITEMS], uint32_t (&v)[ITEMS], uint32_t (&p)[ITEMS], uint32_t len,
+                                            const LdsArr<K>& sa) {
+  // (the sort takes its elements in any order)
 #pragma unroll
   for (int i = 0; i < ITEMS; i++) {
-    if (i * THREADS + threadIdx.x >= cnt) {
+    if (i * THREADS + threadIdx.x >= len) {
       k[i] = KMax<K>::v;
       v[i] = kPadIdx;
     }
@@ -48,18 +42,62 @@ __device__ __forceinline__ void sort_stretch(const SegReader<K, F32, PAY>& rd, u
   __syncthreads();
 }
 
-// A whole segment so, and to the output.
+// The stretch [c0, c0 + cnt) of a segment so.  A segment of at most THREADS runs
+// is read through a RunMap, built in the memory at map (looking 12288 elements
+// up one by one, 10 dependent loads each, takes as long as sorting them).
 template <typename K, bool F32, bool PAY, int THREADS, int ITEMS>
-__device__ __forceinline__ void sort_pairs(const Work& w, const FinalSeg& f, const LdsArr<K>& sa, const K* in_keys,
-                                           const uint32_t* in_pay, K* keys_out, uint32_t* perm_out,
-                                           uint32_t* pay_out) {
-  const SegReader<K, F32, PAY> rd{w, f, in_keys, in_pay};
-  sort_stretch<K, F32, PAY, THREADS, ITEMS>(rd, 0, f.len, sa);
-  for (uint32_t j = threadIdx.x; j < f.len; j += THREADS) {
+__device__ __forceinline__ void sort_stretch(const SegReader<K, F32, PAY>& rd, uint32_t c0, uint32_t cnt,
+                                             const LdsArr<K>& sa, void* map) {
+  K k[ITEMS];
+  uint32_t v[ITEMS], p[ITEMS];
+  const FinalSeg& f = rd.f;
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));  // (addresses are not kept from one segment to the next)
+  if (f.src && f.nt <= THREADS) {  // uniform
+    RunMap<THREADS, THREADS * ITEMS>& m = *reinterpret_cast<RunMap<THREADS, THREADS * ITEMS>*>(map);
+    const int s = (int)f.src - 1;
+    const uint32_t *o = rd.w.offs[s] + f.col, r = (uint32_t)t < f.nt ? rd.w.runs[s][f.col + t] : 0u;
+    const uint32_t ofs = (uint32_t)t < f.nt ? o[t] - o[0] : 0u;
+    uint64_t bal;
+    m.clear(t);
+    __syncthreads();
+    m.mark(t, t, f.nt, ofs, r & 0xFFFFu, c0, cnt, bal);
+    __syncthreads();
+    m.number(t, t, ofs, r >> 16, c0, rd.w.tile_log2, bal);
+    __syncthreads();
+    const BufView<K, PAY> bv{rd.w.buf_rec[s] + f.pstart * BufView<K, PAY>::W};
+    m.each(t, cnt, [&](int i, uint32_t d) { bv.get(d, k[i], v[i], p[i]); });
+  } else {
+    uint32_t j[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; i++) j[i] = c0 + min((uint32_t)(i * THREADS + t), cnt - 1);
+    rd.get_all(j, k, v, p);
+  }
+  merge_pairs<K, PAY, THREADS, ITEMS>(k, v, p, cnt, sa);
+}
+
+// The same in the smallest of four shapes that holds the stretch.
+template <typename K, bool F32, bool PAY, int THREADS, int ITEMS>
+__device__ __forceinline__ void sort_stretch_fit(const SegReader<K, F32, PAY>& rd, uint32_t c0, uint32_t cnt,
+                                                 const LdsArr<K>& sa, void* map) {
+  if (cnt <= THREADS)
+    sort_stretch<K, F32, PAY, THREADS, 1>(rd, c0, cnt, sa, map);
+  else if (cnt <= THREADS * ITEMS / 4)
+    sort_stretch<K, F32, PAY, THREADS, ITEMS / 4>(rd, c0, cnt, sa, map);
+  else if (cnt <= THREADS * ITEMS / 2)
+    sort_stretch<K, F32, PAY, THREADS, ITEMS / 2>(rd, c0, cnt, sa, map);
+  else
+    sort_stretch<K, F32, PAY, THREADS, ITEMS>(rd, c0, cnt, sa, map);
+}
+
+// len sorted elements to the output (start of the segment).
+template <typename K, bool F32, bool PAY, int THREADS>
+__device__ __forceinline__ void put_pairs(const LdsArr<K>& sa, uint32_t len, K* kout, uint32_t* pout, uint32_t* yout) {
+  for (uint32_t j = threadIdx.x; j < len; j += THREADS) {
     const int q = lpad(j);
-    keys_out[f.start + j] = to_output<K, F32>(sa.key(q));
-    if (perm_out) perm_out[f.start + j] = sa.v[q];
-    if constexpr (PAY) pay_out[f.start + j] = sa.p[q];
+    kout[j] = to_output<K, F32>(sa.key(q));
+    if (pout) pout[j] = sa.v[q];
+    if constexpr (PAY) yout[j] = sa.p[q];
   }
   __syncthreads();
 }
@@ -83,9 +121,27 @@ __device__ __forceinline__ void sort_pairs(const Work& w, const FinalSeg& f, con
 // Equal words of different elements (keys that differ in few low bits, or
 // equal keys near to each other) get equal ranks, which leaves the sum of all
 // ranks below len (len - 1) / 2: such a segment (uniform test) goes on with
-// the next 32 bits of (d, x) among its equals (rank_ties).  A segment whose
-// ranking would take more than kRankBudget compares per element (keys
-// clustered far apart) is marked kPairsFlag and left to k_local_rare.
+// the next 32 bits of (d, x) among its equals (rank_ties).
+//
+// A key that a part of a segment shares makes a long bin and a large group of
+// equal words.  Its elements lie in every wave, which then all loop as long as
+// the bin is; so from kRankOwn compares per element on, and among more than
+// kTiesOwn pairs of equals, a thread ranks the words at its places of the
+// sorted bins and not its own (2000 segments of 8000 u64 keys, 3 % of them 0:
+// 2010 -> 386 us; 4096 of 4096, 10 % of them 0: 2550 -> 386).  Where ranks are
+// few compares each, the own words are ranked: by place takes more barriers and
+// passes (2000 segments of 8000 gaussian u64 keys, 192 us, 206 with all equal
+// words by place).
+//
+// A segment whose ranking would take more than kRankBudget compares per element
+// or kRankTotal in all (most keys clustered far apart from others) is marked
+// kPairsFlag and left to the merge sort of k_local_rare.  Where LDS and
+// registers allow it, it is merge sorted on the spot instead: by the one-wave
+// workgroups (16384 rows of 256 f32 keys, as many of every magnitude, took 1115
+// us when handed over, 92 so) and for a plain call's only workgroup, which
+// gives up at half of kRankTotal if the words drop key bits, as every compare is
+// then made twice (12000 u64 keys in 300 clusters: 88 us ranked, 72 merge
+// sorted).
 //
 // Few distinct keys need no case of their own: d then has few bits and the
 // bins go on with the position.
@@ -94,7 +150,8 @@ __device__ __forceinline__ void sort_pairs(const Work& w, const FinalSeg& f, con
 // and HBM.  Hence 32-bit words computed once, one bin per element (few
 // compares), and element minima by their upper halves first.  LDS is 8 B per
 // element: words and bins share the memory of the staging area.
-constexpr uint32_t kRankBudget = 128;
+constexpr uint32_t kRankBudget = 128, kRankTotal = 1u << 19;  // compares: per element, in all
+constexpr uint32_t kRankOwn = 4, kTiesOwn = 1024;
 
 // Exclusive scan of the THREADS * BPT bin counts in place (bin is 16-byte
 // aligned, BPT a multiple of 4); returns the sum of their squares, uniformly.
@@ -135,11 +192,32 @@ __device__ __forceinline__ uint32_t bins_scan(uint32_t* bin, uint32_t len, uint3
   return cost;
 }
 
+// How many of a[0, n) are below v, U at a time (a[n, n + U - 1) may be read;
+// PAST: they are not below v either).
+template <bool PAST, int U>
+__device__ __forceinline__ uint32_t count_below(const uint32_t* a, uint32_t n, uint32_t v) {
+  uint32_t less = 0;
+#pragma unroll 1
+  for (uint32_t k = 0; k < n; k += U) {
+    uint32_t x[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) x[u] = a[k + u];
+#pragma unroll
+    for (int u = 0; u < U; u++) less += (x[u] < v) & (u == 0 || PAST || k + u < n) ? 1u : 0u;
+  }
+  return less;
+}
+
 // Ranks of a segment with equal words.  Elements of equal rank r are a group
 // of m that owns the ranks r .. r + m - 1; `rounds` times, the groups are
-// ordered by the next 32 bits limb(round, i).  fr and cnt hold N values each
-// and are free on entry and exit (a barrier on both sides).
-template <int THREADS, int ITEMS, typename LimbFn>
+// ordered by the next 32 bits limb(round, i), U values read at a time.  fr and
+// cnt hold N values each (fr: and 3 beyond) and are free on entry and exit (a
+// barrier on both sides).
+// BY_PLACE: a thread counts for the values at places i * THREADS + t instead
+// of for its own elements.  Neighbouring lanes are then in one group, loop
+// alike and read the same word, and a large group keeps only its own waves
+// busy (its elements lie in every wave), for two more barriers and passes.
+template <int THREADS, int ITEMS, int U, bool BY_PLACE, typename LimbFn>
 __device__ __forceinline__ void rank_ties(uint32_t* fr, uint32_t* cnt, uint32_t len, uint32_t (&rank)[ITEMS],
                                           int rounds, LimbFn limb, int t) {
 #pragma unroll 1
@@ -154,28 +232,88 @@ __device__ __forceinline__ void rank_ties(uint32_t* fr, uint32_t* cnt, uint32_t 
       if (t < (int)len - i * THREADS) pl[i] = atomicAdd(&cnt[rank[i]], 1u);
     }
     __syncthreads();
+    if constexpr (BY_PLACE) {
 #pragma unroll
-    for (int i = 0; i < ITEMS; i++)
-      if (t < (int)len - i * THREADS) fr[rank[i] + pl[i]] = limb(round, i);
-    __syncthreads();
+      for (int i = 0; i < ITEMS; i++)  // the group's size joins the place in it
+        if (t < (int)len - i * THREADS) pl[i] |= cnt[rank[i]] << 16;
+      __syncthreads();
 #pragma unroll
-    for (int i = 0; i < ITEMS; i++) {
-      if (t < (int)len - i * THREADS) {
-        const uint32_t m = cnt[rank[i]], v = limb(round, i), r0 = rank[i];
-#pragma unroll 1
-        for (uint32_t q = 0; m > 1 && q < m; q++) rank[i] += fr[r0 + q] < v ? 1u : 0u;
+      for (int i = 0; i < ITEMS; i++) {
+        if (t < (int)len - i * THREADS) {
+          const uint32_t p = rank[i] + (pl[i] & 0xFFFFu);
+          fr[p] = limb(round, i);
+          cnt[p] = (pl[i] & 0xFFFF0000u) | rank[i];
+          pl[i] = p;
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++) {
+        if (t < (int)len - i * THREADS) {
+          uint32_t* const c = cnt + i * THREADS + t;
+          const uint32_t g = *c, m = g >> 16;
+          *c = m > 1 ? count_below<false, U>(fr + (g & 0xFFFFu), m, fr[i * THREADS + t]) : 0u;
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++)
+        if (t < (int)len - i * THREADS) rank[i] += cnt[pl[i]];
+    } else {
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++)
+        if (t < (int)len - i * THREADS) fr[rank[i] + pl[i]] = limb(round, i);
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++) {
+        if (t < (int)len - i * THREADS) {
+          const uint32_t m = cnt[rank[i]];
+          if (m > 1) rank[i] += count_below<false, U>(fr + rank[i], m, limb(round, i));
+        }
       }
     }
     __syncthreads();
   }
 }
 
+// Ranks words in bins by place: on entry rank[i] is the place in the bin, on
+// exit the bin's start plus the smaller words in it.  Returns the sum of the
+// thread's ranks; a barrier must follow before fr is written.
+template <int THREADS, int ITEMS>
+__device__ __forceinline__ uint32_t rank_by_place(uint32_t* fr, const uint32_t* bin, uint32_t len,
+                                                  uint32_t (&wd)[ITEMS], int bsh, uint32_t (&rank)[ITEMS], int t) {
+#pragma unroll
+  for (int i = 0; i < ITEMS; i++) {
+    if (t < (int)len - i * THREADS) {
+      rank[i] += bin[wd[i] >> bsh];
+      fr[rank[i]] = wd[i];
+    }
+  }
+  if (t < 3) fr[len + t] = ~0u;
+  __syncthreads();
+  uint32_t sum = 0;
+#pragma unroll
+  for (int i = 0; i < ITEMS; i++) {
+    if (t < (int)len - i * THREADS) {
+      const uint32_t x = fr[i * THREADS + t], b = x >> bsh, s0 = bin[b];
+      wd[i] = s0 + count_below<true, 4>(fr + s0, bin[b + 1] - s0, x);
+      sum += wd[i];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < ITEMS; i++)
+    if (t < (int)len - i * THREADS) fr[i * THREADS + t] = wd[i];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < ITEMS; i++)
+    if (t < (int)len - i * THREADS) rank[i] = fr[rank[i]];
+  return sum;
+}
+
 // Sorts the final segments of the classes in a bit mask, the longest class
 // first.  DIRECT: the whole input [0, n) of a plain call instead, by one
-// workgroup, which also runs the merge sort if its bins are too crowded (up to
-// kDirectPairs elements, as LDS holds pairs; longer inputs are left to
-// k_local_rare through ctl->direct_rare).
-constexpr int kDirectPairs = 8192;
+// workgroup.
 template <typename K, bool F32, bool PAY, int THREADS, int ITEMS, int WPE, bool DIRECT = false>
 __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t classes, const K* in_keys,
                                                              const uint32_t* in_pay, K* keys_out, uint32_t* perm_out,
@@ -183,12 +321,14 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
   constexpr int N = THREADS * ITEMS;
   constexpr int LB = 31 - __builtin_clz((unsigned)N);  // 2^LB bins: one per element, or more than half
   constexpr int BPT = (1 << LB) / THREADS;
-  // words, then bins; the staging area of the output uses the same memory
-  constexpr int NP = lpad_size(N);
-  __shared__ __align__(16) uint32_t s_mem[DIRECT && N <= kDirectPairs ? 3 * NP : 2 * N + 8];
+  constexpr bool PAIRS = DIRECT || THREADS == kWave;  // crowded segments are merge sorted on the spot
+  constexpr int NP = lpad_size(N), KW = (int)(sizeof(K) / 4);
+  // words, then bins; the staging area of the output and the pairs use the same memory
+  constexpr int MEM = PAIRS ? (KW + 1 + (PAY ? 1 : 0)) * NP : 0;
+  __shared__ __align__(16) uint32_t s_mem[MEM > 2 * N + 8 ? MEM : 2 * N + 8];
   __shared__ uint32_t s_red[6 * (THREADS / kWave)];
   __shared__ uint32_t s_tmp[2 * (THREADS / kWave)];
-  __shared__ uint32_t s_sum;
+  __shared__ uint32_t s_sum, s_crowd;
   __shared__ RunMap<DIRECT ? kWave : THREADS, DIRECT ? kWave : N> map;  // of the next segment, if it lies in a buffer
   uint32_t* const fr = s_mem;           // N words, and 3 beyond
   uint32_t* const bin = s_mem + N + 4;  // 2^LB + 1 bins
@@ -306,6 +446,7 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
 #pragma unroll
     for (int b = 0; b < BPT / 4; b++) reinterpret_cast<uint4*>(bin)[b * THREADS + t] = make_uint4(0, 0, 0, 0);
     if (t == 0) s_sum = 0;
+    if (DIRECT && t == 0) s_crowd = 0;
     // bounds of the keys (64-bit keys: of their upper halves) and positions
     constexpr int KS = sizeof(K) == 8 ? 32 : 0;
     uint32_t hmn = ~0u, hmx = 0u, imn = ~0u, imx = 0u;
@@ -355,10 +496,22 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
       for (int i = 0; i < ITEMS; i++)
         wd[i] = ((rb ? (uint32_t)(key[i] - mn) : 0u) << (sl & 31)) | ((idx[i] - imn) >> si);
     }
+    // One workgroup alone, whose atomics would queue up at crowded bins (7 of
+    // 32 us for 4001 keys): a wave of whose first elements kCrowdLanes share the
+    // bin of one of two of them leaves its elements out, and if those waves
+    // are few their elements are counted after all.
+    constexpr int kCrowdLanes = 6;
+    bool out = false;
+    if constexpr (DIRECT) {
+      const uint32_t b = wd[0] >> bsh;
+      const uint64_t same = __ballot(b == lane_u32(b, 0) || b == lane_u32(b, 21));
+      out = __ballot(t < (int)len) == ~0ull && __popcll(same) >= kCrowdLanes;
+      if (out && lane_id() == 0) atomicAdd(&s_crowd, 1u);
+    }
 #pragma unroll
     for (int i = 0; i < ITEMS; i++) {
       rank[i] = 0;  // first the place in the bin
-      if (t < (int)len - i * THREADS) rank[i] = atomicAdd(&bin[wd[i] >> bsh], 1u);
+      if (t < (int)len - i * THREADS && !out) rank[i] = atomicAdd(&bin[wd[i] >> bsh], 1u);
     }
     if constexpr (!DIRECT) {
       if (fn.src) map.mark(t, t, fn.nt, rn.ofs, rn.c, 0u, fn.len, bal);
@@ -367,50 +520,69 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
     if constexpr (!DIRECT) {
       if (fn.src) map.number(t, t, rn.ofs, rn.e, 0u, w.tile_log2, bal);
     }
-    const bool rare = bins_scan<THREADS, BPT>(bin, len, s_tmp, t) > kRankBudget * len;  // uniform
-    if (rare) {
-      if constexpr (!DIRECT) {
+    bool many = false;  // uniform
+    if constexpr (DIRECT) {
+      const uint32_t waves = s_crowd;
+      many = waves * 4 * kWave >= min(len, (uint32_t)THREADS) && waves > 0;
+      if (!many && waves > 0) {
+#pragma unroll
+        for (int i = 0; i < ITEMS; i++)
+          if (t < (int)len - i * THREADS && out) rank[i] = atomicAdd(&bin[wd[i] >> bsh], 1u);
+        __syncthreads();
+      }
+    }
+    const uint32_t cost = many ? ~0u : bins_scan<THREADS, BPT>(bin, len, s_tmp, t);  // uniform
+    const uint32_t limit = DIRECT ? kRankTotal >> (sr ? 1 : 0) : min(kRankBudget * len, kRankTotal);
+    const bool crowded = many || cost > limit;
+    if (crowded) {
+      if constexpr (!PAIRS) {
         if (t == 0) {
           seg_at(q)->src = src | kPairsFlag;
           if (src) w.ctl->pairs_in[src - 1] = 1;
         }
-      } else if constexpr (N > kDirectPairs) {
-        if (t == 0) w.ctl->direct_rare = 1;
       } else {
-        sort_pairs<K, F32, PAY, THREADS, ITEMS>(w, f, LdsArr<K>{s_mem, s_mem + NP, s_mem + 2 * NP, nullptr}, in_keys,
-                                                in_pay, keys_out, perm_out, pay_out);
+        const LdsArr<K> sa{s_mem, s_mem + (KW - 1) * NP, s_mem + KW * NP, s_mem + (KW + 1) * NP};
+        constexpr int H = DIRECT && ITEMS <= 8 ? ITEMS / 2 : ITEMS;
+        if (H < ITEMS && len <= THREADS * H) {  // uniform
+          K k[H];
+          uint32_t v[H], y[H];
+#pragma unroll
+          for (int i = 0; i < H; i++) {
+            k[i] = key[i];
+            v[i] = idx[i];
+            if constexpr (PAY) y[i] = pay[i];
+          }
+          merge_pairs<K, PAY, THREADS, H>(k, v, y, len, sa);
+        } else {
+          merge_pairs<K, PAY, THREADS, ITEMS>(key, idx, pay, len, sa);
+        }
+        put_pairs<K, F32, PAY, THREADS>(sa, len, kout, pout, yout);
       }
     } else {
-#pragma unroll
-    for (int i = 0; i < ITEMS; i++)
-      if (t < (int)len - i * THREADS) fr[bin[wd[i] >> bsh] + rank[i]] = wd[i];
-    if (t < 3) fr[len + t] = ~0u;
-    __syncthreads();
-    // bin start and size of every element, then its rank
-#pragma unroll
-    for (int i = 0; i < ITEMS; i++) {
-      if (t < (int)len - i * THREADS) {
-        const uint32_t b = wd[i] >> bsh, s0 = bin[b];
-        rank[i] = ((bin[b + 1] - s0) << 16) | s0;
-      }
-    }
     uint32_t sum = 0;
+    if (cost <= kRankOwn * len) {  // uniform
 #pragma unroll
-    for (int i = 0; i < ITEMS; i++) {
-      if (t < (int)len - i * THREADS) {
-        const uint32_t* a = fr + (rank[i] & 0xFFFFu);
-        uint32_t n = rank[i] >> 16, less = 0;
-#pragma unroll 1
-        for (uint32_t k = 0; k < n; k += 4) {
-          const uint32_t x0 = a[k], x1 = a[k + 1], x2 = a[k + 2], x3 = a[k + 3];
-          less += x0 < wd[i] ? 1u : 0u;
-          less += x1 < wd[i] ? 1u : 0u;
-          less += x2 < wd[i] ? 1u : 0u;
-          less += x3 < wd[i] ? 1u : 0u;
+      for (int i = 0; i < ITEMS; i++)
+        if (t < (int)len - i * THREADS) fr[bin[wd[i] >> bsh] + rank[i]] = wd[i];
+      if (t < 3) fr[len + t] = ~0u;
+      __syncthreads();
+      // bin start and size of every element, then its rank
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++) {
+        if (t < (int)len - i * THREADS) {
+          const uint32_t b = wd[i] >> bsh, s0 = bin[b];
+          rank[i] = ((bin[b + 1] - s0) << 16) | s0;
         }
-        rank[i] = (rank[i] & 0xFFFFu) + less;
-        sum += rank[i];
       }
+#pragma unroll
+      for (int i = 0; i < ITEMS; i++) {
+        if (t < (int)len - i * THREADS) {
+          rank[i] = (rank[i] & 0xFFFFu) + count_below<true, 4>(fr + (rank[i] & 0xFFFFu), rank[i] >> 16, wd[i]);
+          sum += rank[i];
+        }
+      }
+    } else {
+      sum = rank_by_place<THREADS, ITEMS>(fr, bin, len, wd, bsh, rank, t);
     }
     const bool exact = sr == 0 && si == 0;  // uniform: words are distinct
     if (!exact) {
@@ -418,15 +590,18 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
       if (lane_id() == kWave - 1) atomicAdd(&s_sum, sum);
     }
     __syncthreads();  // every word read
-    if (!exact && s_sum != (uint32_t)(((uint64_t)len * (len - 1)) >> 1)) {
+    const uint32_t missing = exact ? 0u : (uint32_t)(((uint64_t)len * (len - 1)) >> 1) - s_sum;  // uniform
+    if (missing != 0) {
       // the bits of (d, x) below the word: those of d that were dropped (sr of
       // them), then x (all of it, or its low si bits)
-      rank_ties<THREADS, ITEMS>(
-          fr, bin, len, rank, sr ? 2 : 1,
-          [&](int round, int i) -> uint32_t {
-            return sr && round == 0 ? (uint32_t)(key[i] - mn) : idx[i] - imn;
-          },
-          t);
+      auto limb = [&](int round, int i) -> uint32_t {
+        return sr && round == 0 ? (uint32_t)(key[i] - mn) : idx[i] - imn;
+      };
+      constexpr int U = sizeof(K) == 8 && !DIRECT ? 2 : 4;
+      if (missing > kTiesOwn)
+        rank_ties<THREADS, ITEMS, U, true>(fr, bin, len, rank, sr ? 2 : 1, limb, t);
+      else
+        rank_ties<THREADS, ITEMS, U, false>(fr, bin, len, rank, sr ? 2 : 1, limb, t);
     }
     // into rank order and out; the last array's registers are free for the
     // next segment once it is staged
@@ -469,7 +644,7 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
     }
     __syncthreads();
     if (more) load(fn, t);
-    if (!rare) {
+    if (!crowded) {
 #pragma unroll
       for (int i = 0; i < ITEMS; i++) {
         const uint32_t j = i * THREADS + t;
@@ -509,18 +684,19 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
 // costs a search for every place.  A segment seldom has more than two chunks;
 // the searches (a chain of dependent loads) run for U elements at a time.
 template <typename K, bool F32, bool PAY, int THREADS, int ITEMS>
-__device__ __forceinline__ void sort_oversize(const Work& w, const FinalSeg& f, const LdsArr<K>& sa, const K* in_keys,
-                                              const uint32_t* in_pay, K* keys_out, uint32_t* perm_out,
-                                              uint32_t* pay_out) {
+__device__ __forceinline__ void sort_oversize(const Work& w, const FinalSeg& f, const LdsArr<K>& sa, void* map,
+                                              const K* in_keys, const uint32_t* in_pay, K* keys_out,
+                                              uint32_t* perm_out, uint32_t* pay_out) {
   using View = BufView<K, PAY>;
-  constexpr uint32_t C = THREADS * ITEMS;
+  // (the debug switch: smaller chunks, so that there are several)
+  const uint32_t C = f.len <= THREADS * ITEMS ? THREADS * ITEMS / 4 : THREADS * ITEMS;
   const SegReader<K, F32, PAY> rd{w, f, in_keys, in_pay};
   const bool own = f.src && uniform(w.ctl->pairs_in[(f.src - 1) ^ 1]) != 0;  // uniform
   const View b{w.buf_rec[f.src == 0 ? 0u : own ? f.src - 1 : (f.src - 1) ^ 1]};
   auto at = [&](uint32_t q) -> uint64_t { return own ? rd.at(q) : f.start + q; };
   for (uint32_t c0 = 0; c0 < f.len; c0 += C) {
     const uint32_t cnt = min(C, f.len - c0);
-    sort_stretch<K, F32, PAY, THREADS, ITEMS>(rd, c0, cnt, sa);
+    sort_stretch_fit<K, F32, PAY, THREADS, ITEMS>(rd, c0, cnt, sa, map);
     for (uint32_t j = threadIdx.x; j < cnt; j += THREADS) {
       const int q = lpad(j);
       b.put(at(c0 + j), sa.key(q), sa.v[q], PAY ? sa.p[q] : 0u);
@@ -568,15 +744,16 @@ __device__ __forceinline__ void sort_oversize(const Work& w, const FinalSeg& f, 
 
 // ---------------------------------------------------------------------------
 // What is left after all classes, in one resident-sized launch: the segments
-// k_local_rank handed over, of every class, by the merge sort of pairs, and
-// the segments longer than the LDS capacity (sort_oversize).  Each thread checks one
-// list entry and the marked ones are collected in LDS, so that the search is
-// parallel rather than a chain of dependent loads; the merge sort runs in the
-// smallest of three shapes that holds the segment.
+// k_local_rank handed over, of every class, by the merge sort of pairs, and the
+// segments longer than the LDS capacity (sort_oversize).  Each thread checks
+// one list entry and the marked ones are collected in LDS, so that the search
+// is parallel rather than a chain of dependent loads.  No register is spilled:
+// scratch memory for spills adds 4 to 6 us to a call, however empty the launch.
 template <typename K, bool F32, bool PAY, int THREADS, int ITEMS>
 __global__ __launch_bounds__(THREADS) void k_local_rare(Work w, const K* in_keys, const uint32_t* in_pay, K* keys_out,
-                                                        uint32_t* perm_out, uint32_t* pay_out, int direct) {
+                                                        uint32_t* perm_out, uint32_t* pay_out) {
   constexpr int NP = lpad_size(THREADS * ITEMS);
+  __shared__ RunMap<THREADS, THREADS * ITEMS> map;  // (large enough for every shape)
   __shared__ uint32_t s_lo[NP];
   __shared__ uint32_t s_hi[sizeof(K) == 8 ? NP : 1];
   __shared__ uint32_t s_v[NP];
@@ -584,12 +761,6 @@ __global__ __launch_bounds__(THREADS) void k_local_rare(Work w, const K* in_keys
   __shared__ uint32_t s_list[THREADS];
   __shared__ uint32_t s_n;
   const LdsArr<K> sa{s_lo, s_hi, s_v, s_p};
-  if (direct) {  // a plain call's whole input
-    if (w.ctl->direct_rare)
-      sort_pairs<K, F32, PAY, THREADS, ITEMS>(w, FinalSeg{0ull, 0ull, (uint32_t)w.n, 0u, 0u, 0u}, sa, in_keys, in_pay, keys_out,
-                                              perm_out, pay_out);
-    return;
-  }
   for (int c = 0; c <= kNumClasses - 2; c++) {
     const uint32_t cnt = final_count(w, c);
     // neighbouring entries go to different workgroups: marked segments
@@ -604,12 +775,10 @@ __global__ __launch_bounds__(THREADS) void k_local_rare(Work w, const K* in_keys
       for (uint32_t k = 0; k < n; k++) {
         FinalSeg f = w.cls[c][s_list[k]];
         f.src &= 0xFFu;
-        if (f.len <= THREADS * ITEMS / 4)
-          sort_pairs<K, F32, PAY, THREADS, ITEMS / 4>(w, f, sa, in_keys, in_pay, keys_out, perm_out, pay_out);
-        else if (f.len <= THREADS * ITEMS / 2)
-          sort_pairs<K, F32, PAY, THREADS, ITEMS / 2>(w, f, sa, in_keys, in_pay, keys_out, perm_out, pay_out);
-        else
-          sort_pairs<K, F32, PAY, THREADS, ITEMS>(w, f, sa, in_keys, in_pay, keys_out, perm_out, pay_out);
+        const SegReader<K, F32, PAY> rd{w, f, in_keys, in_pay};
+        sort_stretch_fit<K, F32, PAY, THREADS, ITEMS>(rd, 0, f.len, sa, &map);
+        put_pairs<K, F32, PAY, THREADS>(sa, f.len, keys_out + f.start, perm_out ? perm_out + f.start : nullptr,
+                                        PAY ? pay_out + f.start : nullptr);
       }
       __syncthreads();
     }
@@ -619,10 +788,7 @@ __global__ __launch_bounds__(THREADS) void k_local_rare(Work w, const K* in_keys
   const uint32_t cnt = final_count(w, kNumClasses - 1);
   for (uint32_t q = blockIdx.x; q < cnt; q += gridDim.x) {
     const FinalSeg f = w.cls[kNumClasses - 1][q];
-    if (f.len <= THREADS * ITEMS)  // (the debug switch: smaller chunks, so that there are several)
-      sort_oversize<K, F32, PAY, THREADS, ITEMS / 4>(w, f, sa, in_keys, in_pay, keys_out, perm_out, pay_out);
-    else
-      sort_oversize<K, F32, PAY, THREADS, ITEMS>(w, f, sa, in_keys, in_pay, keys_out, perm_out, pay_out);
+    sort_oversize<K, F32, PAY, THREADS, ITEMS>(w, f, sa, &map, in_keys, in_pay, keys_out, perm_out, pay_out);
   }
 }
 
@@ -634,8 +800,6 @@ static int direct_launch(const Work& w, const K* kin, K* kout, uint32_t* perm_ou
       "(k_local_rank<K, F32, PAY, " + std::to_string(T) + ", " + std::to_string(I) + ", true>)";
   RS_LAUNCH_TAGGED((k_local_rank<K, F32, false, T, I, 4, true>), tag.c_str(), 1, T, st, w, 1u, kin, nullptr, kout,
                    perm_out, nullptr);
-  if constexpr (T * I > kDirectPairs)
-    RS_LAUNCH((k_local_rare<K, F32, false, 768, 16>), 1, 768, st, w, kin, nullptr, kout, perm_out, nullptr, 1);
   return 0;
 }
 
@@ -688,15 +852,13 @@ int launch_local_ranks(uint32_t classes, const Work& w, const K* kin, const uint
     rc = rank_launch<K, F32, PAY, 512, 8, PAY ? 4 : 6>(classes & 0x38u, 12, w, kin, pay_in, kout, perm_out, pay_out,
                                                        st);
   if (!rc) rc = rank_launch<K, F32, PAY, 256, 4, 8>(classes & 0x04u, 16, w, kin, pay_in, kout, perm_out, pay_out, st);
-  if (!rc) rc = rank_launch<K, F32, PAY, 64, 4, 8>(classes & 0x03u, 32, w, kin, pay_in, kout, perm_out, pay_out, st);
+  if (!rc)  // (seven waves per SIMD where the pairs would spill registers at eight)
+    rc = rank_launch<K, F32, PAY, 64, 4, PAY || sizeof(K) == 8 ? 7 : 8>(classes & 0x03u, 32, w, kin, pay_in, kout,
+                                                                       perm_out, pay_out, st);
   if (rc) return rc;
-  if constexpr (PAY) {
-    RS_LAUNCH((k_local_rare<K, F32, PAY, 1024, 8>), grid_for(1u << 30, 1), 1024, st, w, kin, pay_in, kout, perm_out,
-              pay_out, 0);
-  } else {
-    RS_LAUNCH((k_local_rare<K, F32, PAY, 768, 16>), grid_for(1u << 30, 1), 768, st, w, kin, pay_in, kout, perm_out,
-              pay_out, 0);
-  }
+  constexpr int T = PAY ? 1024 : 768;
+  RS_LAUNCH((k_local_rare<K, F32, PAY, T, PAY ? 8 : 16>), grid_for(1u << 30, 1), T, st, w, kin, pay_in, kout,
+            perm_out, pay_out);
   return 0;
 }
 
