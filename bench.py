@@ -58,8 +58,9 @@ def load_traffic(name: str = "traffic.json"):
 def kernel_key(name: str) -> str:
     """Normalise a launch tag "(k_split<K, F32, true, PAY, 1024, 8>)" or a
     profiler name "rs::k_split<unsigned long, false, true, false, 1024, 8>(...)"
-    to "k_split/l1/1024/8" (the split kernels carry their level) or
-    "k_local_rank/512/8"."""
+    to "k_split/l1/1024/8" (the split kernels carry their level, and "tiled" for
+    the form by tile thresholds) or "k_local_rank/512/8" (its workgroup shape;
+    "direct" for the one-workgroup plain calls; tags leave its occupancy out)."""
     import re
 
     m = re.search(r"(k_[a-z_0-9]+)\s*<([^>]*)>", name)
@@ -71,7 +72,28 @@ def kernel_key(name: str) -> str:
     parts = [base]
     if base in ("k_split", "k_splitters") and len(args) > 2:
         parts.append("l1" if args[2] == "true" else "l2")
+    if base == "k_split" and len(args) == 7 and args[6] == "true":
+        parts.append("tiled")
+    if base == "k_splitters":
+        nums = []  # (one shape, which its tag names by constants)
+    if base == "k_local_rank":
+        nums = nums[:2]
+        if args[-1] == "true":
+            parts.append("direct")
     return "/".join(parts + nums)
+
+
+def measured_bytes(traffic: dict, timing: dict, names, calls: int):
+    """Measured HBM bytes per call of the kernels of a pass (launch tags; timing:
+    tag -> (launches, ms) over `calls` calls), or None if one of them is not
+    among the profiled ones."""
+    total = 0.0
+    for name in names:
+        k = traffic["kernels"].get(kernel_key(name))
+        if k is None:
+            return None
+        total += k["hbm_bytes_per_launch"] * timing[name][0] / calls
+    return total
 
 
 def kernel_class(name: str) -> str:
@@ -238,11 +260,7 @@ def bench_plain(args, R, torch):
             if traffic:
                 # measured HBM bytes per sort (rocprofv3 FETCH_SIZE + WRITE_SIZE of
                 # every kernel of the pass) over the pass's algorithmic bytes
-                meas = 0.0
-                for k in a["kernels"]:
-                    kk = kernel_key(k)
-                    if kk in traffic["kernels"]:
-                        meas += traffic["kernels"][kk]["hbm_bytes_per_launch"] * timing[k][0] / args.steps
+                meas = measured_bytes(traffic, timing, a["kernels"], args.steps)
                 e["traffic_ratio"] = round(meas / (bpk[c] * n), 3) if meas else None
         passes[c] = e
     # dominant single kernel (by total time)
@@ -385,8 +403,7 @@ def bench_batched(args, R, torch):
             if traffic:
                 # measured HBM bytes per call of the pass's kernels (rocprofv3
                 # FETCH_SIZE + WRITE_SIZE) over its algorithmic bytes
-                meas = sum(traffic["kernels"][kernel_key(k)]["hbm_bytes_per_launch"] * timing[k][0] / calls
-                           for k in timing if kernel_class(k) == c and kernel_key(k) in traffic["kernels"])
+                meas = measured_bytes(traffic, timing, [k for k in timing if kernel_class(k) == c], calls)
                 e["traffic_ratio"] = round(meas / pass_bytes[c], 3) if meas else None
         passes[c] = e
     return {

@@ -856,9 +856,12 @@ int launch_local_ranks(uint32_t classes, const Work& w, const K* kin, const uint
     rc = rank_launch<K, F32, PAY, 64, 4, PAY || sizeof(K) == 8 ? 7 : 8>(classes & 0x03u, 32, w, kin, pay_in, kout,
                                                                        perm_out, pay_out, st);
   if (rc) return rc;
-  constexpr int T = PAY ? 1024 : 768;
-  RS_LAUNCH((k_local_rare<K, F32, PAY, T, PAY ? 8 : 16>), grid_for(1u << 30, 1), T, st, w, kin, pay_in, kout,
-            perm_out, pay_out);
+  if constexpr (PAY)
+    RS_LAUNCH((k_local_rare<K, F32, PAY, 1024, 8>), grid_for(1u << 30, 1), 1024, st, w, kin, pay_in, kout, perm_out,
+              pay_out);
+  else
+    RS_LAUNCH((k_local_rare<K, F32, PAY, 768, 16>), grid_for(1u << 30, 1), 768, st, w, kin, pay_in, kout, perm_out,
+              pay_out);
   return 0;
 }
 
