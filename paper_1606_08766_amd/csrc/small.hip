@@ -148,7 +148,7 @@ int launch_rfis_class(int c, const Work& w, const K* kin, const uint32_t* pay_in
       RS_LAUNCH((k_rfis<K, F32, PAY, 256, 1024>), g2, 256, st, w, ca, kin, pay_in, kout, perm_out, pay_out);
       break;
     default:
-      return -3;  // not this algorithm's class (small_class_algo)
+      return -3;  // not this algorithm's class (class_algo)
   }
   return 0;
 }
@@ -234,9 +234,21 @@ __global__ __launch_bounds__(THREADS) void k_rquick(Work w, int cls, const K* in
     const SegReader<K, F32, PAY> rd{w, f, in_keys, in_pay};
     const uint32_t n = f.len;
     const uint64_t rstream = f.start * 0x9E3779B97F4A7C15ull + 0x52515549434Bull;
-    // stage the input in buffer 1 (coalesced)
-    for (uint32_t j = threadIdx.x; j < n; j += THREADS) {
-      rd.get(j, bk[1][j], bv[1][j]);
+    // stage the input in buffer 1 (coalesced, four elements of a thread at a
+    // time: those of a bucket are looked up by a chain of loads each)
+    for (uint32_t j0 = threadIdx.x; j0 < n; j0 += 4 * THREADS) {
+      uint32_t j[4], v[4], y[4];
+      K k[4];
+#pragma unroll
+      for (int u = 0; u < 4; u++) j[u] = min(j0 + u * THREADS, n - 1);
+      rd.get_all(j, k, v, y);
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        if (j0 + u * THREADS < n) {
+          bk[1][j[u]] = k[u];
+          bv[1][j[u]] = v[u];
+        }
+      }
     }
     if (threadIdx.x < P) {
       off[threadIdx.x] = (uint32_t)((uint64_t)threadIdx.x * n / P);
@@ -432,7 +444,7 @@ int launch_rquick_class(int c, const Work& w, const K* kin, const uint32_t* pay_
                 seed);
       break;
     default:
-      return -3;  // not this algorithm's class (small_class_algo)
+      return -3;  // not this algorithm's class (class_algo)
   }
   return 0;
 }
