@@ -134,14 +134,19 @@ __device__ __forceinline__ void put_pairs(const LdsArr<K>& sa, uint32_t len, K* 
 // words by place).
 //
 // A segment whose ranking would take more than kRankBudget compares per element
-// or kRankTotal in all (most keys clustered far apart from others) is marked
-// kPairsFlag and left to the merge sort of k_local_rare.  Where LDS and
-// registers allow it, it is merge sorted on the spot instead: by the one-wave
-// workgroups (16384 rows of 256 f32 keys, as many of every magnitude, took 1115
-// us when handed over, 92 so) and for a plain call's only workgroup, which
-// gives up at half of kRankTotal if the words drop key bits, as every compare is
-// then made twice (12000 u64 keys in 300 clusters: 88 us ranked, 72 merge
-// sorted).
+// or kRankTotal in all, half of it if the words drop key bits (most keys
+// clustered far apart from others), is marked kPairsFlag and left to the merge
+// sort of k_local_rare.  Half of kRankTotal for all would hand over the segments
+// of few values that many elements share (3145728 u64 keys below 16: 112 us as
+// it is, 174 so), and all of it for all would rank rows with a shared key
+// (2000 of 8000 u64 keys, 10 % of them 0: 657 us as it is, 795 so).
+// Where LDS and registers allow it, a segment is merge sorted on the spot
+// instead: by the one-wave workgroups (16384 rows of 256 f32 keys, as many of
+// every magnitude, took 1115 us when handed over, 92 so) and for a plain call's
+// only workgroup, which has nothing to hand over to and gives up at a third of
+// kRankBudget, or a fifth if the words drop key bits, as every compare is then
+// made twice (12000 u64 keys in 300 clusters: 88 us ranked, 72 merge sorted;
+// 4001 with 10 % of them 0: 41, 30).
 //
 // Few distinct keys need no case of their own: d then has few bits and the
 // bins go on with the position.
@@ -150,7 +155,7 @@ __device__ __forceinline__ void put_pairs(const LdsArr<K>& sa, uint32_t len, K* 
 // and HBM.  Hence 32-bit words computed once, one bin per element (few
 // compares), and element minima by their upper halves first.  LDS is 8 B per
 // element: words and bins share the memory of the staging area.
-constexpr uint32_t kRankBudget = 128, kRankTotal = 1u << 19;  // compares: per element, in all
+constexpr uint32_t kRankBudget = 128, kRankTotal = 1u << 20;  // compares: per element, in all
 constexpr uint32_t kRankOwn = 4, kTiesOwn = 1024;
 
 // Exclusive scan of the THREADS * BPT bin counts in place (bin is 16-byte
@@ -497,15 +502,18 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
         wd[i] = ((rb ? (uint32_t)(key[i] - mn) : 0u) << (sl & 31)) | ((idx[i] - imn) >> si);
     }
     // One workgroup alone, whose atomics would queue up at crowded bins (7 of
-    // 32 us for 4001 keys): a wave of whose first elements kCrowdLanes share the
+    // 32 us for 4001 keys): a wave of whose first elements crowd_lanes share the
     // bin of one of two of them leaves its elements out, and if those waves
-    // are few their elements are counted after all.
-    constexpr int kCrowdLanes = 6;
+    // are few their elements are counted after all.  More lanes where the words
+    // hold all key bits: with 6, 12000 u64 keys below 16, which rank well, were
+    // merge sorted (26 us, 74 so); with 16, 250 keys of 16 values spread over
+    // the type were ranked (9.4 us, 12.4 so).
+    const int crowd_lanes = sr ? 6 : 16;
     bool out = false;
     if constexpr (DIRECT) {
       const uint32_t b = wd[0] >> bsh;
       const uint64_t same = __ballot(b == lane_u32(b, 0) || b == lane_u32(b, 21));
-      out = __ballot(t < (int)len) == ~0ull && __popcll(same) >= kCrowdLanes;
+      out = __ballot(t < (int)len) == ~0ull && __popcll(same) >= crowd_lanes;
       if (out && lane_id() == 0) atomicAdd(&s_crowd, 1u);
     }
 #pragma unroll
@@ -532,7 +540,8 @@ __global__ __launch_bounds__(THREADS, WPE) void k_local_rank(Work w, uint32_t cl
       }
     }
     const uint32_t cost = many ? ~0u : bins_scan<THREADS, BPT>(bin, len, s_tmp, t);  // uniform
-    const uint32_t limit = DIRECT ? kRankTotal >> (sr ? 1 : 0) : min(kRankBudget * len, kRankTotal);
+    const uint32_t limit = min((!DIRECT ? kRankBudget : sr ? kRankBudget / 5 : kRankBudget / 3) * len,
+                               sr ? kRankTotal / 2 : kRankTotal);
     const bool crowded = many || cost > limit;
     if (crowded) {
       if constexpr (!PAIRS) {

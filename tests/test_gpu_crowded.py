@@ -118,3 +118,36 @@ def test_shared_keys_take_little_longer(rows, length):
     uniform = ms(dev(x))
     shared = ms(dev(np.where(rng.random(n) < 0.1, np.uint64(0), x)))
     assert shared < 8 * uniform, (uniform, shared)
+
+
+@pytest.mark.parametrize("kt", ["u64", "u32"])
+@pytest.mark.parametrize("n,most", [(12_000, 2.5), (3_145_728, 1.35)])
+def test_few_values_rank(kt, n, most):
+    """Keys below 16 are ranked and not merge sorted: 1.7 times as long as uniform
+    ones where one workgroup sorts them all (4.6 when it merge sorted them), 1.1
+    times at 3145728 u64 keys (1.65 when their segments were handed over); the
+    bounds lie between."""
+    rng = np.random.default_rng(7)
+    dt = np.uint64 if kt == "u64" else np.uint32
+    x = rng.integers(0, 1 << (63 if kt == "u64" else 31), n, dtype=np.uint64).astype(dt)
+    few = rng.integers(0, 16, n).astype(dt)
+    ek, ep, _ = O.sort(few)
+    ko, po = gpu_sort(few)
+    assert same_bits(ko, ek) and np.array_equal(po, ep)
+
+    def ms(t):
+        for _ in range(20):
+            R.sort(t)
+        torch.cuda.synchronize()
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(50):
+            R.sort(t)
+        b.record()
+        torch.cuda.synchronize()
+        return a.elapsed_time(b) / 50
+
+    banner("time of uniform keys and of keys of few values")
+    uniform, shared = ms(dev(x)), ms(dev(few))
+    print(n, kt, uniform, shared, flush=True)
+    assert shared < most * uniform, (uniform, shared)
